@@ -153,9 +153,10 @@ int potts_sweep_heatbath_thr(potts_state *s, const uint32_t thr[4], int64_t nswe
  * lattice in LDS and runs all sweeps of a call in one launch), 4 = the
  * colour-split kernel (L % 32 == 0, L <= 65520: a call copies the lattice into
  * two colour planes in the second buffer, sweeps there and copies it back;
- * the automatic choice for such L above 2048 that kernel 7 does not take),
- * 5 = the multi-sweep tile kernel (L % 16 == 0, L <= 65520; the automatic
- * choice for 256 < L <= 2048 that kernel 7 does not take: each
+ * the automatic choice for such L above 3584 that kernel 7 does not take),
+ * 5 = the multi-sweep tile kernel (to be asked for, L % 16 == 0 and L <=
+ * 65520; the automatic choice, for any L, up to 3584 where kernel 6 does not
+ * take it, outside stream capture: each
  * launch runs several sweeps, one LDS tile
  * per workgroup whose halo is recomputed, and moves the row-major lattice
  * between the state's two buffers; with library-owned buffers they trade
@@ -168,7 +169,7 @@ int potts_sweep_heatbath_thr(potts_state *s, const uint32_t thr[4], int64_t nswe
  * them instead of computing them; the automatic choice for such L),
  * 7 = persistent sweeps on LDS bands (L % 32 == 0, L <= 16384, a band shape
  * from potts_tune_band whose grid the GPU holds at once; the automatic choice
- * for 2048 <= L <= 4096 when it can take the lattice): each workgroup keeps
+ * for 3584 < L <= 4096 when it can take the lattice): each workgroup keeps
  * a band of whole rows of the colour-split lattice in LDS for up to 64 sweeps
  * per cooperative launch and trades its two edge rows with the neighbouring
  * bands after every half sweep (an exchange buffer of 2 x L x L / rows bytes,
@@ -184,11 +185,11 @@ int potts_tune(potts_state *s, int32_t kernel, int32_t strip_rows, int32_t max_g
 
 /* Shape of the multi-sweep tile kernel (kernel 5): tiles of tx bytes (a
  * multiple of 16 dividing L) by ty rows (even, dividing L), `sweeps` sweeps
- * per launch (1..8; the tile reads 2 x sweeps halo rows above and below and
- * 16 halo bytes left and right, and one tile with its halo must fit in
- * 44 KiB of LDS); 0 for any of them = automatic (tx: the largest of 256 ..
- * 16 up to L/8 dividing L, ty: 16 rows up to L = 1024 and 32 above, or the
- * largest even divisor below, 4 sweeps).  Results never depend on it.
+ * per launch (1..8; the tile reads 2 x sweeps halo rows above and below, at
+ * most L); (ty + 4 sweeps) x (tx + 64) must stay within 44 KiB.  0 for all =
+ * automatic, by the length of each call; 0 for some of them = tx: the largest
+ * of 256 .. 16 up to L/8 dividing L, ty: 16 rows up to L = 1024 and 32 above,
+ * or the largest even divisor below, 4 sweeps.  Results never depend on it.
  * Errors: EINVAL (a shape the lattice cannot take; the old one is kept). */
 int potts_tune_tiles(potts_state *s, int32_t tx, int32_t ty, int32_t sweeps);
 

@@ -39,8 +39,8 @@
 // Records: the colour-0 pass counts the band's new colour-0 values, the
 // colour-1 pass its new colour-1 values and the differing neighbours of its
 // colour-1 sites (every bond once); per sweep the workgroup adds them into
-// partial-record set s (striped by workgroup), folded into ring slot t0 + s
-// after the launch as for the tile kernel.
+// partial-record set s (striped by workgroup), which fold_sets_kernel turns
+// into the ring slot of sweep t0 + s after the launch.
 #include <hip/hip_runtime.h>
 
 #include "device.hpp"
@@ -318,6 +318,30 @@ __global__ __launch_bounds__(BLOCK) void band_kernel(BandParams p) {
   }
 }
 
+// Set s of the partial records (nstripes stripes) summed into ring slot
+// t0 + s, then cleared; one workgroup per set.
+constexpr int kFoldBlock = 256;
+
+__global__ __launch_bounds__(kFoldBlock) void fold_sets_kernel(BandParams p, unsigned long long *ring, uint64_t cap) {
+  __shared__ unsigned long long acc[257];
+  const uint32_t s = blockIdx.x;
+  const uint32_t n = p.q + 1, sw = stripe_words(p.q), total = p.nstripes * n;
+  unsigned long long *set = p.stripes + (uint64_t)s * p.nstripes * sw;
+  unsigned long long *slot = ring + ((p.t0 + s) & (cap - 1)) * (uint64_t)n;
+  for (uint32_t i = threadIdx.x; i < n; i += kFoldBlock) acc[i] = 0;
+  __syncthreads();
+  for (uint32_t k = threadIdx.x; k < total; k += kFoldBlock) {
+    const uint32_t st = k / n, i = k - st * n;
+    const unsigned long long v = set[st * sw + i];
+    if (v) {
+      atomicAdd(&acc[i], v);
+      set[st * sw + i] = 0;
+    }
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < n; i += kFoldBlock) slot[i] = acc[i];
+}
+
 template <int CMP, bool PRIV, bool WIDE, int BLOCK>
 const void *kernel_of() {
   return reinterpret_cast<const void *>(&band_kernel<CMP, PRIV, WIDE, BLOCK>);
@@ -392,6 +416,12 @@ hipError_t launch_band(const BandParams &p, uint32_t block, hipStream_t stream) 
   BandParams arg = p;
   void *args[] = {&arg};
   return hipLaunchCooperativeKernel(k, dim3(p.bands), dim3(block), args, (unsigned)lds, stream);
+}
+
+hipError_t launch_fold_sets(const BandParams &p, unsigned long long *ring, uint64_t cap, hipStream_t stream) {
+  if (p.nsweeps == 0) return hipSuccess;
+  hipLaunchKernelGGL(fold_sets_kernel, dim3(p.nsweeps), dim3(kFoldBlock), 0, stream, p, ring, cap);
+  return hipGetLastError();
 }
 
 }  // namespace potts

@@ -13,8 +13,9 @@ namespace potts {
 // rows b*rows .. b*rows + rows - 1 of both colour planes of a packed L x L
 // lattice (L % 32 == 0) in LDS for nsweeps <= kBandMaxSweeps sweeps and
 // trades its edge rows with bands b-1 and b+1 (mod bands) through xbuf and
-// flags.  The record of sweep t0 + s is added into partial-record set s as
-// for the tile kernel (launch_fold_sets).
+// flags.  The record of sweep t0 + s is added into partial-record set s
+// (nstripes stripes of stripe_words(q) words, set s at stripes + s x nstripes
+// x stripe_words(q)), which launch_fold_sets sums into ring slot t0 + s.
 constexpr uint32_t kBandMaxSweeps = 64;
 constexpr size_t kBandMaxLds = 136u * 1024u;   // dynamic LDS of one band (static LDS up to 20 KB)
 
@@ -43,5 +44,6 @@ bool band_shape_ok(uint32_t L, uint32_t rows, uint32_t block);
 // whether a grid of L / rows workgroups of `block` lanes can be resident at once
 hipError_t band_resident(uint32_t L, uint32_t q, uint32_t rows, uint32_t block, bool *fits);
 hipError_t launch_band(const BandParams &p, uint32_t block, hipStream_t stream);
+hipError_t launch_fold_sets(const BandParams &p, unsigned long long *ring, uint64_t cap, hipStream_t stream);
 
 }  // namespace potts

@@ -15,6 +15,7 @@
 #include "drawn.hpp"
 #include "band.hpp"
 #include "kernels.hpp"
+#include "tiles.hpp"
 
 struct potts_state {
   int32_t L = 0, q = 0;
@@ -61,9 +62,10 @@ struct potts_state {
   int32_t g_K = 0;
   bool g_wide = false;
   // several sweeps per launch on LDS tiles (tiles.hip): the shape asked for
-  // (0 = automatic) and the partial records of a launch's sweeps
+  // (0 = automatic) and the totals of two launches
   uint32_t tile_tx = 0, tile_ty = 0, tile_sweeps = 0;
-  unsigned long long *tstripes = nullptr;
+  uint32_t *tparts = nullptr;
+  size_t tparts_words = 0;
   // pre-drawn random words of a chunk of sweeps (drawn.hpp), allocated on first use
   uint32_t *drawn = nullptr;
   // persistent sweeps on LDS bands (band.hip): the shape asked for (0 =
@@ -151,7 +153,7 @@ void release(potts_state *s) {
   if (s->g_desc) (void)hipFree(s->g_desc);
   if (s->g_tiles) (void)hipFree(s->g_tiles);
   if (s->hb_dev) (void)hipFree(s->hb_dev);
-  if (s->tstripes) (void)hipFree(s->tstripes);
+  if (s->tparts) (void)hipFree(s->tparts);
   if (s->drawn) (void)hipFree(s->drawn);
   if (s->bxbuf) (void)hipFree(s->bxbuf);
   if (s->bflags) (void)hipFree(s->bflags);
@@ -278,6 +280,7 @@ bool drawn_ok(const potts_state *s) { return potts::drawn_fits((uint32_t)s->L, (
 
 bool use_drawn(const potts_state *s) { return drawn_ok(s) && (s->kernel == 6 || s->kernel == 0); }
 
+// kernel 0: under stream capture, where the tiles leave it to this kernel
 bool use_resident(const potts_state *s) {
   return resident_ok(s) && (s->kernel == 3 || s->kernel == 6 || s->kernel == 0);
 }
@@ -288,44 +291,69 @@ bool packed_ok(const potts_state *s) { return strip_ok(s) && s->L % 32 == 0; }
 bool auto_tiles(const potts_state *s);
 
 bool use_packed(const potts_state *s) {
-  return packed_ok(s) && (s->kernel == 4 || (s->kernel == 0 && !auto_tiles(s)));
+  return packed_ok(s) && (s->kernel == 4 || (s->kernel == 0 && !auto_tiles(s) && !drawn_ok(s)));
 }
 
 bool use_strip(const potts_state *s) { return strip_ok(s) && (s->kernel == 1 || s->kernel == 0); }
 
-// The tile shape (interior tx bytes x ty rows, sweeps per launch) of the
-// multi-sweep tile kernel: the one asked for, else about 256-512 tiles per
-// lattice (tx the largest of 256 .. 16 bytes up to L/8 dividing L, ty 16 rows
-// up to L = 1024 and 32 above, or the largest even divisor below), 4 sweeps
-// per launch.  Measured on MI355X (q = 6, ps per site update): L = 512 64x16
-// 16.9 (128x16 21.6, 256x32 32.6), L = 1024 128x16 6.1 (64x16 6.4, 256x32
-// 8.3), L = 2048 256x32 2.67 (256x64 with 8 sweeps 3.05, 128x16 3.64).
-bool tile_shape(const potts_state *s, uint32_t *tx, uint32_t *ty, uint32_t *sweeps) {
+// The shapes potts_tune_tiles takes: tx a multiple of 16 and ty even, both
+// dividing L, and (ty + 4 sweeps) x (tx + 64) within 44 KiB.
+bool tile_choice_ok(uint32_t L, uint32_t tx, uint32_t ty, uint32_t sweeps) {
+  const uint32_t halo = 2u * sweeps;
+  return L % 16 == 0 && tx >= 16 && tx % 16 == 0 && L % tx == 0 && ty >= 2 && ty % 2 == 0 && L % ty == 0 && halo >= 2 &&
+         halo <= 2u * potts::kTileMaxSweeps && halo <= L && (uint64_t)(ty + 2u * halo) * (tx + 64u) <= 44u * 1024u;
+}
+
+// The tile shape of the multi-sweep tile kernel: the one asked for (what is
+// left open: tx the largest of 256 .. 16 bytes up to L/8 dividing L, ty 16
+// rows up to L = 1024 and 32 above, or the largest even divisor below, 4
+// sweeps per launch), else the automatic one for a call of nsweeps sweeps.
+bool tile_shape(const potts_state *s, int64_t nsweeps, potts::TileParams *p) {
   const uint32_t L = (uint32_t)s->L;
-  *sweeps = s->tile_sweeps ? s->tile_sweeps : 4u;
-  *tx = s->tile_tx;
-  *ty = s->tile_ty;
-  for (uint32_t c = 256; !*tx && c >= 16; c /= 2)
-    if (L % c == 0 && (c * 8 <= L || c == 16)) *tx = c;
-  for (uint32_t c = L <= 1024 ? 16u : 32u; !*ty && c >= 2; c /= 2)
-    if (L % c == 0) *ty = c;
-  return *tx && *ty && potts::tile_shape_ok(L, *tx, *ty, 2u * *sweeps);
+  p->L = L;
+  p->q = (uint32_t)s->q;
+  uint32_t n = s->tile_sweeps, tx = s->tile_tx, ty = s->tile_ty;
+  if (n || tx || ty) {
+    if (!n) n = 4;
+    for (uint32_t c = 256; !tx && c >= 16; c /= 2)
+      if (L % c == 0 && (c * 8 <= L || c == 16)) tx = c;
+    for (uint32_t c = L <= 1024 ? 16u : 32u; !ty && c >= 2; c /= 2)
+      if (L % c == 0) ty = c;
+    return tile_choice_ok(L, tx, ty, n) && potts::set_tile_shape(*p, tx, ty, n);
+  }
+  return potts::auto_tile_shape(*p, nsweeps);
 }
 
 bool tiles_ok(const potts_state *s) {
-  uint32_t tx, ty, n;
-  return s->L % 16 == 0 && s->L <= 65520 && tile_shape(s, &tx, &ty, &n);
+  potts::TileParams p{};
+  return s->L <= (int32_t)potts::kTileMaxL && tile_shape(s, 1, &p);
 }
 
-// the automatic choice for lattices too large for one workgroup's LDS and too
-// small for a half sweep to hide a kernel boundary: the colour-split kernel
-// runs L = 512 / 1024 / 2048 at 48.7 / 12.2 / 3.47 ps per site update, the
-// tiles at 16.9 / 6.1 / 2.67; from L = 4096 (1.64 against 1.86) the halo work
-// costs more than the launches it saves
-bool auto_tiles(const potts_state *s) { return s->L > 256 && s->L <= 2048 && tiles_ok(s); }
+// the automatic choice for lattices too large for pre-drawn words and too
+// small for a half sweep to hide a kernel boundary.  Measured on MI355X (q = 6,
+// us per sweep, 200 sweeps a call; in brackets what else takes the size): L =
+// 100 1.6 (one launch per half sweep 5.6), 256 1.6 (LDS-resident 21.9), 512
+// 1.8 (colour-split 12.1), 1000 3.2 (chunk 29.8), 1024 3.2 (colour-split
+// 12.0), 2048 7.0 (bands 8.0), 2560 10.4 (bands 16.9), 3584 18.2 (bands 19.8);
+// at L = 4096 the bands win, 18.0 against 21.7.
+bool auto_tiles(const potts_state *s) { return !drawn_ok(s) && s->L <= 3584; }
+
+// Whether the state's stream is being captured into a graph.  There the sizes
+// that the tiles took over stay with the kernels that work in place and
+// allocate nothing.
+bool capturing(const potts_state *s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s->stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st == hipStreamCaptureStatusActive;
+}
 
 bool use_tiles(const potts_state *s) {
-  return tiles_ok(s) && (s->kernel == 5 || (s->kernel == 0 && !use_resident(s) && auto_tiles(s)));
+  if (s->kernel == 5) return tiles_ok(s);
+  if (s->kernel != 0 || !auto_tiles(s)) return false;
+  return !capturing(s) || (s->L > 256 && s->L < 2048 && s->L % 16 == 0);
 }
 
 bool wide_table(const uint32_t thr[4]) { return !thr[0] || !thr[1] || !thr[2] || !thr[3]; }
@@ -379,13 +407,12 @@ bool band_ok(potts_state *s) {
   return s->L % 32 == 0 && s->L <= 16384 && band_shape(s, &rows, &block);
 }
 
-// The automatic choice for L = 2048 .. 4096: measured on MI355X (q = 6, ps
-// per site update), L = 2048 2.06 (8-row bands of 512 lanes; the tile kernel
-// 2.68), L = 4096 1.08 (16-row bands of 1024 lanes; the colour-split kernel
-// 1.64).  At L = 1024 the tile kernel stays ahead (6.1 against 9.1: a half
-// sweep there is shorter than the exchange of edge rows), and from L = 8192
-// no band of whole rows whose grid the GPU holds at once fits in LDS.
-bool auto_band(potts_state *s) { return s->L >= 2048 && s->L <= 4096 && band_ok(s); }
+// The automatic choice for 3584 < L <= 4096: L = 4096 takes 18.0 us per sweep
+// (q = 6; the colour-split kernel 27.0, the tile kernel 21.7).  Below, the
+// exchange of edge rows (4 us per half sweep, whatever the size) costs more
+// than the tiles' halos, and from L = 8192 no band of whole rows whose grid
+// the GPU holds at once fits in LDS.
+bool auto_band(potts_state *s) { return s->L > 3584 && s->L <= 4096 && band_ok(s); }
 
 bool use_band(potts_state *s) { return s->kernel == 7 ? band_ok(s) : s->kernel == 0 && auto_band(s); }
 
@@ -658,48 +685,61 @@ int run_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
 }
 
 // Sweeps on LDS tiles, several per launch (tiles.hip), ping-ponging the
-// row-major lattice between the state's two buffers; each launch's records
-// are folded into their ring slots right after it.
+// row-major lattice between the state's two buffers; each launch folds the
+// records of the one before it.
 int run_tiles(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
-  uint32_t tx, ty, per;
-  if (!tile_shape(s, &tx, &ty, &per)) return fail(POTTS_EINVAL, "no tile shape for this lattice");
-  const uint32_t sw = potts::stripe_words((uint32_t)s->q);
-  const uint64_t words = (uint64_t)potts::kTileMaxSweeps * kStripes * sw;
-  if (!s->tstripes) {
-    if (hipMalloc(&s->tstripes, words * sizeof(unsigned long long)) != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(POTTS_ENOMEM, "allocation of the tile partial records failed");
-    }
-    HIP_TRY(potts::launch_fill_u64(s->tstripes, words, 0ull, s->stream));
-  }
-  s->planes_valid = false;  // the second buffer now holds row-major lattices
   potts::TileParams p{};
-  p.L = (uint32_t)s->L;
-  p.q = (uint32_t)s->q;
+  if (!tile_shape(s, nsweeps, &p)) return fail(POTTS_EINVAL, "no tile shape for this lattice");
+  const uint32_t ntiles = p.tiles_x * p.tiles_y, nparts = potts::tile_parts(ntiles);
+  const size_t words = (size_t)p.sweeps * nparts * (p.q + 1u);
+  if (2 * words > s->tparts_words) {
+    if (s->tparts) (void)hipFree(s->tparts);
+    s->tparts = nullptr;
+    s->tparts_words = 0;
+    if (hipMalloc(&s->tparts, 2 * words * sizeof(uint32_t)) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(POTTS_ENOMEM, "allocation of the tile totals failed");
+    }
+    s->tparts_words = 2 * words;
+  }
+  // parts that tiles share are added to
+  if (nparts < ntiles)
+    HIP_TRY(potts::launch_fill_u64(reinterpret_cast<unsigned long long *>(s->tparts), words, 0ull, s->stream));
+  s->planes_valid = false;  // the second buffer now holds row-major lattices
   p.k0 = (uint32_t)s->seed;
   p.k1 = (uint32_t)(s->seed >> 32);
   for (int i = 0; i < 4; ++i) p.thr.v[i] = thr[i];
-  p.tx = tx;
-  p.ty = ty;
-  p.halo = 2u * per;
-  p.tiles_x = p.L / tx;
-  p.stripes = s->tstripes;
-  p.nstripes = kStripes;
+  potts::TileFold last{};
+  last.q = p.q;
+  last.nparts = nparts;
+  last.shared = nparts < ntiles;
+  last.ring = s->records;
+  last.cap = (uint64_t)s->rec_cap;
+  last.bonds = 2ull * n_sites(s);
+  // the records of one launch go to ring slots of their own
+  const int64_t per = std::min<int64_t>(p.sweeps, s->rec_cap);
   uint8_t *cur = s->spins, *other = s->spins2;
-  for (int64_t done = 0; done < nsweeps; done += per) {
+  uint32_t turn = 0;
+  for (int64_t done = 0; done < nsweeps; done += per, turn ^= 1u) {
     p.nsweeps = (uint32_t)std::min<int64_t>(per, nsweeps - done);
     p.t0 = (uint64_t)(s->t + done);
     p.src = cur;
     p.dst = other;
+    p.parts = s->tparts + turn * words;
+    p.fold = last;
     HIP_TRY(potts::launch_tiles(p, s->stream));
-    HIP_TRY(potts::launch_fold_sets(p, s->records, (uint64_t)s->rec_cap, s->stream));
+    last.parts = p.parts;
+    last.t0 = p.t0;
+    last.nsweeps = p.nsweeps;
     std::swap(cur, other);
   }
+  HIP_TRY(potts::launch_tile_fold(last, s->stream));
   if (cur != s->spins) {
-    if (s->owns_spins) {
+    if (s->owns_spins && !capturing(s)) {
       std::swap(s->spins, s->spins2);  // library-owned: the buffers trade roles
     } else {
-      // the caller's buffer holds the lattice after every call
+      // the caller's buffer holds the lattice after every call, and a graph's
+      // replay ends where the next one starts
       HIP_TRY(hipMemcpyAsync(s->spins, cur, (size_t)n_sites(s), hipMemcpyDeviceToDevice, s->stream));
     }
   }
@@ -805,10 +845,6 @@ int run_band(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   p.k1 = (uint32_t)(s->seed >> 32);
   for (int i = 0; i < 4; ++i) p.thr.v[i] = thr[i];
   p.wait_ticks = s->bclock_khz * wait_us / 1000u;
-  potts::TileParams f{};
-  f.q = q;
-  f.stripes = s->bstripes;
-  f.nstripes = kStripes;
   // one launch's records fold into distinct ring slots
   const int64_t kmax = std::min<int64_t>(potts::kBandMaxSweeps, s->rec_cap);
   for (int64_t done = 0; done < nsweeps;) {
@@ -818,9 +854,7 @@ int run_band(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     p.epoch = s->bepoch;
     HIP_TRY(potts::launch_band(p, block, s->stream));
     s->bepoch += 2u * (uint32_t)K;
-    f.t0 = p.t0;
-    f.nsweeps = (uint32_t)K;
-    HIP_TRY(potts::launch_fold_sets(f, s->records, (uint64_t)s->rec_cap, s->stream));
+    HIP_TRY(potts::launch_fold_sets(p, s->records, (uint64_t)s->rec_cap, s->stream));
     done += K;
   }
   s->t += nsweeps;
@@ -852,8 +886,8 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     s->planes_valid = false;
   }
   if (use_drawn(s)) return run_drawn(s, thr, nsweeps);
-  if (use_resident(s)) return run_resident(s, thr, nsweeps);
   if (use_tiles(s)) return run_tiles(s, thr, nsweeps);
+  if (use_resident(s)) return run_resident(s, thr, nsweeps);
   const int64_t rl = s->q + 1;
   HIP_TRY(potts::launch_fill_u64(s->records + (s->t % s->rec_cap) * rl, (uint64_t)rl, 0ull, s->stream));
   if (use_packed(s)) return run_packed(s, thr, nsweeps);
@@ -1140,8 +1174,8 @@ int potts_tune_tiles(potts_state *s, int32_t tx, int32_t ty, int32_t sweeps) {
   s->tile_tx = (uint32_t)tx;
   s->tile_ty = (uint32_t)ty;
   s->tile_sweeps = (uint32_t)sweeps;
-  uint32_t a, b, c;
-  if ((tx || ty || sweeps) && !tile_shape(s, &a, &b, &c)) {
+  potts::TileParams p{};
+  if ((tx || ty || sweeps) && !tile_shape(s, 1, &p)) {
     s->tile_tx = old_tx;
     s->tile_ty = old_ty;
     s->tile_sweeps = old_n;
@@ -1202,7 +1236,7 @@ int potts_tune(potts_state *s, int32_t kernel, int32_t strip_rows, int32_t max_g
     return fail(POTTS_EINVAL, "band kernel needs L % 32 == 0, L <= 16384 and a band shape whose grid fits the GPU");
   if (kernel == 6 && !drawn_ok(s))
     return fail(POTTS_EINVAL, "pre-drawn resident kernel needs L % 16 == 0 and L*L <= 4096");
-  if (kernel == 5 && !tiles_ok(s)) return fail(POTTS_EINVAL, "tile kernel needs L % 16 == 0 and a tile shape");
+  if (kernel == 5 && (s->L % 16 || !tiles_ok(s))) return fail(POTTS_EINVAL, "tile kernel needs L % 16 == 0 and a tile shape");
   if (kernel == 4 && !packed_ok(s))
     return fail(POTTS_EINVAL, "colour-split kernel needs L % 32 == 0 and L <= 65520");
   if (kernel == 1 && !strip_ok(s)) return fail(POTTS_EINVAL, "strip kernel needs L % 16 == 0 and L <= 65520");

@@ -65,6 +65,25 @@ __device__ __forceinline__ Words philox_tail(uint32_t x0, const PhiloxHead &h) {
   return Words{c0, c1, c2, c3};
 }
 
+// Two blocks of one half sweep, round by round: four independent products at
+// a time, for waves that have a SIMD to themselves.
+__device__ __forceinline__ void philox_tail2(uint32_t xa, uint32_t xb, const PhiloxHead &h, Words &a, Words &b) {
+  uint32_t k0 = h.k0, k1 = h.k1;
+  a = Words{xa, h.x1, h.x2, h.x3};
+  b = Words{xb, h.x1, h.x2, h.x3};
+#pragma unroll
+  for (int r = 1; r < 10; ++r) {
+    const uint64_t a0 = (uint64_t)kPhiloxM0 * a.w0, b0 = (uint64_t)kPhiloxM0 * b.w0;
+    const uint64_t a1 = (uint64_t)kPhiloxM1 * a.w2, b1 = (uint64_t)kPhiloxM1 * b.w2;
+    a = Words{xor3((uint32_t)(a1 >> 32), a.w1, k0), (uint32_t)a1, xor3((uint32_t)(a0 >> 32), a.w3, k1), (uint32_t)a0};
+    b = Words{xor3((uint32_t)(b1 >> 32), b.w1, k0), (uint32_t)b1, xor3((uint32_t)(b0 >> 32), b.w3, k1), (uint32_t)b0};
+    // holds the two blocks in step: the scheduler would run one after the other
+    asm("" : "+v"(a.w0), "+v"(a.w2), "+v"(b.w0), "+v"(b.w2));
+    k0 += kWeyl0;
+    k1 += kWeyl1;
+  }
+}
+
 __device__ __forceinline__ Words philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                uint32_t k0, uint32_t k1) {
   const PhiloxHead h = philox_head(c0, c2, c3, k0, k1);

@@ -259,20 +259,19 @@ __device__ __forceinline__ Row8 update8(uint32_t s_lo, uint32_t s_hi, uint32_t p
   return r;
 }
 
-// The same update for the 4 active sites of 8 row bytes, given their words:
-// s/p/u/d are the packed active, passive, up and down bytes, side the dword
-// left (O == 0) or right (O == 1) of the 8 bytes, k the four proposals
-// packed (site j in byte j) and a0..a3 the four acceptance words.
-struct Row4 {
-  uint32_t out_x, out_y;  // the 8 bytes after the update
-  uint32_t ns;            // the 4 updated bytes, packed
-  uint32_t nz;            // colour 1: differing-neighbour flags of the new spins
+// The update of the 4 active sites of one dword, given their words: s/p/u/d
+// are the packed active, passive, up and down bytes, side the passive dword
+// left (O == 0) or right (O == 1), k the four proposals packed (site j in
+// byte j) and a0..a3 the four acceptance words.
+struct Site4 {
+  uint32_t ns;  // the 4 updated bytes, packed
+  uint32_t nz;  // colour 1: differing-neighbour flags of the new spins
 };
 
 template <int COLOUR, int O, int CMP, bool WIDE>
-__device__ __forceinline__ Row4 update4_drawn(uint32_t s, uint32_t p, uint32_t u, uint32_t d, uint32_t side,
-                                              uint32_t k, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3,
-                                              const uint8_t *table) {
+__device__ __forceinline__ Site4 update_sites4(uint32_t s, uint32_t p, uint32_t u, uint32_t d, uint32_t side,
+                                               uint32_t k, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3,
+                                               const uint8_t *table) {
   const uint32_t x = O == 0 ? alignbyte(p, side, 3) : alignbyte(side, p, 1);
   const uint32_t ps = diff_pattern<CMP>(s, u, d, p, x);
   const uint32_t pk = diff_pattern<CMP>(k, u, d, p, x);
@@ -305,13 +304,29 @@ __device__ __forceinline__ Row4 update4_drawn(uint32_t s, uint32_t p, uint32_t u
     ns = perm(k, s, sel);
     if (COLOUR == 1) nz = perm(pk, ps, sel);
   }
+  return Site4{ns, nz};
+}
+
+// The same for the 4 active sites of 8 bytes of a row-major row, packed by
+// the caller, with the 8 bytes after the update.
+struct Row4 {
+  uint32_t out_x, out_y;  // the 8 bytes after the update
+  uint32_t ns;            // the 4 updated bytes, packed
+  uint32_t nz;            // colour 1: differing-neighbour flags of the new spins
+};
+
+template <int COLOUR, int O, int CMP, bool WIDE>
+__device__ __forceinline__ Row4 update4_drawn(uint32_t s, uint32_t p, uint32_t u, uint32_t d, uint32_t side,
+                                              uint32_t k, uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3,
+                                              const uint8_t *table) {
+  const Site4 o = update_sites4<COLOUR, O, CMP, WIDE>(s, p, u, d, side, k, a0, a1, a2, a3, table);
   constexpr uint32_t sel_w0 = O ? 0x05010400u : 0x01050004u;
   constexpr uint32_t sel_w1 = O ? 0x07030602u : 0x03070206u;
   Row4 r;
-  r.out_x = perm(ns, p, sel_w0);
-  r.out_y = perm(ns, p, sel_w1);
-  r.ns = ns;
-  r.nz = nz;
+  r.out_x = perm(o.ns, p, sel_w0);
+  r.out_y = perm(o.ns, p, sel_w1);
+  r.ns = o.ns;
+  r.nz = o.nz;
   return r;
 }
 
