@@ -709,8 +709,9 @@ int run_tiles(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   p.k0 = (uint32_t)s->seed;
   p.k1 = (uint32_t)(s->seed >> 32);
   for (int i = 0; i < 4; ++i) p.thr.v[i] = thr[i];
-  potts::TileFold last{};
-  last.q = p.q;
+  potts::RecordFold last{};
+  last.n = p.q + 1u;
+  last.comp = 1;
   last.nparts = nparts;
   last.shared = nparts < ntiles;
   last.ring = s->records;
@@ -733,7 +734,7 @@ int run_tiles(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     last.nsweeps = p.nsweeps;
     std::swap(cur, other);
   }
-  HIP_TRY(potts::launch_tile_fold(last, s->stream));
+  HIP_TRY(potts::launch_record_fold(last, s->stream));
   if (cur != s->spins) {
     if (s->owns_spins && !capturing(s)) {
       std::swap(s->spins, s->spins2);  // library-owned: the buffers trade roles

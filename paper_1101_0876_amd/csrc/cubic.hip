@@ -34,7 +34,10 @@ struct potts3d_state {
   uint64_t seed = 0;
   int64_t t = 0;
   uint8_t *spins = nullptr;   // row-major cube
-  uint8_t *planes = nullptr;  // colour-split copy (L % 32 == 0)
+  uint8_t *planes = nullptr;  // colour-split copy
+  bool no_planes = false;     // there was no memory for it: the chunk kernel sweeps
+  uint32_t *parts = nullptr;  // totals of two sweeps of the colour-split kernel
+  size_t parts_words = 0;
   bool spins_valid = true;    // spins holds the current configuration
   bool planes_valid = false;  // planes holds it
   int32_t kernel = 0;         // 0 automatic, 1 colour-split, 2 chunk
@@ -234,6 +237,7 @@ void release(potts3d_state *s) {
   if (s->stream) (void)hipStreamSynchronize(s->stream);
   if (s->spins) (void)hipFree(s->spins);
   if (s->planes) (void)hipFree(s->planes);
+  if (s->parts) (void)hipFree(s->parts);
   if (s->records) (void)hipFree(s->records);
   if (s->scratch) (void)hipFree(s->scratch);
   if (s->stats_out) (void)hipFree(s->stats_out);
@@ -241,16 +245,25 @@ void release(potts3d_state *s) {
   delete s;
 }
 
+// what potts3d_tune takes the colour-split kernel for
 bool packed_ok(const potts3d_state *s) { return s->L % 32 == 0; }
 
-bool use_packed(const potts3d_state *s) { return s->kernel == 1 || (s->kernel == 0 && packed_ok(s)); }
+// The automatic choice: the colour-split kernel where L % 32 == 0, and from L =
+// 68 for every L (partial items): the chunk kernel's launches all end in one
+// line of atomics and its bytes are merged one by one.  Measured on MI355X (q =
+// 3, us per sweep, the chunk kernel in brackets): L = 60 14.3 (11.5), 100 13.9
+// (32.0), 200 27.8 (124), 300 42.8 (158), 1000 1010 (3140).  Without memory
+// for the second copy the chunk kernel sweeps such an L in place.
+bool use_packed(const potts3d_state *s) {
+  return s->kernel == 1 || (s->kernel == 0 && (packed_ok(s) || (s->L > 64 && !s->no_planes)));
+}
 
 // longest walk that still leaves >= 2048 workgroups to spread over the chip
 uint32_t packed_rows(const potts3d_state *s) {
   if (s->rows) return (uint32_t)s->rows;
-  const uint64_t L = (uint64_t)s->L, ipr = L / 32;
+  const uint64_t L = (uint64_t)s->L, ipr = potts::cube::plane_pitch((uint32_t)s->L) / 16u;
   for (uint32_t R : {32u, 16u, 8u, 4u})
-    if (ipr * L * (L / R) >= 2048ull * kBlock) return R;
+    if (L % R == 0 && ipr * L * (L / R) >= 2048ull * kBlock) return R;
   return 2;
 }
 
@@ -265,9 +278,11 @@ int sync_spins(potts3d_state *s) {
 // make the colour-split copy current (allocated on first use)
 int sync_planes(potts3d_state *s) {
   if (s->planes_valid) return POTTS_OK;
-  if (!s->planes && hipMalloc(&s->planes, (size_t)s->L * s->L * s->L) != hipSuccess) {
+  const size_t bytes = 2 * (size_t)s->L * s->L * potts::cube::plane_pitch((uint32_t)s->L);
+  if (!s->planes && hipMalloc(&s->planes, bytes) != hipSuccess) {
     (void)hipGetLastError();
     s->planes = nullptr;
+    s->no_planes = true;
     return fail(POTTS_ENOMEM, "device allocation of the colour planes failed");
   }
   HIP_TRY3(potts::cube::launch_pack(s->spins, s->planes, (uint32_t)s->L, s->stream));
@@ -281,41 +296,67 @@ int run(potts3d_state *s, const uint32_t thr[6], int64_t nsweeps) {
   if (nsweeps > INT64_MAX - s->t) return fail(POTTS_ERANGE, "sweep counter overflow");
   if (nsweeps == 0) return POTTS_OK;
   const int64_t rl = s->q + 1;
-  const bool packed = use_packed(s);
-  const int rc = packed ? sync_planes(s) : sync_spins(s);
+  bool packed = use_packed(s);
+  int rc = packed ? sync_planes(s) : sync_spins(s);
+  if (rc == POTTS_ENOMEM && s->kernel == 0 && !packed_ok(s)) {
+    packed = false;
+    rc = sync_spins(s);
+  }
   if (rc) return rc;
-  // the first sweep's slot; each colour-1 launch clears the next one
-  const int64_t slot = s->t & (s->rec_cap - 1);
-  HIP_TRY3(hipMemsetAsync(s->records + slot * rl, 0, (size_t)rl * 8, s->stream));
   if (packed) {
     potts::cube::CubeLaunch l{};
-    l.planes = s->planes;
-    l.plane_bytes = (uint64_t)s->L * s->L * s->L / 2;
     l.L = (uint32_t)s->L;
     l.q = (uint32_t)s->q;
-    l.ipr = l.L / 32;
+    const uint32_t pitch = potts::cube::plane_pitch(l.L);
+    l.planes = s->planes;
+    l.plane_bytes = (uint64_t)l.L * l.L * pitch;
+    l.ipr = pitch / 16u;
     l.rows = packed_rows(s);
     l.nitems = l.ipr * l.L * (l.L / l.rows);
     l.k0 = (uint32_t)s->seed;
     l.k1 = (uint32_t)(s->seed >> 32);
     for (int i = 0; i < 6; ++i) l.thr.v[i] = thr[i];
-    const unsigned grid = potts::cube::packed_grid(l);
+    potts::cube::set_groups(l);
+    const size_t words = (size_t)l.groups * (l.q + 1u);
+    if (2 * words > s->parts_words) {
+      if (s->parts) (void)hipFree(s->parts);
+      s->parts = nullptr;
+      s->parts_words = 0;
+      if (hipMalloc(&s->parts, 2 * words * sizeof(uint32_t)) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(POTTS_ENOMEM, "device allocation of the record totals failed");
+      }
+      s->parts_words = 2 * words;
+    }
+    potts::RecordFold last{};
+    last.nparts = l.groups;
+    last.n = l.q + 1u;
+    last.comp = 1;
+    last.ring = s->records;
+    last.cap = (uint64_t)s->rec_cap;
+    last.bonds = 3ull * (uint64_t)s->L * s->L * s->L;
     for (int64_t k = 0; k < nsweeps; ++k) {
       const int64_t t = s->t + k;
       l.t_lo = (uint32_t)(uint64_t)t;
       l.t_hi = (uint32_t)((uint64_t)t >> 32);
-      l.rec = s->records + (t & (s->rec_cap - 1)) * rl;
-      l.rec_clear = nullptr;
-      HIP_TRY3(potts::cube::launch_packed(l, 0, grid, s->stream));
-      l.rec_clear = s->records + ((t + 1) & (s->rec_cap - 1)) * rl;
-      HIP_TRY3(potts::cube::launch_packed(l, 1, grid, s->stream));
+      l.parts = s->parts + (k & 1) * words;
+      l.fold = last;
+      HIP_TRY3(potts::cube::launch_packed(l, 0, s->stream));
+      HIP_TRY3(potts::cube::launch_packed(l, 1, s->stream));
+      last.parts = l.parts;
+      last.t0 = (uint64_t)t;
+      last.nsweeps = 1;
     }
+    HIP_TRY3(potts::launch_record_fold(last, s->stream));
     s->spins_valid = false;
   } else {
     CubeSweep p{};
     p.c = cube_of(s);
     for (int i = 0; i < 6; ++i) p.thr[i] = thr[i];
     const unsigned grid = grid_of(p.c.nchunks, 4096);
+    // the first sweep's slot; each colour-1 launch clears the next one
+    const int64_t slot = s->t & (s->rec_cap - 1);
+    HIP_TRY3(hipMemsetAsync(s->records + slot * rl, 0, (size_t)rl * 8, s->stream));
     for (int64_t k = 0; k < nsweeps; ++k) {
       const int64_t t = s->t + k;
       p.t_lo = (uint32_t)(uint64_t)t;

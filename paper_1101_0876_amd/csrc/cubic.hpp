@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fold.hpp"
+
 namespace potts {
 namespace cube {
 
@@ -14,23 +16,25 @@ struct CubeThr {
 
 struct CubeLaunch {
   uint8_t *planes;         // plane 0, then plane 1 (plane_bytes each)
-  uint64_t plane_bytes;    // L^3 / 2
+  uint64_t plane_bytes;    // L^2 x plane_pitch(L)
   uint32_t L, q;
-  uint32_t ipr;            // L / 32 items (16 packed bytes) per row
+  uint32_t ipr;            // plane_pitch(L) / 16 items per row
   uint32_t rows;           // R: rows of one item's walk (even, divides L)
   uint32_t nitems;         // ipr * L * (L / R)
-  uint32_t xcd_stride;     // grid / 8 when the grid is a multiple of 8, else 0 (set by packed_grid)
+  uint32_t groups;         // workgroups of the half sweep (set_groups)
+  uint32_t xcd_stride;     // groups / 8 when that is whole, else 0 (set_groups)
   uint32_t k0, k1;         // Philox key
   uint32_t t_lo, t_hi;     // sweep index
   CubeThr thr;
-  unsigned long long *rec;        // this sweep's record {e_sat, hist[q]} (both colours add to it)
-  unsigned long long *rec_clear;  // zeroed by the colour-1 launch (the next sweep's record), or null
+  uint32_t *parts;         // this sweep's totals, groups x (q + 1) words (fold.hpp): differing neighbours, populations
+  RecordFold fold;         // the sweep before, folded by the colour-0 launch
 };
 
-// Workgroups for l (also sets l.xcd_stride).
-unsigned packed_grid(CubeLaunch &l);
-hipError_t launch_packed(const CubeLaunch &l, int colour, unsigned grid, hipStream_t stream);
-// Row-major cube (L^3 bytes) <-> the two colour planes; L % 32 == 0.
+// bytes of one plane row: L / 2 rounded up to whole items
+uint32_t plane_pitch(uint32_t L);
+void set_groups(CubeLaunch &l);
+hipError_t launch_packed(const CubeLaunch &l, int colour, hipStream_t stream);
+// Row-major cube (L^3 bytes) <-> the two colour planes.
 hipError_t launch_pack(const uint8_t *cube, uint8_t *planes, uint32_t L, hipStream_t stream);
 hipError_t launch_unpack(const uint8_t *planes, uint8_t *cube, uint32_t L, hipStream_t stream);
 

@@ -15,6 +15,7 @@
 #include <algorithm>
 
 #include "device.hpp"
+#include "fold.hpp"
 #include "kernels.hpp"
 
 namespace potts {
@@ -344,6 +345,11 @@ __global__ void fill_u64_kernel(unsigned long long *p, uint64_t n, unsigned long
   if (i < n) p[i] = value;
 }
 
+__global__ __launch_bounds__(1024) void record_fold_kernel(RecordFold f) {
+  __shared__ unsigned long long acc[kFoldWords];
+  fold_part(f, blockIdx.x, acc);
+}
+
 inline unsigned grid_for(uint64_t items) { return (unsigned)((items + kBlock - 1) / kBlock); }
 
 // persistent grid: enough workgroups to fill the chip, never more than the work
@@ -358,6 +364,12 @@ hipError_t launch_fill_u64(unsigned long long *p, uint64_t n, unsigned long long
                            hipStream_t stream) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(fill_u64_kernel, dim3(grid_for(n)), dim3(kBlock), 0, stream, p, n, value);
+  return hipGetLastError();
+}
+
+hipError_t launch_record_fold(const RecordFold &f, hipStream_t stream) {
+  if (f.nsweeps == 0) return hipSuccess;
+  hipLaunchKernelGGL(record_fold_kernel, dim3(fold_groups(f)), dim3(1024), 0, stream, f);
   return hipGetLastError();
 }
 

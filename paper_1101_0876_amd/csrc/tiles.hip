@@ -180,41 +180,6 @@ __device__ __forceinline__ void tile_item(const Ctx &x, const Item &it, Drawn &w
   if (COLOUR == 1) atomicAdd(x.nz, (uint32_t)__popc(o.nz & it.mask & 0xF0F0F0F0u));
 }
 
-// Workgroup g of a fold: kFoldWords words of one sweep's totals, summed over
-// the launch's parts into the sweep's ring slot.  (A workgroup per sweep took
-// 40 us for 256 tiles at q = 200, longer than the launch it ran beside.)
-constexpr uint32_t kFoldWords = 16;
-
-__host__ __device__ inline uint32_t fold_groups(const TileFold &f) {
-  return f.nsweeps * ((f.q + kFoldWords) / kFoldWords);  // q + 1 words a sweep
-}
-
-__device__ __forceinline__ void fold_part(const TileFold &f, uint32_t g, unsigned long long *acc) {
-  const uint32_t n = f.q + 1u, per = (n + kFoldWords - 1u) / kFoldWords;
-  const uint32_t s = g / per, w = (g - s * per) * kFoldWords + (threadIdx.x % kFoldWords);
-  if (threadIdx.x < kFoldWords) acc[threadIdx.x] = 0;
-  __syncthreads();
-  if (w < n) {
-    unsigned long long sum = 0;
-#pragma unroll 8
-    for (uint32_t b = threadIdx.x / kFoldWords; b < f.nparts; b += blockDim.x / kFoldWords) {
-      uint32_t *at = f.parts + ((size_t)s * f.nparts + b) * n + w;
-      sum += *at;
-      if (f.shared) *at = 0;
-    }
-    if (sum) atomicAdd(&acc[threadIdx.x % kFoldWords], sum);
-  }
-  __syncthreads();
-  // word 0 of the totals: differing neighbours; 2 L^2 bonds in all
-  if (threadIdx.x < kFoldWords && w < n)
-    f.ring[((f.t0 + s) & (f.cap - 1)) * (uint64_t)n + w] = w ? acc[threadIdx.x] : f.bonds - acc[0];
-}
-
-__global__ __launch_bounds__(kMaxBlock) void tile_fold_kernel(TileFold f) {
-  __shared__ unsigned long long acc[kFoldWords];
-  fold_part(f, blockIdx.x, acc);
-}
-
 template <int CMP, bool PRIV>
 constexpr uint32_t kStaticHist = PRIV && CMP == 0 ? 64u * 16u * kTileMaxSweeps : 1u;
 
@@ -512,16 +477,10 @@ bool auto_tile_shape(TileParams &p, int64_t nsweeps) {
 hipError_t launch_tiles(const TileParams &p, hipStream_t stream) {
   if (p.nsweeps == 0) return hipSuccess;
   if (!tile_fits(p) || p.nsweeps > p.sweeps || p.lift < p.hx || p.lift < p.hy || p.lift % p.L || !p.src || !p.dst ||
-      !p.parts || (p.fold.nsweeps && (!p.fold.parts || p.fold.q != p.q)))
+      !p.parts || (p.fold.nsweeps && (!p.fold.parts || p.fold.n != p.q + 1u)))
     return hipErrorInvalidValue;
   const bool wide = !p.thr.v[0] || !p.thr.v[1] || !p.thr.v[2] || !p.thr.v[3];
   return wide ? launch_w<true>(p, stream) : launch_w<false>(p, stream);
-}
-
-hipError_t launch_tile_fold(const TileFold &f, hipStream_t stream) {
-  if (f.nsweeps == 0) return hipSuccess;
-  hipLaunchKernelGGL(tile_fold_kernel, dim3(fold_groups(f)), dim3(kMaxBlock), 0, stream, f);
-  return hipGetLastError();
 }
 
 }  // namespace potts

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fold.hpp"
 #include "kernels.hpp"
 
 namespace potts {
@@ -13,25 +14,12 @@ constexpr uint32_t kTileMaxSweeps = 8;
 constexpr uint32_t kTileMaxL = 65520;
 constexpr size_t kTileMaxLds = 158u * 1024u;  // dynamic LDS of one tile (2 KB more are static)
 
-// A launch's totals: one part of q + 1 words per sweep and tile, or, past
-// kTileMaxParts tiles, that many parts that tiles share (tile b adds to part
-// b % kTileMaxParts; the fold clears them).  Word 0 holds the differing
-// neighbours of the colour-1 sites, word 1 + v the sites with value v; sweep
-// s, part b at (s * parts + b) * (q + 1).
+// A launch's totals (fold.hpp): one part of q + 1 words per sweep and tile, or,
+// past kTileMaxParts tiles, that many parts that tiles share (tile b adds to
+// part b % kTileMaxParts).  Word 0 holds the differing neighbours of the
+// colour-1 sites, word 1 + v the sites with value v.
 constexpr uint32_t kTileMaxParts = 4096;
 __host__ __device__ inline uint32_t tile_parts(uint32_t ntiles) { return ntiles < kTileMaxParts ? ntiles : kTileMaxParts; }
-
-// The totals of a finished launch, to be summed into the record ring.
-struct TileFold {
-  uint32_t *parts;
-  uint32_t nparts, q;
-  bool shared;               // parts that several tiles add to
-  uint32_t nsweeps;          // sweeps of that launch (0: nothing to fold)
-  uint64_t t0;               // its first sweep; record of t0 + s to ring slot (t0 + s) % cap
-  unsigned long long *ring;
-  uint64_t cap;              // a power of two, at least nsweeps
-  uint64_t bonds;            // 2 L^2
-};
 
 struct TileParams {
   const uint8_t *src;  // row-major L x L lattice
@@ -50,7 +38,7 @@ struct TileParams {
   uint32_t w_magic;          // ceil(2^32 / dwords per region row and plane)
   uint32_t narrow;           // the region wraps more than once
   uint32_t *parts;           // this launch's totals
-  TileFold fold;             // the launch before it, folded by extra workgroups
+  RecordFold fold;           // the launch before it, folded by extra workgroups
 };
 
 // Sets the shape fields for p.L and p.q; false when no launch of it exists.
@@ -59,6 +47,5 @@ bool set_tile_shape(TileParams &p, uint32_t tx, uint32_t ty, uint32_t sweeps);
 // with, by a model of one launch (tiles.hip).
 bool auto_tile_shape(TileParams &p, int64_t nsweeps);
 hipError_t launch_tiles(const TileParams &p, hipStream_t stream);
-hipError_t launch_tile_fold(const TileFold &f, hipStream_t stream);
 
 }  // namespace potts
