@@ -153,10 +153,13 @@ int potts_sweep_heatbath_thr(potts_state *s, const uint32_t thr[4], int64_t nswe
  * lattice in LDS and runs all sweeps of a call in one launch), 4 = the
  * colour-split kernel (L % 32 == 0, L <= 65520: a call copies the lattice into
  * two colour planes in the second buffer, sweeps there and copies it back;
- * the automatic choice for such L above 3584 that kernel 7 does not take),
+ * the automatic choice above 4736, for calls of one sweep above 3584, where
+ * kernel 7 does not take the lattice; there it takes L % 32 != 0 too, on planes
+ * of its own, allocated on first use),
  * 5 = the multi-sweep tile kernel (to be asked for, L % 16 == 0 and L <=
- * 65520; the automatic choice, for any L, up to 3584 where kernel 6 does not
- * take it, outside stream capture: each
+ * 65520; the automatic choice, for any L, up to 3584, up to 4736 for calls of
+ * several sweeps, where kernels 6 and 7 do not take it, outside stream
+ * capture: each
  * launch runs several sweeps, one LDS tile
  * per workgroup whose halo is recomputed, and moves the row-major lattice
  * between the state's two buffers; with library-owned buffers they trade
@@ -169,7 +172,7 @@ int potts_sweep_heatbath_thr(potts_state *s, const uint32_t thr[4], int64_t nswe
  * them instead of computing them; the automatic choice for such L),
  * 7 = persistent sweeps on LDS bands (L % 32 == 0, L <= 16384, a band shape
  * from potts_tune_band whose grid the GPU holds at once; the automatic choice
- * for 3584 < L <= 4096 when it can take the lattice): each workgroup keeps
+ * for 4032 < L <= 4096 when it can take the lattice): each workgroup keeps
  * a band of whole rows of the colour-split lattice in LDS for up to 64 sweeps
  * per cooperative launch and trades its two edge rows with the neighbouring
  * bands after every half sweep (an exchange buffer of 2 x L x L / rows bytes,

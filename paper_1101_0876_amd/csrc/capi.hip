@@ -43,7 +43,11 @@ struct potts_state {
   // into its two colour planes; the row-major lattice in spins is rebuilt
   // only when something reads it, and the copy only when it is stale.
   bool spins_valid = true;    // spins holds the current configuration
-  bool planes_valid = false;  // spins2 holds it, colour-split
+  bool planes_valid = false;  // the planes hold it, colour-split
+  // the planes of L % 32 != 0, whose padded rows do not fit in spins2
+  // (allocated on first use; no_rag: there was no memory for them)
+  uint8_t *rag_planes = nullptr;
+  bool no_rag = false;
   // heat-bath draw table of the colour-split kernel (device copy, and the host
   // copy it was uploaded from, valid for hb_thr and q)
   potts::HbTable *hb_dev = nullptr;
@@ -114,10 +118,13 @@ int hip_fail(hipError_t e, const char *what) {
     if (hip_err_ != hipSuccess) return hip_fail(hip_err_, #call); \
   } while (0)
 
+// The buffer of the colour-split copy.
+uint8_t *planes_of(const potts_state *s) { return s->L % 32 ? s->rag_planes : s->spins2; }
+
 // Makes the row-major lattice current (queued on the state's stream).
 int sync_spins(potts_state *s) {
   if (s->spins_valid) return POTTS_OK;
-  HIP_TRY(potts::launch_unpack(s->spins2, s->spins, (uint32_t)s->L, s->stream));
+  HIP_TRY(potts::launch_unpack(planes_of(s), s->spins, (uint32_t)s->L, s->stream));
   s->spins_valid = true;
   return POTTS_OK;
 }
@@ -154,6 +161,7 @@ void release(potts_state *s) {
   if (s->g_tiles) (void)hipFree(s->g_tiles);
   if (s->hb_dev) (void)hipFree(s->hb_dev);
   if (s->tparts) (void)hipFree(s->tparts);
+  if (s->rag_planes) (void)hipFree(s->rag_planes);
   if (s->drawn) (void)hipFree(s->drawn);
   if (s->bxbuf) (void)hipFree(s->bxbuf);
   if (s->bflags) (void)hipFree(s->bflags);
@@ -288,10 +296,33 @@ bool use_resident(const potts_state *s) {
 // the colour-split copy needs 16-byte groups of packed bytes: L % 32 == 0
 bool packed_ok(const potts_state *s) { return strip_ok(s) && s->L % 32 == 0; }
 
-bool auto_tiles(const potts_state *s);
+bool auto_tiles(const potts_state *s, int64_t nsweeps);
+bool capturing(const potts_state *s);
 
-bool use_packed(const potts_state *s) {
-  return packed_ok(s) && (s->kernel == 4 || (s->kernel == 0 && !auto_tiles(s) && !drawn_ok(s)));
+// The colour-split kernel with partial items, the automatic choice for L % 32
+// != 0 above the tiles' range (q = 6, us per sweep on MI355X: L = 5000 33.6, the
+// chunk kernel 136; L = 6000 44.0, the strip kernel 59.0; L = 10000 95, 98).
+// Not under stream capture (it may have to allocate its planes) nor where there
+// was no memory for them.
+bool use_rag(const potts_state *s, int64_t nsweeps) {
+  return s->L % 32 != 0 && s->kernel == 0 && s->L <= 65520 && !s->no_rag && !auto_tiles(s, nsweeps) && !drawn_ok(s) &&
+         !capturing(s);
+}
+
+// Allocates the planes of L % 32 != 0; false: no memory, the kernels that
+// sweep in place take the lattice.
+bool rag_ready(potts_state *s) {
+  if (s->rag_planes) return true;
+  const size_t bytes = 2 * (size_t)s->L * potts::plane_pitch((uint32_t)s->L);
+  if (hipMalloc(&s->rag_planes, bytes) == hipSuccess) return true;
+  (void)hipGetLastError();
+  s->rag_planes = nullptr;
+  s->no_rag = true;
+  return false;
+}
+
+bool use_packed(const potts_state *s, int64_t nsweeps) {
+  return packed_ok(s) && (s->kernel == 4 || (s->kernel == 0 && !auto_tiles(s, nsweeps) && !drawn_ok(s)));
 }
 
 bool use_strip(const potts_state *s) { return strip_ok(s) && (s->kernel == 1 || s->kernel == 0); }
@@ -334,9 +365,14 @@ bool tiles_ok(const potts_state *s) {
 // us per sweep, 200 sweeps a call; in brackets what else takes the size): L =
 // 100 1.6 (one launch per half sweep 5.6), 256 1.6 (LDS-resident 21.9), 512
 // 1.8 (colour-split 12.1), 1000 3.2 (chunk 29.8), 1024 3.2 (colour-split
-// 12.0), 2048 7.0 (bands 8.0), 2560 10.4 (bands 16.9), 3584 18.2 (bands 19.8);
-// at L = 4096 the bands win, 18.0 against 21.7.
-bool auto_tiles(const potts_state *s) { return !drawn_ok(s) && s->L <= 3584; }
+// 12.0), 2048 7.3 (bands 8.0), 2560 10.1 (bands 16.9), 3584 18.2 (bands 19.8),
+// 3968 21.4 (bands 25.8), 4224 23.1 (colour-split 32.2), 4608 27.8 (31.1), 4864
+// 32.6 (31.4).  A call of one sweep recomputes its halo for nothing: there the
+// colour-split kernel takes over above 3584 (41 against 47 us a call at L =
+// 3968).
+bool auto_tiles(const potts_state *s, int64_t nsweeps) {
+  return !drawn_ok(s) && (s->L <= 3584 || (s->L <= 4736 && nsweeps > 1));
+}
 
 // Whether the state's stream is being captured into a graph.  There the sizes
 // that the tiles took over stay with the kernels that work in place and
@@ -350,9 +386,9 @@ bool capturing(const potts_state *s) {
   return st == hipStreamCaptureStatusActive;
 }
 
-bool use_tiles(const potts_state *s) {
+bool use_tiles(const potts_state *s, int64_t nsweeps) {
   if (s->kernel == 5) return tiles_ok(s);
-  if (s->kernel != 0 || !auto_tiles(s)) return false;
+  if (s->kernel != 0 || !auto_tiles(s, nsweeps)) return false;
   return !capturing(s) || (s->L > 256 && s->L < 2048 && s->L % 16 == 0);
 }
 
@@ -407,12 +443,13 @@ bool band_ok(potts_state *s) {
   return s->L % 32 == 0 && s->L <= 16384 && band_shape(s, &rows, &block);
 }
 
-// The automatic choice for 3584 < L <= 4096: L = 4096 takes 18.0 us per sweep
-// (q = 6; the colour-split kernel 27.0, the tile kernel 21.7).  Below, the
+// The automatic choice for 4032 < L <= 4096: L = 4096 takes 18.0 us per sweep
+// (q = 6; the colour-split kernel 25.4, the tile kernel 21.9).  Below, bands
+// leave CUs idle (L = 3968, 124 bands of 32 rows: 25.8, tiles 21.4) or their
 // exchange of edge rows (4 us per half sweep, whatever the size) costs more
 // than the tiles' halos, and from L = 8192 no band of whole rows whose grid
 // the GPU holds at once fits in LDS.
-bool auto_band(potts_state *s) { return s->L > 3584 && s->L <= 4096 && band_ok(s); }
+bool auto_band(potts_state *s) { return s->L > 4032 && s->L <= 4096 && band_ok(s); }
 
 bool use_band(potts_state *s) { return s->kernel == 7 ? band_ok(s) : s->kernel == 0 && auto_band(s); }
 
@@ -547,18 +584,17 @@ uint32_t strip_rows(const potts_state *s) {
 }
 
 // rows per item of the colour-split kernel (32 sites per item row): the
-// tallest of 32, 16, 8 that still gives 2^20 items (4096 workgroups), else 4.
-// Measured on MI355X (q = 6): L = 4096 / 8192 / 16384 / 32768 run at
-// 1.69 / 0.95 / 0.82 / 0.85 ps per site update with 4 / 4 / 8 / 32 rows.  Up to
-// L = 4096 a sweep is bound by launch and per-workgroup overheads, and the
-// shortest walk (most workgroups) wins: q = 9, L = 1024 / 2048 / 4096 take
-// 12.8 / 14.3 / 27.4 us per sweep with 2 rows, 17.3 / 18.5 / 29.0 with 4.
+// tallest of 32, 16, 8 that still gives 2^20 items (4096 workgroups), else 2 up
+// to L = 7168 and 4 above.  Measured on MI355X (q = 6, us per sweep): L = 4128
+// 28.9 / 33.1 with 2 / 4 rows, 6144 41.3 / 43.7, 7168 54.8 / 55.6, 8192 65.3 /
+// 63.3, 16384 221.9 / 218.1 and 214.3 with 8.  The shortest walk gives most
+// workgroups where launches and per-workgroup overheads bind.
 uint32_t packed_rows(const potts_state *s) {
   if (s->rows) return s->rows;
   const uint32_t L = (uint32_t)s->L;
   for (uint32_t r = 32; r >= 8; r /= 2)
-    if (L % r == 0 && (uint64_t)(L / r) * (L / 32) >= (1ull << 20)) return r;
-  return L <= 4096 ? 2 : 4;
+    if (L % r == 0 && (uint64_t)(L / r) * (potts::plane_pitch(L) / 16u) >= (1ull << 20)) return r;
+  return L <= 7168 ? 2 : 4;
 }
 
 void drop_graph(potts_state *s) {
@@ -629,15 +665,15 @@ int capture_graph(potts_state *s, const potts::StripParams &p, int32_t K, bool w
 int run_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   const uint32_t L = (uint32_t)s->L;
   if (!s->planes_valid) {
-    HIP_TRY(potts::launch_pack(s->spins, s->spins2, L, s->stream));
+    HIP_TRY(potts::launch_pack(s->spins, planes_of(s), L, s->stream));
     s->planes_valid = true;
   }
   s->spins_valid = false;
   potts::StripLaunch l{};
   potts::StripParams &p = l.single;
   const uint32_t rows = packed_rows(s);
-  fill_strip_params(p, s->spins2, L, (uint32_t)s->q, s->seed, thr, rows);
-  potts::set_items(p, L / 32, L, rows);
+  fill_strip_params(p, planes_of(s), L, (uint32_t)s->q, s->seed, thr, rows);
+  potts::set_items(p, potts::plane_pitch(L) / 16u, L, rows);
   p.ring = s->records;
   p.cap = (uint64_t)s->rec_cap;
   p.stripes = s->stripes;
@@ -649,7 +685,7 @@ int run_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   // whole graphs of graph_sweeps sweeps first (one workgroup per tile, as the
   // grid-stride launch when the item count fits the grid), the rest direct
   int64_t done = 0;
-  const int32_t K = s->graph_sweeps;
+  const int32_t K = L % 32 ? 0 : s->graph_sweeps;
   if (K > 0 && nsweeps >= K && need <= groups) {
     if (!s->g_exec || s->g_K != K || s->g_rows != rows || s->g_wide != wide || s->g_wpe != s->wpe) {
       const int rc = capture_graph(s, p, K, wide);
@@ -677,7 +713,7 @@ int run_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   if (!s->owns_spins) {
     // caller-owned buffers: the row-major lattice is current after every call,
     // and the next call packs it again, so writes between calls are seen
-    HIP_TRY(potts::launch_unpack(s->spins2, s->spins, L, s->stream));
+    HIP_TRY(potts::launch_unpack(planes_of(s), s->spins, L, s->stream));
     s->spins_valid = true;
     s->planes_valid = false;
   }
@@ -878,7 +914,8 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   if (nsweeps == 0) return POTTS_OK;
   const bool band = use_band(s);
   if (band) return run_band(s, thr, nsweeps);
-  if (use_resident(s) || !use_packed(s)) {
+  const bool rag = use_rag(s, nsweeps) && rag_ready(s);
+  if (!rag && (use_resident(s) || !use_packed(s, nsweeps))) {
     // every other kernel sweeps the row-major lattice (the LDS-resident one
     // too, although the lattice may have a colour-split copy from heat-bath
     // sweeps)
@@ -887,11 +924,11 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     s->planes_valid = false;
   }
   if (use_drawn(s)) return run_drawn(s, thr, nsweeps);
-  if (use_tiles(s)) return run_tiles(s, thr, nsweeps);
+  if (use_tiles(s, nsweeps)) return run_tiles(s, thr, nsweeps);
   if (use_resident(s)) return run_resident(s, thr, nsweeps);
   const int64_t rl = s->q + 1;
   HIP_TRY(potts::launch_fill_u64(s->records + (s->t % s->rec_cap) * rl, (uint64_t)rl, 0ull, s->stream));
-  if (use_packed(s)) return run_packed(s, thr, nsweeps);
+  if (rag || use_packed(s, nsweeps)) return run_packed(s, thr, nsweeps);
   if (use_strip(s)) {
     potts::StripLaunch l{};
     potts::StripParams &p = l.single;

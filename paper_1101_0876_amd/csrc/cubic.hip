@@ -261,7 +261,7 @@ bool use_packed(const potts3d_state *s) {
 // longest walk that still leaves >= 2048 workgroups to spread over the chip
 uint32_t packed_rows(const potts3d_state *s) {
   if (s->rows) return (uint32_t)s->rows;
-  const uint64_t L = (uint64_t)s->L, ipr = potts::cube::plane_pitch((uint32_t)s->L) / 16u;
+  const uint64_t L = (uint64_t)s->L, ipr = potts::plane_pitch((uint32_t)s->L) / 16u;
   for (uint32_t R : {32u, 16u, 8u, 4u})
     if (L % R == 0 && ipr * L * (L / R) >= 2048ull * kBlock) return R;
   return 2;
@@ -278,7 +278,7 @@ int sync_spins(potts3d_state *s) {
 // make the colour-split copy current (allocated on first use)
 int sync_planes(potts3d_state *s) {
   if (s->planes_valid) return POTTS_OK;
-  const size_t bytes = 2 * (size_t)s->L * s->L * potts::cube::plane_pitch((uint32_t)s->L);
+  const size_t bytes = 2 * (size_t)s->L * s->L * potts::plane_pitch((uint32_t)s->L);
   if (!s->planes && hipMalloc(&s->planes, bytes) != hipSuccess) {
     (void)hipGetLastError();
     s->planes = nullptr;
@@ -307,7 +307,7 @@ int run(potts3d_state *s, const uint32_t thr[6], int64_t nsweeps) {
     potts::cube::CubeLaunch l{};
     l.L = (uint32_t)s->L;
     l.q = (uint32_t)s->q;
-    const uint32_t pitch = potts::cube::plane_pitch(l.L);
+    const uint32_t pitch = potts::plane_pitch(l.L);
     l.planes = s->planes;
     l.plane_bytes = (uint64_t)l.L * l.L * pitch;
     l.ipr = pitch / 16u;

@@ -30,8 +30,6 @@ struct CubeLaunch {
   RecordFold fold;         // the sweep before, folded by the colour-0 launch
 };
 
-// bytes of one plane row: L / 2 rounded up to whole items
-uint32_t plane_pitch(uint32_t L);
 void set_groups(CubeLaunch &l);
 hipError_t launch_packed(const CubeLaunch &l, int colour, hipStream_t stream);
 // Row-major cube (L^3 bytes) <-> the two colour planes.

@@ -466,8 +466,6 @@ void launch_w(const CubeLaunch &l, unsigned grid, hipStream_t stream) {
 
 }  // namespace
 
-uint32_t plane_pitch(uint32_t L) { return (L / 2u + 15u) & ~15u; }
-
 void set_groups(CubeLaunch &l) {
   const uint64_t groups = ((uint64_t)l.nitems + kBlock - 1) / kBlock;
   l.groups = (uint32_t)groups;

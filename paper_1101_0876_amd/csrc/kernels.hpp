@@ -182,6 +182,9 @@ void fill_slab_params(StripParams &p, uint8_t *slab, uint32_t L, uint32_t h, uin
 // nrows up to 32 that still gives at least `want` items
 uint32_t auto_strip_rows(uint32_t L, uint32_t nrows, uint64_t want);
 
+// bytes of one row of a colour plane: L / 2 rounded up to whole 16-byte items
+inline uint32_t plane_pitch(uint32_t L) { return (L / 2u + 15u) & ~15u; }
+
 hipError_t launch_fill_u64(unsigned long long *p, uint64_t n, unsigned long long value,
                            hipStream_t stream);
 hipError_t launch_init(const InitParams &p, hipStream_t stream);
@@ -194,6 +197,7 @@ hipError_t launch_strip(const StripLaunch &l, int colour, unsigned grid, uint32_
                         hipStream_t stream);
 // colour-split single-lattice kernel (packed.hip): l.single describes the
 // split copy (spins = its two planes, ipr = L/32); pack/unpack convert
+// (L % 32 != 0: launch_packed_single only, ipr = plane_pitch(L)/16)
 // qmax: the largest q of the launch's jobs (selects the comparison mode and
 // histogram form); l.tiles set: batched jobs through the tile table
 hipError_t launch_packed(const StripLaunch &l, int colour, unsigned grid, uint32_t qmax, bool wide,

@@ -18,13 +18,23 @@
 // their jobs before a run and unpack them after it.
 // Both copies are plain streaming kernels.
 //
+// Rows are stored in a pitch of whole 16-byte items; where L % 32 != 0 (RAG,
+// single lattices) the last item of a row is partial (edge.hpp) and the planes
+// have a buffer of their own.
+//
 // Work item: 16 packed bytes (16 active sites) of R consecutive rows of the
 // active plane, walked downwards like the strip kernel: each passive row is
 // loaded once and serves as the down, the same-row and the up neighbour.
 // Batches of lattices run the same kernel through a tile table.
+//
+// What bounds it: VALU issue (28 operations a site, 17 of them the random
+// words).  Both rows of a step are read before either is stored; measured on
+// MI355X (q = 6, us per sweep) L = 6144 43.4 (44.0 with each row read after the
+// one before was stored), 16384 215 (217), 32768 863 (876).
 #include <hip/hip_runtime.h>
 
 #include "device.hpp"
+#include "edge.hpp"
 #include "kernels.hpp"
 #include "sweep_row.hpp"
 
@@ -43,24 +53,37 @@ struct PCarry {
 struct PSums {
   uint32_t nz;
   uint32_t sites;
+  uint32_t missing;
 };
 
-// One packed row: active bytes at a_off, the passive row below at d_off, the
-// passive dword beside the item at side_off (left of it when O == 0, right
-// when O == 1).  ctr: Philox chunk of the item's first active byte.
-template <int COLOUR, int O, int CMP, bool PRIV, bool WIDE>
+// Operands of one packed row: active bytes at a_off, the passive row below at
+// d_off, the passive dword beside the item at side_off (left of it when O == 0,
+// right when O == 1).
+struct PIn {
+  u32x4 a, dn;
+  uint32_t side;
+};
+
+__device__ __forceinline__ PIn packed_load(__amdgpu_buffer_rsrc_t rs, uint32_t a_off, uint32_t d_off,
+                                           uint32_t side_off) {
+  return PIn{load16(rs, a_off), load16(rs, d_off), load4(rs, side_off)};
+}
+
+// One packed row, stored at a_off.  ctr: Philox chunk of the item's first
+// active byte.
+template <int COLOUR, int O, int CMP, bool PRIV, bool WIDE, bool RAG>
 __device__ __forceinline__ void packed_row(const StripParams &p, const PhiloxHead &h,
                                            __amdgpu_buffer_rsrc_t rs, const uint8_t *table, uint8_t *hist,
-                                           uint32_t lane_off, uint32_t a_off, uint32_t d_off, uint32_t side_off,
+                                           uint32_t lane_off, const Edge &edge, const PIn &in, uint32_t a_off,
                                            uint32_t ctr, PCarry &cy, PSums &sums) {
-  const u32x4 a = load16(rs, a_off);
-  const u32x4 dn = load16(rs, d_off);
-  const uint32_t side = load4(rs, side_off);
+  const u32x4 a = in.a, dn = in.dn;
+  const uint32_t side = RAG && O == 0 ? in.side << edge.shift : in.side;
+  const u32x4 pp = RAG && O == 1 ? with_wrap(edge, cy.p, side) : cy.p;
   // two groups of 8 sites; each needs the passive dword beyond its own pair
-  const Row8 r0 = update8<COLOUR, O, CMP, WIDE>(a.x, a.y, cy.p.x, cy.p.y, cy.u.x, cy.u.y, dn.x, dn.y,
-                                                O == 0 ? side : cy.p.z, ctr, h, p.q, table);
-  const Row8 r1 = update8<COLOUR, O, CMP, WIDE>(a.z, a.w, cy.p.z, cy.p.w, cy.u.z, cy.u.w, dn.z, dn.w,
-                                                O == 0 ? cy.p.y : side, ctr + 4u, h, p.q, table);
+  const Row8 r0 = update8<COLOUR, O, CMP, WIDE, !RAG>(a.x, a.y, pp.x, pp.y, cy.u.x, cy.u.y, dn.x, dn.y,
+                                                      O == 0 ? side : pp.z, ctr, h, p.q, table);
+  const Row8 r1 = update8<COLOUR, O, CMP, WIDE, !RAG>(a.z, a.w, pp.z, pp.w, cy.u.z, cy.u.w, dn.z, dn.w,
+                                                      O == 0 ? pp.y : side, ctr + 4u, h, p.q, table);
   u32x4 out;
   out.x = r0.ns_lo;
   out.y = r0.ns_hi;
@@ -68,27 +91,35 @@ __device__ __forceinline__ void packed_row(const StripParams &p, const PhiloxHea
   out.w = r1.ns_hi;
   store16(rs, a_off, out);
   if (COLOUR == 1) {
-    sums.nz += __popc(r0.nz_lo & 0xF0F0F0F0u) + __popc(r0.nz_hi & 0xF0F0F0F0u) +
-               __popc(r1.nz_lo & 0xF0F0F0F0u) + __popc(r1.nz_hi & 0xF0F0F0F0u);
-    sums.sites += 16;
+    constexpr uint32_t m = 0xF0F0F0F0u;
+    sums.nz += RAG ? __popc(r0.nz_lo & m & edge.valid[0]) + __popc(r0.nz_hi & m & edge.valid[1]) +
+                         __popc(r1.nz_lo & m & edge.valid[2]) + __popc(r1.nz_hi & m & edge.valid[3])
+                   : __popc(r0.nz_lo & m) + __popc(r0.nz_hi & m) + __popc(r1.nz_lo & m) + __popc(r1.nz_hi & m);
+    sums.sites += RAG ? 16u - edge.missing : 16u;
+  }
+  if (RAG) {  // bytes that are no sites are counted as value 0, and taken off at the end
+    out.x &= edge.valid[0];
+    out.y &= edge.valid[1];
+    out.z &= edge.valid[2];
+    out.w &= edge.valid[3];
   }
   if (PRIV) {
-    count_active_private(hist, lane_off, r0.ns_lo, r0.ns_hi);
-    count_active_private(hist, lane_off, r1.ns_lo, r1.ns_hi);
+    count_active_private(hist, lane_off, out.x, out.y);
+    count_active_private(hist, lane_off, out.z, out.w);
   } else {
-    count_active_shared(reinterpret_cast<uint32_t *>(hist), r0.ns_lo, r0.ns_hi);
-    count_active_shared(reinterpret_cast<uint32_t *>(hist), r1.ns_lo, r1.ns_hi);
+    count_active_shared(reinterpret_cast<uint32_t *>(hist), out.x, out.y);
+    count_active_shared(reinterpret_cast<uint32_t *>(hist), out.z, out.w);
   }
   cy.u = cy.p;
   cy.p = dn;
 }
 
-// p.spins: the packed lattice; p.ipr = L/32 items per row band; the whole
+// p.spins: the packed lattice; p.ipr = pitch/16 items per row band; the whole
 // lattice (no slab mode); records through p.stripes when set, else the slot.
 // TILED: workgroup -> (job, item range) from the tile table (batched
 // lattices, as in the strip kernel); otherwise the single descriptor with a
 // grid-stride loop.
-template <int COLOUR, int CMP, bool PRIV, bool WIDE, bool TILED, int BLOCK>
+template <int COLOUR, int CMP, bool PRIV, bool WIDE, bool TILED, int BLOCK, bool RAG = false>
 __device__ __forceinline__ void packed_body(const StripLaunch &launch) {
   constexpr int kWaves = BLOCK / 64;
   __shared__ __align__(16) uint32_t table_words[512];
@@ -117,7 +148,11 @@ __device__ __forceinline__ void packed_body(const StripLaunch &launch) {
   // a workgroup's bond count reaches 2N / grid, beyond 32 bits on the largest
   // lattices with few workgroups: counted in 64 bits
   __shared__ unsigned long long esum;
-  if (threadIdx.x == 0) esum = 0;
+  __shared__ uint32_t no_sites;  // counted bytes that are no sites (RAG)
+  if (threadIdx.x == 0) {
+    esum = 0;
+    no_sites = 0;
+  }
   if (p.stripes) {
     __shared__ unsigned long long fold_acc[COLOUR == 0 ? 257 : 1];
     if (COLOUR == 0 && lead && launch.sweep > 0) fold_stripes<BLOCK>(p, t - 1, fold_acc);
@@ -131,39 +166,46 @@ __device__ __forceinline__ void packed_body(const StripLaunch &launch) {
   uint8_t *hist_bytes = reinterpret_cast<uint8_t *>(hist);
   const uint32_t lane_off = lane * 4u;
   const uint32_t L = p.L;
-  const uint32_t half = L >> 1;           // bytes per plane row
-  const uint32_t plane = half * L;        // bytes per plane
+  const uint32_t half = L >> 1;                      // sites per plane row
+  const uint32_t pitch = RAG ? p.ipr * 16u : half;   // bytes per plane row
+  const uint32_t plane = pitch * L;                  // bytes per plane
   const uint32_t a_base = COLOUR == 0 ? 0u : plane;
   const uint32_t p_base = COLOUR == 0 ? plane : 0u;
   const uint32_t rows = p.rows;
-  PSums sums{0, 0};
+  PSums sums{0, 0, 0};
 
   for (uint32_t item = first; item < end; item += stride) {
     const uint32_t rb = p.item_shift >= 0 ? item >> p.item_shift
                                           : (uint32_t)__umul64hi((uint64_t)item, p.item_magic);
     const uint32_t xi = item - rb * p.ipr;
     const uint32_t col = xi * 16u;
-    const uint32_t left_col = col == 0 ? half - 4 : col - 4;
-    const uint32_t right_col = col + 16 == half ? 0u : col + 16;
+    const uint32_t left_col = col == 0 ? (RAG ? last_dword(half) : half - 4u) : col - 4u;
+    const uint32_t right_col = col + 16u == pitch ? 0u : col + 16u;
+    Edge edge{};
+    if (RAG) edge = edge_of(col, half);
     const uint32_t r0 = rb * rows;  // even, so row r0 has O = COLOUR
     const uint32_t rp = r0 == 0 ? L - 1 : r0 - 1;
     PCarry cy;
-    cy.u = load16(rs, p_base + rp * half + col);
-    cy.p = load16(rs, p_base + r0 * half + col);
+    cy.u = load16(rs, p_base + rp * pitch + col);
+    cy.p = load16(rs, p_base + r0 * pitch + col);
     uint32_t ctr = r0 * p.row_words + (col >> 1);
-    constexpr bool kLeftFirst = COLOUR == 0;  // row parity 0: O = COLOUR
+    // row parity 0: O = COLOUR
+    const uint32_t side0 = COLOUR == 0 ? left_col : right_col, side1 = COLOUR == 0 ? right_col : left_col;
     for (uint32_t k = 0; k < rows; k += 2) {
       const uint32_t y = r0 + k;
-      packed_row<COLOUR, COLOUR, CMP, PRIV, WIDE>(
-          p, h, rs, table, hist_bytes, lane_off, a_base + y * half + col, p_base + (y + 1) * half + col,
-          p_base + y * half + (kLeftFirst ? left_col : right_col), ctr, cy, sums);
-      ctr += p.row_words;
       const uint32_t yd = k + 2 == rows ? (r0 + rows == L ? 0u : r0 + rows) : y + 2;
-      packed_row<COLOUR, COLOUR ^ 1, CMP, PRIV, WIDE>(
-          p, h, rs, table, hist_bytes, lane_off, a_base + (y + 1) * half + col, p_base + yd * half + col,
-          p_base + (y + 1) * half + (kLeftFirst ? right_col : left_col), ctr, cy, sums);
+      // both rows' operands before either row's store, which would hold them back
+      const uint32_t a0 = a_base + y * pitch + col, a1 = a0 + pitch;
+      const PIn in0 = packed_load(rs, a0, p_base + (y + 1) * pitch + col, p_base + y * pitch + side0);
+      const PIn in1 = packed_load(rs, a1, p_base + yd * pitch + col, p_base + (y + 1) * pitch + side1);
+      packed_row<COLOUR, COLOUR, CMP, PRIV, WIDE, RAG>(p, h, rs, table, hist_bytes, lane_off, edge, in0, a0, ctr, cy,
+                                                       sums);
+      ctr += p.row_words;
+      packed_row<COLOUR, COLOUR ^ 1, CMP, PRIV, WIDE, RAG>(p, h, rs, table, hist_bytes, lane_off, edge, in1, a1, ctr,
+                                                           cy, sums);
       ctr += p.row_words;
     }
+    if (RAG) sums.missing += edge.missing * rows;
   }
 
   unsigned long long *rec = p.ring + (t & (p.cap - 1)) * (uint64_t)(q + 1);
@@ -171,6 +213,10 @@ __device__ __forceinline__ void packed_body(const StripLaunch &launch) {
     // at most 4 x 2^29 bonds per wave (L < 2^16): 32 bits suffice up to here
     const uint32_t e = wave_sum(4u * sums.sites - sums.nz);
     if (lane == 0 && e) atomicAdd(&esum, (unsigned long long)e);
+  }
+  if (RAG) {
+    const uint32_t m = wave_sum(sums.missing);
+    if (lane == 0 && m) atomicAdd(&no_sites, m);
   }
   __syncthreads();
   if (PRIV) {
@@ -183,7 +229,8 @@ __device__ __forceinline__ void packed_body(const StripLaunch &launch) {
   unsigned long long *dst =
       p.stripes ? p.stripes + ((t & 1) * p.nstripes + (bid & (p.nstripes - 1))) * (uint64_t)stripe_words(q) : rec;
   for (uint32_t v = threadIdx.x; v < q; v += BLOCK) {
-    const uint32_t s = PRIV ? partial[v] : hist[v];
+    uint32_t s = PRIV ? partial[v] : hist[v];
+    if (RAG && v == 0) s -= no_sites;
     if (s) atomicAdd(&dst[1 + v], (unsigned long long)s);
   }
   if (COLOUR == 1 && threadIdx.x == 0 && esum) atomicAdd(&dst[0], esum);
@@ -195,6 +242,11 @@ __device__ __forceinline__ void packed_body(const StripLaunch &launch) {
 template <int COLOUR, int CMP, bool PRIV, bool WIDE, bool TILED, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void packed_kernel(StripLaunch launch) {
   packed_body<COLOUR, CMP, PRIV, WIDE, TILED, BLOCK>(launch);
+}
+
+template <int COLOUR, int CMP, bool PRIV, bool WIDE>
+__global__ __launch_bounds__(kBlock) void packed_rag_kernel(StripLaunch launch) {
+  packed_body<COLOUR, CMP, PRIV, WIDE, false, kBlock, true>(launch);
 }
 
 template <int COLOUR, int CMP, bool PRIV, bool WIDE, bool TILED, int BLOCK>
@@ -268,6 +320,49 @@ __global__ __launch_bounds__(kBlock) void unpack_kernel(const uint8_t *src, uint
   out[1] = hi;
 }
 
+// The same for L % 32 != 0: one thread per dword of a plane row, the padding
+// set to 0 (pack).
+__global__ __launch_bounds__(kBlock) void pack_rag_kernel(const uint8_t *src, uint8_t *dst, uint32_t L, uint32_t pitch) {
+  const uint32_t dwords = pitch >> 2;
+  const uint64_t g = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (g >= (uint64_t)dwords * L) return;
+  const uint32_t y = (uint32_t)(g / dwords), j = (uint32_t)(g - (uint64_t)y * dwords);
+  const uint32_t *in = reinterpret_cast<const uint32_t *>(src + (size_t)y * L);
+  const uint32_t lo = 8u * j < L ? in[2u * j] : 0u, hi = 8u * j + 4u < L ? in[2u * j + 1u] : 0u;
+  const size_t plane = (size_t)pitch * L, at = (size_t)y * pitch + 4u * j;
+  // even x has colour y & 1
+  *reinterpret_cast<uint32_t *>(dst + (y & 1u) * plane + at) = perm(hi, lo, kSel<0>);
+  *reinterpret_cast<uint32_t *>(dst + ((y & 1u) ^ 1u) * plane + at) = perm(hi, lo, kSel<1>);
+}
+
+__global__ __launch_bounds__(kBlock) void unpack_rag_kernel(const uint8_t *src, uint8_t *dst, uint32_t L,
+                                                            uint32_t pitch) {
+  const uint32_t dwords = pitch >> 2;
+  const uint64_t g = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (g >= (uint64_t)dwords * L) return;
+  const uint32_t y = (uint32_t)(g / dwords), j = (uint32_t)(g - (uint64_t)y * dwords);
+  const size_t plane = (size_t)pitch * L, at = (size_t)y * pitch + 4u * j;
+  const uint32_t even = *reinterpret_cast<const uint32_t *>(src + (y & 1u) * plane + at);
+  const uint32_t odd = *reinterpret_cast<const uint32_t *>(src + ((y & 1u) ^ 1u) * plane + at);
+  uint32_t *out = reinterpret_cast<uint32_t *>(dst + (size_t)y * L);
+  if (8u * j < L) out[2u * j] = perm(odd, even, 0x05010400u);
+  if (8u * j + 4u < L) out[2u * j + 1u] = perm(odd, even, 0x07030602u);
+}
+
+template <int COLOUR, bool WIDE>
+hipError_t launch_rag(const StripLaunch &l, unsigned grid, hipStream_t stream) {
+  const uint32_t q = l.single.q;
+  if (q <= 16)
+    hipLaunchKernelGGL((packed_rag_kernel<COLOUR, 0, true, WIDE>), dim3(grid), dim3(kBlock), 0, stream, l);
+  else if (q <= kPrivateHistMaxQ)
+    hipLaunchKernelGGL((packed_rag_kernel<COLOUR, 1, true, WIDE>), dim3(grid), dim3(kBlock), 0, stream, l);
+  else if (q <= 128)
+    hipLaunchKernelGGL((packed_rag_kernel<COLOUR, 1, false, WIDE>), dim3(grid), dim3(kBlock), 0, stream, l);
+  else
+    hipLaunchKernelGGL((packed_rag_kernel<COLOUR, 2, false, WIDE>), dim3(grid), dim3(kBlock), 0, stream, l);
+  return hipGetLastError();
+}
+
 template <int COLOUR, bool WIDE, bool TILED>
 hipError_t launch_w(const StripLaunch &l, unsigned grid, uint32_t q, hipStream_t stream) {
   if (q <= 16)
@@ -313,6 +408,12 @@ hipError_t launch_packed(const StripLaunch &l, int colour, unsigned grid, uint32
 
 hipError_t launch_packed_single(const StripLaunch &l, int colour, unsigned grid, uint32_t qmax, bool wide,
                                 uint32_t wpe, hipStream_t stream) {
+  if (l.single.L % 32) {
+    if (l.tiles || l.single.ipr * 16u != plane_pitch(l.single.L)) return hipErrorInvalidValue;
+    if (grid == 0) return hipSuccess;
+    if (colour == 0) return wide ? launch_rag<0, true>(l, grid, stream) : launch_rag<0, false>(l, grid, stream);
+    return wide ? launch_rag<1, true>(l, grid, stream) : launch_rag<1, false>(l, grid, stream);
+  }
   if (wpe == 0 || qmax > 16 || l.tiles) return launch_packed(l, colour, grid, qmax, wide, stream);
   if (grid == 0) return hipSuccess;
   if (colour == 0) {
@@ -349,6 +450,12 @@ hipError_t launch_fold_advance(StripParams *d, uint32_t sweeps, hipStream_t stre
 }
 
 hipError_t launch_pack(const uint8_t *row_major, uint8_t *packed, uint32_t L, hipStream_t stream) {
+  if (L % 32) {
+    const uint64_t n = (uint64_t)(plane_pitch(L) >> 2) * L;
+    hipLaunchKernelGGL(pack_rag_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, stream,
+                       row_major, packed, L, plane_pitch(L));
+    return hipGetLastError();
+  }
   const uint64_t n = (uint64_t)(L >> 5) * L;
   hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, stream, row_major,
                      packed, L);
@@ -356,6 +463,12 @@ hipError_t launch_pack(const uint8_t *row_major, uint8_t *packed, uint32_t L, hi
 }
 
 hipError_t launch_unpack(const uint8_t *packed, uint8_t *row_major, uint32_t L, hipStream_t stream) {
+  if (L % 32) {
+    const uint64_t n = (uint64_t)(plane_pitch(L) >> 2) * L;
+    hipLaunchKernelGGL(unpack_rag_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, stream, packed,
+                       row_major, L, plane_pitch(L));
+    return hipGetLastError();
+  }
   const uint64_t n = (uint64_t)(L >> 5) * L;
   hipLaunchKernelGGL(unpack_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, stream, packed,
                      row_major, L);

@@ -49,3 +49,50 @@ def test_cubes(potts, oracle_lib, L, q, rows):
         recs.append(oracle_lib.sweeps3d(s, q, 5, t + 1, 1, tables[0]))
         assert np.array_equal(c.records(0, t + 2), np.concatenate(recs))
         assert np.array_equal(c.spins(), s)
+
+
+# L / 2 % 16 = 2 .. 14, rows per item from 2 to 32
+PLANES = [(4740, 6, 0), (4744, 16, 4), (4748, 17, 2), (4752, 64, 16), (4756, 65, 0), (4760, 129, 8), (4764, 256, 2)]
+
+
+@pytest.mark.parametrize("L,q,rows", PLANES)
+def test_lattices(potts, oracle_lib, L, q, rows):
+    """Above the tiles' range: two sweeps of the colour-split kernel under the
+    narrow and the wide table, a strip or chunk sweep in between, a heat-bath
+    sweep after them."""
+    print(f"ragged lattice L={L} q={q} rows={rows}", flush=True)
+    thr, zeros = oracle_lib.threshold_table(beta_c(q)), np.array([9, 0, 7, 0], dtype=np.uint32)
+    s = oracle_lib.init(L, q, 5, 1)
+    recs = []
+    with potts.Lattice(L, q, 5, 1) as lat:
+        lat.tune(0, rows)
+        for t, (table, kernel) in enumerate([(thr, 0), (zeros, 0), (thr, 2), (thr, 0)]):
+            lat.tune(kernel, rows)
+            lat.sweep_thr(table, 1)
+            recs.append(oracle_lib.sweeps(s, q, 5, t, 1, table))
+        lat.sweep_heatbath_thr(thr, 1)
+        recs.append(oracle_lib.heatbath_sweeps(s, q, 5, 4, 1, thr))
+        assert np.array_equal(lat.records(0, 5), np.concatenate(recs))
+        assert np.array_equal(lat.spins(), s)
+
+
+def test_caller_buffers(potts, oracle_lib):
+    """The caller's buffer is current after each call, and a write into it is
+    where the next call starts."""
+    import torch
+
+    L, q = 4748, 7
+    thr = oracle_lib.threshold_table(beta_c(q))
+    s = oracle_lib.init(L, q, 8, 1)
+    with potts.Lattice.from_torch(L, q, 8, 1) as lat:
+        lat.sweep_thr(thr, 1)
+        oracle_lib.sweeps(s, q, 8, 0, 1, thr, record=False)
+        torch.cuda.synchronize()
+        assert np.array_equal(lat._keep[0].cpu().numpy().reshape(L, L), s)
+        s[:] = np.random.default_rng(5).integers(0, q, (L, L), dtype=np.uint8)
+        lat._keep[0].copy_(torch.from_numpy(s.reshape(-1)))
+        torch.cuda.synchronize()
+        lat.sweep_thr(thr, 2)
+        oracle_lib.sweeps(s, q, 8, 1, 2, thr, record=False)
+        torch.cuda.synchronize()
+        assert np.array_equal(lat._keep[0].cpu().numpy().reshape(L, L), s)
