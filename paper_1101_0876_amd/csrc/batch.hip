@@ -32,6 +32,7 @@
 
 #include "../../include/potts.h"
 #include "kernels.hpp"
+#include "tiles.hpp"
 #include "tune_cache.hpp"
 
 namespace potts {
@@ -86,7 +87,7 @@ struct potts_batch {
   potts_batch_opts opts{};
   hipStream_t stream = nullptr, side = nullptr;
   bool owns_stream = false;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_t0 = nullptr, ev_t1 = nullptr;
+  hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_tiles = nullptr, ev_t0 = nullptr, ev_t1 = nullptr;
   uint8_t *arena = nullptr;                 // all lattices (row-major)
   uint8_t *planes = nullptr;                // colour-split copies of the colour-split jobs
   unsigned long long *rec_arena = nullptr;  // all record rings
@@ -109,6 +110,14 @@ struct potts_batch {
   std::vector<size_t> strip_desc_off, tile_off, tile_count;  // per strip group
   potts::ResidentJob *d_res = nullptr;      // per resident group and chunk
   std::vector<size_t> res_off;              // per (group, chunk)
+  // multi-sweep tile launches of the resident jobs, where they are few (see
+  // tile_runs): second lattices, totals, descriptors and tables, allocated on
+  // first use
+  uint8_t *other = nullptr;
+  uint32_t *d_tparts = nullptr;
+  potts::TileParams *d_tjobs = nullptr;
+  potts::TileRef *d_trefs = nullptr;
+  size_t other_cap = 0, tparts_cap = 0, tjobs_cap = 0, trefs_cap = 0;
   potts::StatsParams *d_stats = nullptr;
   double *d_stats_out = nullptr;
   hipGraph_t graph = nullptr;
@@ -126,9 +135,10 @@ void release(potts_batch *b) {
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->graph) (void)hipGraphDestroy(b->graph);
   for (void *p : {(void *)b->arena, (void *)b->planes, (void *)b->rec_arena, (void *)b->d_strip, (void *)b->d_tiles,
-                  (void *)b->d_res, (void *)b->d_stats, (void *)b->d_stats_out})
+                  (void *)b->d_res, (void *)b->d_stats, (void *)b->d_stats_out, (void *)b->other,
+                  (void *)b->d_tparts, (void *)b->d_tjobs, (void *)b->d_trefs})
     if (p) (void)hipFree(p);
-  for (hipEvent_t e : {b->ev_fork, b->ev_join, b->ev_t0, b->ev_t1})
+  for (hipEvent_t e : {b->ev_fork, b->ev_join, b->ev_tiles, b->ev_t0, b->ev_t1})
     if (e) (void)hipEventDestroy(e);
   if (b->side) (void)hipStreamDestroy(b->side);
   if (b->owns_stream && b->stream) (void)hipStreamDestroy(b->stream);
@@ -334,6 +344,79 @@ int autotune(potts_batch *b, bool time_new) {
   return POTTS_OK;
 }
 
+// Grows a device buffer to n entries of `size` bytes (its contents are not
+// kept; nothing of the batch is in flight); false: no memory.
+bool grow(void **p, size_t *cap, size_t n, size_t size) {
+  if (n <= *cap) return true;
+  if (*p) (void)hipFree(*p);
+  *p = nullptr;
+  *cap = 0;
+  if (hipMalloc(p, n * size) != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+    return false;
+  }
+  *cap = n;
+  return true;
+}
+
+// The resident jobs' remaining sweeps as multi-sweep tile launches, while
+// their lattices hold at most kTileSites sites together: one workgroup sweeps
+// an L = 256 lattice in 27 us and leaves the other CUs idle.  Measured on MI355X
+// (100 sweeps of L = 64 .. 256, the whole run): 4 jobs 1.7 ms (resident launches
+// 3.9), 24 jobs 2.2 (4.2), 96 jobs 3.7 (5.2).  With more sites the
+// GPU is full either way, and one workgroup per lattice recomputes no halos.
+// Empty: the resident launches take them (also without memory for the tiles).
+constexpr uint64_t kTileSites = 1ull << 23;
+
+std::vector<potts::TileRun> tile_runs(potts_batch *b, std::vector<std::vector<int>> &run_jobs) {
+  std::vector<potts::TileRun> runs;
+  uint64_t sites = 0;
+  size_t njobs = 0;
+  for (const ResidentGroup &g : b->res_groups)
+    for (int j : g.jobs) {
+      sites += (uint64_t)b->jobs[j].L * b->jobs[j].L;
+      ++njobs;
+    }
+  if (sites == 0 || sites > kTileSites || !grow((void **)&b->other, &b->other_cap, (size_t)sites, 1)) return {};
+  size_t at = 0;
+  for (const ResidentGroup &g : b->res_groups) {
+    potts::TileRun r;
+    r.qc = (uint32_t)g.qc;
+    r.wide = g.wide;
+    std::vector<int> mine;
+    for (int j : g.jobs) {
+      const potts_job &job = b->jobs[j];
+      const int64_t left = b->target[j] - b->done[j];
+      if (left <= 0) continue;
+      potts::add_tile_job(r, b->arena + b->lat_off[j], b->other + at, (uint32_t)job.L, (uint32_t)job.q, job.seed,
+                          &b->thr[(size_t)j * 4], (uint64_t)b->done[j], (uint64_t)left, b->rec_arena + b->rec_off[j],
+                          (uint64_t)b->ring[j]);
+      at += (size_t)job.L * job.L;
+      mine.push_back(j);
+    }
+    if (mine.empty()) continue;
+    runs.push_back(r);
+    run_jobs.push_back(mine);
+  }
+  size_t words = 0, nrefs = 0;
+  for (potts::TileRun &r : runs) {
+    if (!potts::plan_tile_run(r)) return {};
+    words += r.parts_words;
+    nrefs += r.refs.size();
+  }
+  if (!grow((void **)&b->d_tparts, &b->tparts_cap, words, sizeof(uint32_t)) ||
+      !grow((void **)&b->d_tjobs, &b->tjobs_cap, njobs, sizeof(potts::TileParams)) ||
+      !grow((void **)&b->d_trefs, &b->trefs_cap, nrefs, sizeof(potts::TileRef)))
+    return {};
+  words = 0;
+  for (potts::TileRun &r : runs) {
+    potts::place_tile_run(r, b->d_tparts + words);
+    words += r.parts_words;
+  }
+  return runs;
+}
+
 // Queues the rest of the run (every job to its nsweeps) on the stream, as a
 // graph when asked.
 int queue_rest(potts_batch *b) {
@@ -363,11 +446,28 @@ int queue_rest(potts_batch *b) {
   rc = upload(b->d_tiles + b->tiles_cap, all_rev.data(), all_rev.size() * sizeof(all_rev[0]), b->stream);
   if (rc) return rc;
 
+  // the resident jobs: tiles, queued beside the graph (a long run has many
+  // turns), or resident launches within it
+  std::vector<std::vector<int>> run_jobs;
+  const std::vector<potts::TileRun> runs = tile_runs(b, run_jobs);
+  {
+    std::vector<potts::TileParams> tjobs;
+    std::vector<potts::TileRef> trefs;
+    for (const potts::TileRun &r : runs) {
+      tjobs.insert(tjobs.end(), r.jobs.begin(), r.jobs.end());
+      trefs.insert(trefs.end(), r.refs.begin(), r.refs.end());
+    }
+    rc = upload(b->d_tjobs, tjobs.data(), tjobs.size() * sizeof(tjobs[0]), b->stream);
+    if (rc) return rc;
+    rc = upload(b->d_trefs, trefs.data(), trefs.size() * sizeof(trefs[0]), b->stream);
+    if (rc) return rc;
+  }
+
   // resident descriptors, one array per (group, chunk)
   std::vector<potts::ResidentJob> all_res;
   b->res_off.clear();
   std::vector<std::pair<size_t, size_t>> res_launch;  // (group, offset) per launch
-  for (size_t gi = 0; gi < b->res_groups.size(); ++gi) {
+  for (size_t gi = 0; gi < b->res_groups.size() && runs.empty(); ++gi) {
     const ResidentGroup &g = b->res_groups[gi];
     int64_t most = 0;
     for (int j : g.jobs) most = std::max<int64_t>(most, b->target[j] - b->done[j]);
@@ -404,6 +504,10 @@ int queue_rest(potts_batch *b) {
     b->graph = nullptr;
   }
   hipStream_t st = b->stream;
+  if (!runs.empty()) {
+    HIP_TRY(hipEventRecord(b->ev_tiles, st));
+    HIP_TRY(hipStreamWaitEvent(b->side, b->ev_tiles, 0));
+  }
   if (use_graph) HIP_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
   int err = POTTS_OK;
   // branch 1: resident launches on the side stream
@@ -440,6 +544,20 @@ int queue_rest(potts_batch *b) {
     HIP_TRY(hipGraphLaunch(b->exec, st));
   }
   if (err) return err;
+  size_t tjob = 0, tref = 0;
+  for (size_t r = 0; r < runs.size(); ++r) {
+    HIP_TRY(potts::launch_tile_run(runs[r], b->d_tjobs + tjob, b->d_trefs + tref, b->side));
+    for (size_t k = 0; k < runs[r].jobs.size(); ++k)
+      if (potts::tile_job_odd(runs[r].jobs[k]))
+        HIP_TRY(hipMemcpyAsync(b->arena + b->lat_off[run_jobs[r][k]], runs[r].jobs[k].dst,
+                               (size_t)runs[r].jobs[k].L * runs[r].jobs[k].L, hipMemcpyDeviceToDevice, b->side));
+    tjob += runs[r].jobs.size();
+    tref += runs[r].refs.size();
+  }
+  if (!runs.empty()) {
+    HIP_TRY(hipEventRecord(b->ev_tiles, b->side));
+    HIP_TRY(hipStreamWaitEvent(st, b->ev_tiles, 0));
+  }
   b->done = b->target;
   return POTTS_OK;
 }
@@ -508,7 +626,7 @@ int potts_batch_create(const potts_job *jobs, int32_t n, const potts_batch_opts 
     b->owns_stream = true;
   }
   B_TRY(hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking));
-  for (hipEvent_t *e : {&b->ev_fork, &b->ev_join}) B_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
+  for (hipEvent_t *e : {&b->ev_fork, &b->ev_join, &b->ev_tiles}) B_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
   B_TRY(hipEventCreate(&b->ev_t0));
   B_TRY(hipEventCreate(&b->ev_t1));
 

@@ -7,9 +7,10 @@
 // free and the job's lattice and record ring fit in the HBM budget, keeps
 // every admitted lattice and its sweep counter resident on the device, and
 // runs iterations: each iteration advances every active job by up to
-// `quantum` sweeps of its current point in shared launches (LDS-resident
-// launches for L <= 256, one tiled strip launch per colour and sweep for the
-// rest), so requests that arrive while others run join the next iteration.
+// `quantum` sweeps of its current point in shared launches (multi-sweep tile
+// launches for L <= 1024 while those jobs are few; else LDS-resident launches
+// for L <= 256 and one tiled strip launch per colour and sweep for the rest),
+// so requests that arrive while others run join the next iteration.
 // When a point's sweeps are done its summary (derived statistics over the last
 // half of the point's sweeps) is computed on the device; when the last point
 // is done the job's memory is released and its completion time recorded.
@@ -43,6 +44,7 @@
 
 #include "../../include/potts.h"
 #include "kernels.hpp"
+#include "tiles.hpp"
 #include "tune_cache.hpp"
 
 namespace potts {
@@ -130,7 +132,14 @@ struct potts_server {
   potts::StripTile *d_tiles = nullptr;
   potts::ResidentJob *d_res = nullptr;
   potts::StatsParams *d_stats = nullptr;
-  size_t cap_strip = 0, cap_tiles = 0, cap_res = 0, cap_stats = 0;
+  // multi-sweep tile launches: descriptors, table, totals, and the second
+  // buffers of the iteration's lattices (at most kTileSites bytes)
+  potts::TileParams *d_tjobs = nullptr;
+  potts::TileRef *d_trefs = nullptr;
+  uint32_t *d_tparts = nullptr;
+  uint8_t *d_other = nullptr;
+  size_t cap_strip = 0, cap_tiles = 0, cap_res = 0, cap_stats = 0, cap_tjobs = 0, cap_trefs = 0, cap_tparts = 0,
+         cap_other = 0;
   void *h_stage = nullptr;  // pinned staging for descriptor uploads
   size_t cap_stage = 0;
   int64_t iterations = 0;
@@ -441,6 +450,18 @@ bool admit(potts_server *s, Job &j, std::string &err) {
   return true;
 }
 
+// Jobs of L <= 1024 run in multi-sweep tile launches while their lattices hold
+// at most kTileSites sites together, and L <= 2048 too where that leaves no job
+// for the strip launches.  Measured on MI355X (ramps of 4 points x 100 sweeps,
+// submission to last result): 4 jobs of L = 128 .. 1024 2.3 ms, 24 of them 8.9
+// ms, 24 of L = 64 .. 256 3.6 ms; with LDS-resident and strip launches 10.3,
+// 22.1 and 12.2 ms (one workgroup sweeps an L = 256 lattice in 25 us, and a
+// strip launch costs 8 us however small its jobs).  96 jobs of L = 128 .. 1024
+// (34 M sites) take 37 ms either way: with more sites the recomputed halos cost
+// what the launches save.
+constexpr int32_t kTileL = 1024, kTileOnlyL = 2048;
+constexpr uint64_t kTileSites = 1ull << 24;
+
 // One iteration over the active jobs: returns 0 or a negative code (message in err).
 int iterate(potts_server *s, std::string &err) {
   const int64_t quantum = s->cfg.quantum;
@@ -461,9 +482,63 @@ int iterate(potts_server *s, std::string &err) {
     return gs.back();
   };
   std::vector<int64_t> step(s->active.size());
+  uint64_t tile_sites = 0, all_sites = 0;
+  for (const auto &jp : s->active) {
+    const uint64_t n = (uint64_t)jp->req.L * jp->req.L;
+    all_sites += jp->req.L <= kTileOnlyL ? n : kTileSites + 1;
+    if (jp->req.L <= kTileL) tile_sites += n;
+  }
+  const int32_t tile_L = all_sites <= kTileSites ? kTileOnlyL : kTileL;
+  if (tile_L == kTileOnlyL) tile_sites = all_sites;
+  std::vector<potts::TileRun> runs;
+  std::vector<std::vector<Job *>> run_jobs;
+  size_t other_bytes = 0;
+  const bool tiles_ok = tile_sites > 0 && tile_sites <= kTileSites &&
+                        reserve_dev((void **)&s->d_other, &s->cap_other, (size_t)tile_sites, 1);
   for (size_t k = 0; k < s->active.size(); ++k) {
     Job &j = *s->active[k];
     step[k] = std::min<int64_t>(quantum, j.left);
+    if (tiles_ok && j.req.L <= tile_L && step[k] > 0) {
+      const uint32_t *thr = &j.thr[(size_t)j.point * 4];
+      const bool wide = !thr[0] || !thr[1] || !thr[2] || !thr[3];
+      const uint32_t qc = (uint32_t)q_class((uint32_t)j.req.q);
+      size_t r = 0;
+      while (r < runs.size() && (runs[r].qc != qc || runs[r].wide != wide)) ++r;
+      if (r == runs.size()) {
+        runs.emplace_back();
+        runs[r].qc = qc;
+        runs[r].wide = wide;
+        run_jobs.emplace_back();
+      }
+      potts::add_tile_job(runs[r], j.lat, s->d_other + other_bytes, (uint32_t)j.req.L, (uint32_t)j.req.q, j.req.seed, thr,
+                          (uint64_t)j.t, (uint64_t)step[k], j.ring, (uint64_t)j.cap);
+      run_jobs[r].push_back(&j);
+      other_bytes += (size_t)j.req.L * j.req.L;
+    }
+  }
+  // without a plan or memory for the totals the jobs go the other way
+  size_t parts_words = 0;
+  bool placed = !runs.empty();
+  for (potts::TileRun &r : runs) {
+    placed = placed && potts::plan_tile_run(r);
+    parts_words += r.parts_words;
+  }
+  placed = placed && reserve_dev((void **)&s->d_tparts, &s->cap_tparts, parts_words, sizeof(uint32_t));
+  if (placed) {
+    parts_words = 0;
+    for (potts::TileRun &r : runs) {
+      potts::place_tile_run(r, s->d_tparts + parts_words);
+      parts_words += r.parts_words;
+    }
+  } else {
+    runs.clear();
+    run_jobs.clear();
+  }
+  std::set<const Job *> tiled;
+  for (const auto &jobs : run_jobs) tiled.insert(jobs.begin(), jobs.end());
+  for (size_t k = 0; k < s->active.size(); ++k) {
+    Job &j = *s->active[k];
+    if (tiled.count(&j)) continue;
     const uint32_t *thr = &j.thr[(size_t)j.point * 4];
     const bool wide = !thr[0] || !thr[1] || !thr[2] || !thr[3];
     group_of(j.resident ? res_groups : strip_groups, q_class((uint32_t)j.req.q), wide).jobs.push_back(&j);
@@ -516,6 +591,12 @@ int iterate(potts_server *s, std::string &err) {
       res.push_back(r);
     }
   }
+  std::vector<potts::TileParams> tjobs;
+  std::vector<potts::TileRef> trefs;
+  for (const potts::TileRun &r : runs) {
+    tjobs.insert(tjobs.end(), r.jobs.begin(), r.jobs.end());
+    trefs.insert(trefs.end(), r.refs.begin(), r.refs.end());
+  }
   // point summaries that complete in this iteration
   std::vector<Pending> pend;
   std::vector<potts::StatsParams> stats;
@@ -539,6 +620,8 @@ int iterate(potts_server *s, std::string &err) {
   if (!reserve_dev((void **)&s->d_strip, &s->cap_strip, desc.size(), sizeof(potts::StripParams)) ||
       !reserve_dev((void **)&s->d_tiles, &s->cap_tiles, tiles.size(), sizeof(potts::StripTile)) ||
       !reserve_dev((void **)&s->d_res, &s->cap_res, res.size(), sizeof(potts::ResidentJob)) ||
+      !reserve_dev((void **)&s->d_tjobs, &s->cap_tjobs, tjobs.size(), sizeof(potts::TileParams)) ||
+      !reserve_dev((void **)&s->d_trefs, &s->cap_trefs, trefs.size(), sizeof(potts::TileRef)) ||
       !reserve_dev((void **)&s->d_stats, &s->cap_stats, stats.size(), sizeof(potts::StatsParams))) {
     err = "descriptor table allocation failed";
     return POTTS_ENOMEM;
@@ -552,8 +635,9 @@ int iterate(potts_server *s, std::string &err) {
     for (size_t i = 0; i < stats.size(); ++i) stats[i].out = d_out + i * 8;
   }
   const size_t b1 = desc.size() * sizeof(desc[0]), b2 = tiles.size() * sizeof(tiles[0]),
-               b3 = res.size() * sizeof(res[0]), b4 = stats.size() * sizeof(stats[0]);
-  if (!reserve_stage(s, b1 + b2 + b3 + b4)) {
+               b3 = res.size() * sizeof(res[0]), b4 = stats.size() * sizeof(stats[0]),
+               b5 = tjobs.size() * sizeof(tjobs[0]), b6 = trefs.size() * sizeof(trefs[0]);
+  if (!reserve_stage(s, b1 + b2 + b3 + b4 + b5 + b6)) {
     err = "pinned staging allocation failed";
     return POTTS_ENOMEM;
   }
@@ -562,11 +646,27 @@ int iterate(potts_server *s, std::string &err) {
   memcpy(h + b1, tiles.data(), b2);
   memcpy(h + b1 + b2, res.data(), b3);
   memcpy(h + b1 + b2 + b3, stats.data(), b4);
+  memcpy(h + b1 + b2 + b3 + b4, tjobs.data(), b5);
+  memcpy(h + b1 + b2 + b3 + b4 + b5, trefs.data(), b6);
   hipError_t e = hipSuccess;
-  if (b1) e = hipMemcpyAsync(s->d_strip, h, b1, hipMemcpyHostToDevice, s->stream);
+  uint8_t *ht = h + b1 + b2 + b3 + b4;
+  if (b5) e = hipMemcpyAsync(s->d_tjobs, ht, b5, hipMemcpyHostToDevice, s->stream);
+  if (e == hipSuccess && b6) e = hipMemcpyAsync(s->d_trefs, ht + b5, b6, hipMemcpyHostToDevice, s->stream);
+  if (e == hipSuccess && b1) e = hipMemcpyAsync(s->d_strip, h, b1, hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess && b2) e = hipMemcpyAsync(s->d_tiles, h + b1, b2, hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess && b3) e = hipMemcpyAsync(s->d_res, h + b1 + b2, b3, hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess && b4) e = hipMemcpyAsync(s->d_stats, h + b1 + b2 + b3, b4, hipMemcpyHostToDevice, s->stream);
+  // tile runs: several sweeps per launch
+  size_t tjob_off = 0, tref_off = 0;
+  for (size_t r = 0; r < runs.size() && e == hipSuccess; ++r) {
+    e = potts::launch_tile_run(runs[r], s->d_tjobs + tjob_off, s->d_trefs + tref_off, s->stream);
+    for (size_t k = 0; k < runs[r].jobs.size() && e == hipSuccess; ++k)
+      if (potts::tile_job_odd(runs[r].jobs[k]))
+        e = hipMemcpyAsync(run_jobs[r][k]->lat, runs[r].jobs[k].dst, (size_t)runs[r].jobs[k].L * runs[r].jobs[k].L,
+                           hipMemcpyDeviceToDevice, s->stream);
+    tjob_off += runs[r].jobs.size();
+    tref_off += runs[r].refs.size();
+  }
   // resident groups: all of this iteration's sweeps in one launch each
   for (size_t gi = 0; gi < res_groups.size() && e == hipSuccess; ++gi) {
     uint32_t max_L = 0, max_q = 0;
@@ -993,7 +1093,8 @@ int potts_server_stop(potts_server *s) {
   if (s->thread.joinable()) s->thread.join();
   const int rc = s->failed;
   (void)hipStreamSynchronize(s->stream);
-  for (void *p : {(void *)s->d_strip, (void *)s->d_tiles, (void *)s->d_res, (void *)s->d_stats})
+  for (void *p : {(void *)s->d_strip, (void *)s->d_tiles, (void *)s->d_res, (void *)s->d_stats, (void *)s->d_tjobs,
+                  (void *)s->d_trefs, (void *)s->d_tparts, (void *)s->d_other})
     if (p) (void)hipFree(p);
   if (s->h_stage) (void)hipHostFree(s->h_stage);
   if (s->owns_stream) (void)hipStreamDestroy(s->stream);

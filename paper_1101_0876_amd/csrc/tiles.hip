@@ -49,6 +49,7 @@
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "device.hpp"
 #include "kernels.hpp"
@@ -77,7 +78,10 @@ __host__ __device__ inline Counters counters_of(uint32_t q, uint32_t nsweeps, bo
 }
 
 // A lane's item: dword i of both planes, in row r of the region.  The lanes
-// past the last item of a row parity repeat its first one, as halo.
+// past the last item of a row parity repeat its first one, as halo, maybe in
+// another wave and so after it: harmless, since an update repeated with the
+// same words changes nothing (a value taken is proposed to itself, a value
+// refused is refused again).
 struct Item {
   uint32_t i, r;
   uint32_t iu;      // the dword above it in the other plane; the one below is W further
@@ -188,22 +192,14 @@ constexpr uint32_t kStaticHist = PRIV && CMP == 0 ? 64u * 16u * kTileMaxSweeps :
 // on the same wave.  The items' addresses, chunks and masks stay in
 // registers.
 template <int CMP, bool PRIV, bool WIDE, int NI>
-__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void tile_kernel(TileParams p) {
-  __shared__ __align__(16) uint32_t table_words[512];
-  // q <= 16: populations in static LDS, whose address folds into the
-  // instructions' offsets
-  __shared__ __align__(16) uint32_t hist16[kStaticHist<CMP, PRIV>];
-  extern __shared__ __align__(16) uint32_t lds[];
+__device__ __forceinline__ void tile_body(const TileParams &p, uint32_t tile, uint32_t *table_words, uint32_t *hist16,
+                                          uint32_t *lds) {
   const uint32_t ntiles = p.tiles_x * p.tiles_y;
-  if (blockIdx.x >= ntiles) {
-    fold_part(p.fold, blockIdx.x - ntiles, reinterpret_cast<unsigned long long *>(lds));
-    return;
-  }
   uint8_t *table = reinterpret_cast<uint8_t *>(table_words);
   const uint32_t L = p.L, q = p.q;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
-  const uint32_t tyi = blockIdx.x / p.tiles_x, txi = blockIdx.x - tyi * p.tiles_x;
+  const uint32_t tyi = tile / p.tiles_x, txi = tile - tyi * p.tiles_x;
   Region a;
   a.y0 = tyi * p.ty;
   a.x0 = txi * p.tx;
@@ -311,7 +307,7 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4, 4)
   for (int n = 0; n < NI; ++n) store_item(item[n]);
   // the tile's totals of each sweep
   const uint32_t n1 = q + 1u;
-  const uint32_t nparts = tile_parts(ntiles), mine = blockIdx.x % nparts;
+  const uint32_t nparts = tile_parts(ntiles), mine = tile % nparts;
   auto put = [&](uint32_t s, uint32_t word, uint32_t sum) {
     uint32_t *at = p.parts + ((size_t)s * nparts + mine) * n1 + word;
     if (nparts == ntiles)
@@ -337,6 +333,54 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4, 4)
       put(s, 1u + v, bins[s * cn.hist_set + v]);
     }
 }
+
+#define POTTS_TILE_LDS                                                                  \
+  __shared__ __align__(16) uint32_t table_words[512];                                    \
+  /* q <= 16: populations in static LDS, whose address folds into the instructions' */   \
+  /* offsets */                                                                          \
+  __shared__ __align__(16) uint32_t hist16[kStaticHist<CMP, PRIV>];                      \
+  extern __shared__ __align__(16) uint32_t lds[]
+
+template <int CMP, bool PRIV, bool WIDE, int NI>
+__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void tile_kernel(TileParams p) {
+  POTTS_TILE_LDS;
+  const uint32_t ntiles = p.tiles_x * p.tiles_y;
+  if (blockIdx.x >= ntiles)
+    fold_part(p.fold, blockIdx.x - ntiles, reinterpret_cast<unsigned long long *>(lds));
+  else
+    tile_body<CMP, PRIV, WIDE, NI>(p, blockIdx.x, table_words, hist16, lds);
+}
+
+// The same for many lattices (TileTable).
+template <int CMP, bool PRIV, bool WIDE, int NI>
+__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void tile_jobs_kernel(TileTable t) {
+  POTTS_TILE_LDS;
+  const TileRef ref = t.refs[blockIdx.x];
+  TileParams p = t.jobs[ref.job];
+  const uint64_t before = (uint64_t)t.turn * p.sweeps;  // sweeps of the turns before
+  const size_t words = (size_t)p.sweeps * tile_parts(p.tiles_x * p.tiles_y) * (p.q + 1u);
+  if (ref.tile & kTileFold) {
+    RecordFold f = p.fold;
+    if (before == 0 || before - p.sweeps >= p.total) return;
+    f.t0 = p.t0 + before - p.sweeps;
+    f.nsweeps = (uint32_t)min((uint64_t)p.sweeps, p.total - (before - p.sweeps));
+    f.parts = p.parts + ((t.turn & 1u) ? 0u : words);
+    const uint32_t g = ref.tile & ~kTileFold;
+    if (g < fold_groups(f)) fold_part(f, g, reinterpret_cast<unsigned long long *>(lds));
+    return;
+  }
+  if (before >= p.total) return;
+  p.nsweeps = (uint32_t)min((uint64_t)p.sweeps, p.total - before);
+  p.t0 += before;
+  if (t.turn & 1u) {
+    const uint8_t *from = p.dst;
+    p.dst = const_cast<uint8_t *>(p.src);
+    p.src = from;
+    p.parts += words;
+  }
+  tile_body<CMP, PRIV, WIDE, NI>(p, ref.tile, table_words, hist16, lds);
+}
+#undef POTTS_TILE_LDS
 
 // dynamic LDS of a workgroup
 size_t lds_bytes(const TileParams &p, bool priv) {
@@ -472,6 +516,140 @@ bool auto_tile_shape(TileParams &p, int64_t nsweeps) {
       }
   }
   return set_tile_shape(p, btx, bty, bs);
+}
+
+// ---- many lattices per launch -------------------------------------------------
+
+void add_tile_job(TileRun &r, uint8_t *spins, uint8_t *other, uint32_t L, uint32_t q, uint64_t seed,
+                  const uint32_t thr[4], uint64_t t0, uint64_t nsweeps, unsigned long long *ring, uint64_t cap) {
+  TileParams p{};
+  p.src = spins;
+  p.dst = other;
+  p.L = L;
+  p.q = q;
+  p.k0 = (uint32_t)seed;
+  p.k1 = (uint32_t)(seed >> 32);
+  for (int i = 0; i < 4; ++i) p.thr.v[i] = thr[i];
+  p.t0 = t0;
+  p.total = nsweeps;
+  p.fold.n = q + 1u;
+  p.fold.comp = 1;
+  p.fold.ring = ring;
+  p.fold.cap = cap;
+  p.fold.bonds = 2ull * L * L;
+  r.jobs.push_back(p);
+}
+
+bool tile_job_odd(const TileParams &p) { return ((p.total + p.sweeps - 1) / p.sweeps) & 1u; }
+
+// Time of one turn over `tiles` tiles of side x side (tile_launch_us; beyond
+// one tile per CU their issue times add up, a little overlapped).
+static float tile_turn_us(uint32_t side, uint32_t sweeps, uint64_t tiles) {
+  const uint32_t R = side + 4u * sweeps;
+  const Lanes lanes = lanes_of(side, side, tile_halo_x(sweeps), 2u * sweeps);
+  if (lanes.ni != 1 && lanes.ni != 2) return 0;
+  const float n = (float)(lanes.ni * ((lanes.waves + 3u) / 4u));
+  const float issue = 0.2f + 0.2f * n * (1.0f - (float)sweeps / (float)R);
+  const float half = issue > 0.47f ? issue : 0.47f, turns = (float)tiles / 256.0f;
+  const float shared = 0.85f * issue * turns;
+  return 3.5f + 0.4f * n + 2.0f * (float)sweeps * (turns > 1.0f && shared > half ? shared : half);
+}
+
+bool plan_tile_run(TileRun &r) {
+  uint64_t most = 0;
+  std::vector<std::pair<uint32_t, uint64_t>> sizes;  // L, jobs of it
+  for (const TileParams &p : r.jobs) {
+    most = p.total > most ? p.total : most;
+    size_t i = 0;
+    while (i < sizes.size() && sizes[i].first != p.L) ++i;
+    if (i == sizes.size()) sizes.push_back({p.L, 0});
+    ++sizes[i].second;
+  }
+  static const uint32_t sides[] = {16, 24, 32, 48, 64, 80, 96};
+  float best = 0;
+  uint32_t side = 0, sweeps = 0;
+  for (uint32_t t : sides) {
+    uint64_t tiles = 0;
+    for (const auto &z : sizes) tiles += z.second * ((z.first + t - 1) / t) * ((z.first + t - 1) / t);
+    for (uint32_t s = 1; s <= kTileMaxSweeps && s <= most; ++s) {
+      const float us = tile_turn_us(t, s, tiles) * (float)((most + s - 1) / s);
+      if (us > 0 && (best == 0 || us < best)) {
+        best = us;
+        side = t;
+        sweeps = s;
+      }
+    }
+  }
+  if (!side) return false;
+  const Lanes lanes = lanes_of(side, side, tile_halo_x(sweeps), 2u * sweeps);
+  r.ni = lanes.ni;
+  r.waves = lanes.waves;
+  r.refs.clear();
+  r.parts_words = 0;
+  r.turns = 0;
+  r.lds = 0;
+  r.ntiles = 0;
+  std::vector<TileRef> folds;
+  for (size_t j = 0; j < r.jobs.size(); ++j) {
+    TileParams &p = r.jobs[j];
+    // sweeps a turn of this job: at most the shape's, the ring's slots, and so
+    // few that the lattice ends where it began where that can be had
+    uint32_t per = sweeps < p.fold.cap ? sweeps : (uint32_t)p.fold.cap;
+    const uint32_t most_per = per;
+    while (per > 1 && ((p.total + per - 1) / per) % 2 != 0) --per;
+    if (((p.total + per - 1) / per) % 2 != 0) per = most_per;
+    if (!set_tile_shape(p, side, side, per)) return false;
+    const uint32_t tiles = p.tiles_x * p.tiles_y, turns = (uint32_t)((p.total + per - 1) / per);
+    if (tiles > kTileMaxParts) return false;
+    for (uint32_t t = 0; t < tiles; ++t) r.refs.push_back(TileRef{(uint32_t)j, t});
+    p.fold.nparts = tiles;
+    p.fold.nsweeps = per;
+    for (uint32_t g = 0; g < fold_groups(p.fold); ++g) folds.push_back(TileRef{(uint32_t)j, kTileFold | g});
+    r.parts_words += 2u * (size_t)per * tiles * (p.q + 1u);
+    r.turns = turns > r.turns ? turns : r.turns;
+    const size_t lds = lds_bytes(p, r.qc == 0);
+    r.lds = lds > r.lds ? lds : r.lds;
+  }
+  r.ntiles = (uint32_t)r.refs.size();
+  r.refs.insert(r.refs.end(), folds.begin(), folds.end());
+  return true;
+}
+
+void place_tile_run(TileRun &r, uint32_t *parts) {
+  for (TileParams &p : r.jobs) {
+    p.parts = parts;
+    parts += 2u * (size_t)p.sweeps * p.fold.nparts * (p.q + 1u);
+  }
+}
+
+template <int CMP, bool PRIV, bool WIDE>
+static hipError_t launch_run_n(const TileRun &r, const TileParams *jobs, const TileRef *refs, hipStream_t stream) {
+  auto kernel = r.ni == 1 ? tile_jobs_kernel<CMP, PRIV, WIDE, 1> : tile_jobs_kernel<CMP, PRIV, WIDE, 2>;
+  hipError_t e = hipSuccess;
+  if (r.lds > 48u * 1024u)
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)r.lds);
+  const unsigned nfold = (unsigned)(r.refs.size() - r.ntiles);
+  for (uint32_t turn = 0; turn <= r.turns && e == hipSuccess; ++turn) {
+    // the last launch only folds
+    const bool last = turn == r.turns;
+    hipLaunchKernelGGL(kernel, dim3(last ? nfold : r.ntiles + (turn ? nfold : 0u)), dim3(64u * r.waves), r.lds, stream,
+                       TileTable{jobs, last ? refs + r.ntiles : refs, turn});
+    e = hipGetLastError();
+  }
+  return e;
+}
+
+template <bool WIDE>
+static hipError_t launch_run_w(const TileRun &r, const TileParams *jobs, const TileRef *refs, hipStream_t stream) {
+  if (r.qc == 0) return launch_run_n<0, true, WIDE>(r, jobs, refs, stream);
+  if (r.qc <= 2) return launch_run_n<1, false, WIDE>(r, jobs, refs, stream);
+  return launch_run_n<2, false, WIDE>(r, jobs, refs, stream);
+}
+
+hipError_t launch_tile_run(const TileRun &r, const TileParams *jobs, const TileRef *refs, hipStream_t stream) {
+  if (r.ntiles == 0 || r.turns == 0) return hipSuccess;
+  if ((r.ni != 1 && r.ni != 2) || r.waves == 0 || r.waves > kMaxBlock / 64u) return hipErrorInvalidValue;
+  return r.wide ? launch_run_w<true>(r, jobs, refs, stream) : launch_run_w<false>(r, jobs, refs, stream);
 }
 
 hipError_t launch_tiles(const TileParams &p, hipStream_t stream) {

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "fold.hpp"
 #include "kernels.hpp"
 
@@ -39,6 +41,7 @@ struct TileParams {
   uint32_t narrow;           // the region wraps more than once
   uint32_t *parts;           // this launch's totals
   RecordFold fold;           // the launch before it, folded by extra workgroups
+  uint64_t total;            // many lattices per launch (TileRun): sweeps of the whole run
 };
 
 // Sets the shape fields for p.L and p.q; false when no launch of it exists.
@@ -47,5 +50,47 @@ bool set_tile_shape(TileParams &p, uint32_t tx, uint32_t ty, uint32_t sweeps);
 // with, by a model of one launch (tiles.hip).
 bool auto_tile_shape(TileParams &p, int64_t nsweeps);
 hipError_t launch_tiles(const TileParams &p, hipStream_t stream);
+
+// Many lattices per launch: launch `turn` runs sweeps turn * sweeps .. of every
+// job that has them left (TileParams::total), from src to dst on even turns and
+// back on odd ones, into the halves of parts in turn, and folds the turn
+// before.  A workgroup finds its job and tile (or kTileFold | fold workgroup)
+// in a table.
+struct TileRef {
+  uint32_t job, tile;
+};
+constexpr uint32_t kTileFold = 0x80000000u;
+
+struct TileTable {
+  const TileParams *jobs;
+  const TileRef *refs;
+  uint32_t turn;
+};
+
+// One group of such jobs (one comparison class and table form): `refs` holds
+// the tiles' entries, then (from ntiles) the folds'.
+struct TileRun {
+  uint32_t qc = 0;      // comparison class: q <= 16, <= 64, <= 128, <= 256
+  bool wide = false;
+  std::vector<TileParams> jobs;
+  std::vector<TileRef> refs;
+  uint32_t ntiles = 0, turns = 0;
+  size_t parts_words = 0;  // totals of all jobs
+  uint32_t ni = 0, waves = 0;
+  size_t lds = 0;
+};
+
+// Adds a lattice of L % 4 == 0 to the run: nsweeps sweeps from t0, lattice in
+// `spins`, `other` a buffer of its size, records to ring.
+void add_tile_job(TileRun &r, uint8_t *spins, uint8_t *other, uint32_t L, uint32_t q, uint64_t seed,
+                  const uint32_t thr[4], uint64_t t0, uint64_t nsweeps, unsigned long long *ring, uint64_t cap);
+// Picks the run's tile shape, lays out its table and counts its totals.
+bool plan_tile_run(TileRun &r);
+// parts: device memory for parts_words words
+void place_tile_run(TileRun &r, uint32_t *parts);
+// the jobs whose lattice ends in `other` (an odd number of turns)
+bool tile_job_odd(const TileParams &p);
+// All turns of the run, from the run's jobs and refs copied to the device.
+hipError_t launch_tile_run(const TileRun &r, const TileParams *jobs, const TileRef *refs, hipStream_t stream);
 
 }  // namespace potts
