@@ -673,7 +673,10 @@ int potts_nnn_observables(potts_nnn_state *s, potts_nnn_obs *out);
 int potts_nnn_get_spins(potts_nnn_state *s, uint8_t *host_out);
 
 /* Kernel choice for later sweeps; every choice gives identical spins and
- * records.  0: automatic (1 when L <= 16380, else 2); 1: one launch per row
+ * records.  0: automatic (several sweeps per launch on LDS tiles with
+ * recomputed halos when L <= 4800 or L > 16380, on a second lattice buffer
+ * allocated on first use; else, under stream capture or without memory for
+ * that buffer, 1 when L <= 16380, else 2); 1: one launch per row
  * class y mod 3 doing its three colours with rows y-1, y, y+1 staged in LDS;
  * 2: one launch per colour, reading the lattice in place.  Errors: EINVAL
  * (kernel outside 0..2, kernel 1 with L > 16380). */

@@ -16,9 +16,11 @@
 //   - records {e1, e2, hist[q]} per sweep: nearest and diagonal satisfied
 //     bonds (2N each) and the populations.
 //
-// Kernels: up to L = 16380 one launch per row class (y mod 3) does the
+// Kernels: up to L = 4800 and above 16380 whole sweeps on LDS tiles
+// (nnn_tiles.hip).  In between (and under stream capture, or without memory for
+// a second lattice buffer) one launch per row class (y mod 3) does the
 // three colours of that class with the three rows around each active row in
-// LDS (below).  Beyond that, a colour pass runs one thread per 6-byte segment
+// LDS (below).  Beyond 16380 a colour pass runs one thread per 6-byte segment
 // of the rows of its colour: the segment's two active sites (x0 = 6m + cx and x0 + 3) and
 // their neighbours are the six bytes x0-1 .. x0+4 of rows y-1, y, y+1, read
 // as three dwords per row and shifted into place with v_alignbyte and v_perm
@@ -39,6 +41,7 @@
 
 #include "../../include/potts.h"
 #include "device.hpp"
+#include "nnn_tiles.hpp"
 #include "sweep_row.hpp"
 
 struct potts_nnn_state {
@@ -52,6 +55,12 @@ struct potts_nnn_state {
   unsigned long long *scratch = nullptr;  // 2 + q words for measurements
   unsigned long long *stripes = nullptr;  // kStripes partial records of 2 + q words, kept zero between sweeps
   int32_t kernel = 0;  // 0 automatic, 1 row class in LDS, 2 segment per colour
+  // multi-sweep tiles (nnn_tiles.hip), allocated on first use: the second
+  // lattice buffer and the totals of two launches
+  uint8_t *other = nullptr;
+  uint32_t *parts = nullptr;
+  size_t parts_words = 0;
+  bool no_other = false;  // there was no memory for them
   bool have_thr = false;
   double thr_beta = 0.0, thr_j2 = 0.0;
   uint64_t thr[81] = {};
@@ -515,6 +524,8 @@ void release(potts_nnn_state *s) {
   if (s->records) (void)hipFree(s->records);
   if (s->scratch) (void)hipFree(s->scratch);
   if (s->stripes) (void)hipFree(s->stripes);
+  if (s->other) (void)hipFree(s->other);
+  if (s->parts) (void)hipFree(s->parts);
   if (s->stream) (void)hipStreamDestroy(s->stream);
   delete s;
 }
@@ -536,6 +547,76 @@ int table81(double beta, double j2, uint64_t thr[81]) {
   return POTTS_OK;
 }
 
+// The automatic choice: tiles up to L = 4800, where three launches and a fold
+// per sweep cost more than the recomputed halos (L = 4092 36 us per sweep
+// against 56, 6000 76 against 79, 8184 158 against 135 on MI355X, q = 9), and
+// again above kRowsMaxL, where nine passes over memory are the alternative (L =
+// 20004 783 us against 1902).
+bool auto_tiles(int32_t L) { return L <= 4800 || (uint32_t)L > kRowsMaxL; }
+
+// Whether the stream is being captured into a graph: the tiles may have to
+// allocate, and swap the lattice's buffers.
+bool capturing(const potts_nnn_state *s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s->stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st == hipStreamCaptureStatusActive;
+}
+
+// Sweeps on tiles, ping-ponging the lattice between two buffers; POTTS_ENOMEM
+// with nothing done where there is no memory for them.
+int run_tiles(potts_nnn_state *s, const uint64_t thr[81], int64_t nsweeps) {
+  potts::nnn::TileParams p{};
+  p.L = (uint32_t)s->L;
+  p.q = (uint32_t)s->q;
+  if (!potts::nnn::auto_tile_shape(p, nsweeps)) return POTTS_ENOMEM;
+  const size_t words = (size_t)p.sweeps * p.tiles_x * p.tiles_y * (p.q + 2u);
+  if (!s->other && hipMalloc(&s->other, (size_t)s->L * s->L) != hipSuccess) {
+    (void)hipGetLastError();
+    s->other = nullptr;
+    s->no_other = true;
+    return POTTS_ENOMEM;
+  }
+  if (2 * words > s->parts_words) {
+    if (s->parts) (void)hipFree(s->parts);
+    s->parts = nullptr;
+    s->parts_words = 0;
+    if (hipMalloc(&s->parts, 2 * words * sizeof(uint32_t)) != hipSuccess) {
+      (void)hipGetLastError();
+      s->no_other = true;
+      return POTTS_ENOMEM;
+    }
+    s->parts_words = 2 * words;
+  }
+  p.k0 = (uint32_t)s->seed;
+  p.k1 = (uint32_t)(s->seed >> 32);
+  std::copy(thr, thr + 81, p.thr);
+  potts::RecordFold last{};
+  last.n = p.q + 2u;
+  last.nparts = p.tiles_x * p.tiles_y;
+  last.ring = s->records;
+  last.cap = (uint64_t)s->rec_cap;
+  uint32_t turn = 0;
+  for (int64_t done = 0; done < nsweeps; done += p.sweeps, turn ^= 1u) {
+    p.nsweeps = (uint32_t)std::min<int64_t>(p.sweeps, nsweeps - done);
+    p.t0 = (uint64_t)(s->t + done);
+    p.src = s->spins;
+    p.dst = s->other;
+    p.parts = s->parts + turn * words;
+    p.fold = last;
+    NNN_TRY(potts::nnn::launch_tiles(p, s->stream));
+    last.parts = p.parts;
+    last.t0 = p.t0;
+    last.nsweeps = p.nsweeps;
+    std::swap(s->spins, s->other);
+  }
+  NNN_TRY(potts::launch_record_fold(last, s->stream));
+  s->t += nsweeps;
+  return POTTS_OK;
+}
+
 int run(potts_nnn_state *s, const uint64_t thr[81], int64_t nsweeps) {
   if (!s) return fail(POTTS_EINVAL, "state is NULL");
   if (nsweeps < 0) return fail(POTTS_EINVAL, "nsweeps must be >= 0");
@@ -543,6 +624,10 @@ int run(potts_nnn_state *s, const uint64_t thr[81], int64_t nsweeps) {
   for (int i = 0; i < 81; ++i)
     if (thr[i] > (1ull << 32)) return fail(POTTS_EINVAL, "table entries must be <= 2^32");
   if (nsweeps == 0) return POTTS_OK;
+  if (s->kernel == 0 && auto_tiles(s->L) && !s->no_other && !capturing(s)) {
+    const int rc = run_tiles(s, thr, nsweeps);
+    if (rc != POTTS_ENOMEM) return rc;
+  }
   const int64_t rl = s->q + 2;
   NnnPass p{};
   p.g = lattice_of(s);
