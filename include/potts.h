@@ -138,7 +138,9 @@ int potts_sweep_thr(potts_state *s, const uint32_t thr[4], int64_t nsweeps);
  * 3 = colour + 4), k is the first value in the ranking whose cumulative
  * weight exceeds floor(w Z / 2^32).  Records, the sweep counter t and the
  * state are shared with potts_sweep, so both kinds of sweep can be mixed.
- * Asynchronous on the state's stream; any L % 4 == 0.
+ * Asynchronous on the state's stream; any L % 4 == 0 (potts_tune kernel 5 and,
+ * up to L = 4096, the automatic choice: the multi-sweep tile kernel; else the
+ * colour-split one, or one thread per 4-byte chunk).
  * Errors: as potts_sweep. */
 int potts_sweep_heatbath(potts_state *s, double beta, int64_t nsweeps);
 /* The same with a caller-supplied table. */

@@ -48,6 +48,9 @@ struct potts_state {
   // (allocated on first use; no_rag: there was no memory for them)
   uint8_t *rag_planes = nullptr;
   bool no_rag = false;
+  // a sweep call of the state was captured into a graph: its replays find the
+  // lattice and the totals where they were then
+  bool captured = false;
   // heat-bath draw table of the colour-split kernel (device copy, and the host
   // copy it was uploaded from, valid for hb_thr and q)
   potts::HbTable *hb_dev = nullptr;
@@ -70,6 +73,8 @@ struct potts_state {
   uint32_t tile_tx = 0, tile_ty = 0, tile_sweeps = 0;
   uint32_t *tparts = nullptr;
   size_t tparts_words = 0;
+  std::vector<uint32_t *> old_tparts;      // outgrown, named by captured launches
+  uint32_t last_tx = 0, last_ty = 0, last_sweeps = 0;  // automatic shape of the call before
   // pre-drawn random words of a chunk of sweeps (drawn.hpp), allocated on first use
   uint32_t *drawn = nullptr;
   // persistent sweeps on LDS bands (band.hip): the shape asked for (0 =
@@ -158,6 +163,7 @@ void release(potts_state *s) {
   if (s->g_exec) (void)hipGraphExecDestroy(s->g_exec);
   if (s->g_graph) (void)hipGraphDestroy(s->g_graph);
   if (s->g_desc) (void)hipFree(s->g_desc);
+  for (uint32_t *p : s->old_tparts) (void)hipFree(p);
   if (s->g_tiles) (void)hipFree(s->g_tiles);
   if (s->hb_dev) (void)hipFree(s->hb_dev);
   if (s->tparts) (void)hipFree(s->tparts);
@@ -322,7 +328,10 @@ bool rag_ready(potts_state *s) {
 }
 
 bool use_packed(const potts_state *s, int64_t nsweeps) {
-  return packed_ok(s) && (s->kernel == 4 || (s->kernel == 0 && !auto_tiles(s, nsweeps) && !drawn_ok(s)));
+  // (a captured call leaves the lattice where it is)
+  return packed_ok(s) &&
+         (s->kernel == 4 ||
+          (s->kernel == 0 && !drawn_ok(s) && (!auto_tiles(s, nsweeps) || (!s->spins_valid && capturing(s)))));
 }
 
 bool use_strip(const potts_state *s) { return strip_ok(s) && (s->kernel == 1 || s->kernel == 0); }
@@ -352,6 +361,9 @@ bool tile_shape(const potts_state *s, int64_t nsweeps, potts::TileParams *p) {
       if (L % c == 0) ty = c;
     return tile_choice_ok(L, tx, ty, n) && potts::set_tile_shape(*p, tx, ty, n);
   }
+  // a captured call allocates nothing: the shape whose totals there is room for
+  if (s->captured && s->last_sweeps && capturing(s))
+    return potts::set_tile_shape(*p, s->last_tx, s->last_ty, s->last_sweeps);
   return potts::auto_tile_shape(*p, nsweeps);
 }
 
@@ -386,10 +398,18 @@ bool capturing(const potts_state *s) {
   return st == hipStreamCaptureStatusActive;
 }
 
+// A call that is being captured: its replays work on the lattice in place, and
+// so do the calls after it on lattices that would leave it for other planes.
+void note_capture(potts_state *s) {
+  if (!capturing(s)) return;
+  s->captured = true;
+  s->no_rag = true;
+}
+
 bool use_tiles(const potts_state *s, int64_t nsweeps) {
   if (s->kernel == 5) return tiles_ok(s);
   if (s->kernel != 0 || !auto_tiles(s, nsweeps)) return false;
-  return !capturing(s) || (s->L > 256 && s->L < 2048 && s->L % 16 == 0);
+  return !capturing(s) || (s->L > 256 && s->L < 2048 && s->L % 16 == 0 && s->spins_valid);
 }
 
 bool wide_table(const uint32_t thr[4]) { return !thr[0] || !thr[1] || !thr[2] || !thr[3]; }
@@ -589,12 +609,14 @@ uint32_t strip_rows(const potts_state *s) {
 // 28.9 / 33.1 with 2 / 4 rows, 6144 41.3 / 43.7, 7168 54.8 / 55.6, 8192 65.3 /
 // 63.3, 16384 221.9 / 218.1 and 214.3 with 8.  The shortest walk gives most
 // workgroups where launches and per-workgroup overheads bind.
-uint32_t packed_rows(const potts_state *s) {
+// The heat bath's walks, with more work per site, are short up to L = 10240 (L =
+// 8192 113.3 / 116.2, 10240 169.9 / 177.2, 12288 242.1 / 239.6).
+uint32_t packed_rows(const potts_state *s, uint32_t short_to = 7168) {
   if (s->rows) return s->rows;
   const uint32_t L = (uint32_t)s->L;
   for (uint32_t r = 32; r >= 8; r /= 2)
     if (L % r == 0 && (uint64_t)(L / r) * (potts::plane_pitch(L) / 16u) >= (1ull << 20)) return r;
-  return L <= 7168 ? 2 : 4;
+  return L <= short_to ? 2 : 4;
 }
 
 void drop_graph(potts_state *s) {
@@ -660,6 +682,19 @@ int capture_graph(potts_state *s, const potts::StripParams &p, int32_t K, bool w
   return POTTS_OK;
 }
 
+// After sweeps on the colour-split copy.  Caller-owned buffers: the row-major
+// lattice is current after every call, and the next call packs it again, so
+// writes between calls are seen.  L % 32 != 0: it is current too, since a
+// captured call works on it in place.
+int end_planes(potts_state *s) {
+  if (!s->owns_spins || s->L % 32) {
+    HIP_TRY(potts::launch_unpack(planes_of(s), s->spins, (uint32_t)s->L, s->stream));
+    s->spins_valid = true;
+    s->planes_valid = s->owns_spins;
+  }
+  return POTTS_OK;
+}
+
 // Sweeps on the colour-split copy in the second buffer (packed.hip): pack,
 // sweep, unpack; records as the strip path (striped partial records).
 int run_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
@@ -710,26 +745,28 @@ int run_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     HIP_TRY(potts::launch_fold_stripes(p, p.t0 + (uint64_t)count - 1, s->stream));
   }
   s->t += nsweeps;
-  if (!s->owns_spins) {
-    // caller-owned buffers: the row-major lattice is current after every call,
-    // and the next call packs it again, so writes between calls are seen
-    HIP_TRY(potts::launch_unpack(planes_of(s), s->spins, L, s->stream));
-    s->spins_valid = true;
-    s->planes_valid = false;
-  }
-  return POTTS_OK;
+  return end_planes(s);
 }
 
 // Sweeps on LDS tiles, several per launch (tiles.hip), ping-ponging the
 // row-major lattice between the state's two buffers; each launch folds the
 // records of the one before it.
-int run_tiles(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
+int run_tiles(potts_state *s, const uint32_t thr[4], int64_t nsweeps, const potts::HbTable *heatbath = nullptr) {
   potts::TileParams p{};
+  p.heatbath = heatbath;
   if (!tile_shape(s, nsweeps, &p)) return fail(POTTS_EINVAL, "no tile shape for this lattice");
+  if (!s->tile_sweeps && !s->tile_tx && !s->tile_ty) {
+    s->last_tx = p.tx;
+    s->last_ty = p.ty;
+    s->last_sweeps = p.sweeps;
+  }
   const uint32_t ntiles = p.tiles_x * p.tiles_y, nparts = potts::tile_parts(ntiles);
   const size_t words = (size_t)p.sweeps * nparts * (p.q + 1u);
   if (2 * words > s->tparts_words) {
-    if (s->tparts) (void)hipFree(s->tparts);
+    if (s->tparts && s->captured)
+      s->old_tparts.push_back(s->tparts);
+    else if (s->tparts)
+      (void)hipFree(s->tparts);
     s->tparts = nullptr;
     s->tparts_words = 0;
     if (hipMalloc(&s->tparts, 2 * words * sizeof(uint32_t)) != hipSuccess) {
@@ -772,7 +809,7 @@ int run_tiles(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   }
   HIP_TRY(potts::launch_record_fold(last, s->stream));
   if (cur != s->spins) {
-    if (s->owns_spins && !capturing(s)) {
+    if (s->owns_spins && !s->captured) {
       std::swap(s->spins, s->spins2);  // library-owned: the buffers trade roles
     } else {
       // the caller's buffer holds the lattice after every call, and a graph's
@@ -912,6 +949,7 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     if (rc) return rc;
   }
   if (nsweeps == 0) return POTTS_OK;
+  note_capture(s);
   const bool band = use_band(s);
   if (band) return run_band(s, thr, nsweeps);
   const bool rag = use_rag(s, nsweeps) && rag_ready(s);
@@ -980,11 +1018,9 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   return POTTS_OK;
 }
 
-// Heat-bath sweeps on the colour-split copy (heatbath_packed.hip): the draw
-// table is rebuilt and uploaded when the thresholds change; records through
-// the striped partial records, as the Metropolis colour-split path.
-int run_heatbath_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
-  const uint32_t L = (uint32_t)s->L;
+// The heat bath's draw table for thr in device memory, rebuilt and uploaded when
+// the thresholds change.
+int heatbath_table(potts_state *s, const uint32_t thr[4]) {
   if (!s->hb_dev) {
     if (hipMalloc(&s->hb_dev, sizeof(potts::HbTable)) != hipSuccess ||
         hipHostMalloc(&s->hb_host, sizeof(potts::HbTable), hipHostMallocDefault) != hipSuccess) {
@@ -1000,16 +1036,25 @@ int run_heatbath_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) 
     memcpy(s->hb_thr, thr, sizeof(s->hb_thr));
     s->hb_valid = true;
   }
+  return POTTS_OK;
+}
+
+// Heat-bath sweeps on the colour-split copy (heatbath_packed.hip), the draw
+// table in place; records through the striped partial records, as the
+// Metropolis colour-split path.
+int run_heatbath_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
+  const uint32_t L = (uint32_t)s->L;
+  const bool fresh = !s->planes_valid && capturing(s);
   if (!s->planes_valid) {
-    HIP_TRY(potts::launch_pack(s->spins, s->spins2, L, s->stream));
+    HIP_TRY(potts::launch_pack(s->spins, planes_of(s), L, s->stream));
     s->planes_valid = true;
   }
   s->spins_valid = false;
   potts::HbLaunch l{};
   potts::StripParams &p = l.p;
-  const uint32_t rows = packed_rows(s);
-  fill_strip_params(p, s->spins2, L, (uint32_t)s->q, s->seed, thr, rows);
-  potts::set_items(p, L / 32, L, rows);
+  const uint32_t rows = packed_rows(s, 10240);
+  fill_strip_params(p, planes_of(s), L, (uint32_t)s->q, s->seed, thr, rows);
+  potts::set_items(p, potts::plane_pitch(L) / 16u, L, rows);
   p.ring = s->records;
   p.cap = (uint64_t)s->rec_cap;
   p.stripes = s->stripes;
@@ -1031,24 +1076,48 @@ int run_heatbath_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) 
     HIP_TRY(potts::launch_fold_stripes(p, p.t0 + (uint64_t)count - 1, s->stream));
   }
   s->t += nsweeps;
-  if (!s->owns_spins) {
-    HIP_TRY(potts::launch_unpack(s->spins2, s->spins, L, s->stream));
-    s->spins_valid = true;
-    s->planes_valid = false;
-  }
+  const int rc = end_planes(s);
+  if (rc || !fresh) return rc;
+  // a captured call that packed: every replay packs what the one before left
+  HIP_TRY(potts::launch_unpack(planes_of(s), s->spins, L, s->stream));
+  s->spins_valid = true;
+  s->planes_valid = false;
   return POTTS_OK;
 }
 
-// Heat-bath sweeps: on the colour-split copy where the lattice has one (L % 32
-// == 0, kernel 0 or 4), else one thread per 4-byte chunk (kernels.hip); the
+// Heat-bath sweeps on tiles where half sweeps are too short to hide a kernel
+// boundary and calls long enough to share a halo.  Measured on MI355X (q = 6,
+// us per sweep; in brackets one launch per half sweep, colour-split or, for
+// the L that are not multiples of 32, per chunk): L = 64 2.4 (17.5), 1000 4.9
+// (31.3), 1024 5.0 (19.6), 2000 12.6 (110), 2048 12.9 (21.2), 3072 23.0 (33.6),
+// 4096 41.5 (43.2); calls of one sweep at L = 3328 48.5 (51.1), 3584 57.6 (57.1),
+// of two at L = 4096 58.4 (51.7).  Not under stream capture: they may have to
+// allocate.
+bool heatbath_tiles(const potts_state *s, int64_t nsweeps) {
+  if (capturing(s)) return false;
+  return s->kernel == 5 ? tiles_ok(s) : s->kernel == 0 && (s->L <= 3584 || (s->L <= 4096 && nsweeps > 3));
+}
+
+// The colour-split kernel with partial items elsewhere (L = 5000 59.5, one
+// chunk per thread 146.9; 10000 173, 278), as use_rag.
+bool heatbath_rag(const potts_state *s) {
+  return s->L % 32 != 0 && s->kernel == 0 && s->L <= 65520 && !s->no_rag && !capturing(s);
+}
+
+// Heat-bath sweeps: on tiles, else on a colour-split copy (kernel 0, or L % 32
+// == 0 and kernel 4 or 7), else one thread per 4-byte chunk (kernels.hip); the
 // sweep counter and records are shared with the Metropolis sweeps.
 int run_heatbath(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   if (!s) return fail(POTTS_EINVAL, "state is NULL");
   if (nsweeps < 0) return fail(POTTS_EINVAL, "nsweeps must be >= 0");
   if (nsweeps > INT64_MAX - s->t) return fail(POTTS_ERANGE, "sweep counter overflow");
   if (nsweeps == 0) return POTTS_OK;
-  if (packed_ok(s) && (s->kernel == 0 || s->kernel == 4 || s->kernel == 7)) {
-    const int64_t rl = s->q + 1;
+  note_capture(s);
+  const int64_t rl = s->q + 1;
+  const bool tiles = heatbath_tiles(s, nsweeps);
+  if (!tiles && ((packed_ok(s) && (s->kernel == 0 || s->kernel == 4 || s->kernel == 7)) || (heatbath_rag(s) && rag_ready(s)))) {
+    const int rc = heatbath_table(s, thr);
+    if (rc) return rc;
     HIP_TRY(potts::launch_fill_u64(s->records + (s->t % s->rec_cap) * rl, (uint64_t)rl, 0ull, s->stream));
     return run_heatbath_packed(s, thr, nsweeps);
   }
@@ -1057,7 +1126,11 @@ int run_heatbath(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     if (rc) return rc;
     s->planes_valid = false;
   }
-  const int64_t rl = s->q + 1;
+  if (tiles) {
+    const int rc = heatbath_table(s, thr);
+    if (rc) return rc;
+    return run_tiles(s, thr, nsweeps, s->hb_dev);
+  }
   HIP_TRY(potts::launch_fill_u64(s->records + (s->t % s->rec_cap) * rl, (uint64_t)rl, 0ull, s->stream));
   potts::SweepParams p{};
   p.spins = s->spins;

@@ -35,9 +35,10 @@ struct potts3d_state {
   int64_t t = 0;
   uint8_t *spins = nullptr;   // row-major cube
   uint8_t *planes = nullptr;  // colour-split copy
-  bool no_planes = false;     // there was no memory for it: the chunk kernel sweeps
+  bool no_planes = false;     // L % 32 != 0: no memory for it, or calls were captured: the chunk kernel sweeps
   uint32_t *parts = nullptr;  // totals of two sweeps of the colour-split kernel
   size_t parts_words = 0;
+  std::vector<uint32_t *> old_parts;  // outgrown (a captured launch may name them)
   bool spins_valid = true;    // spins holds the current configuration
   bool planes_valid = false;  // planes holds it
   int32_t kernel = 0;         // 0 automatic, 1 colour-split, 2 chunk
@@ -238,6 +239,7 @@ void release(potts3d_state *s) {
   if (s->spins) (void)hipFree(s->spins);
   if (s->planes) (void)hipFree(s->planes);
   if (s->parts) (void)hipFree(s->parts);
+  for (uint32_t *p : s->old_parts) (void)hipFree(p);
   if (s->records) (void)hipFree(s->records);
   if (s->scratch) (void)hipFree(s->scratch);
   if (s->stats_out) (void)hipFree(s->stats_out);
@@ -256,6 +258,15 @@ bool packed_ok(const potts3d_state *s) { return s->L % 32 == 0; }
 // for the second copy the chunk kernel sweeps such an L in place.
 bool use_packed(const potts3d_state *s) {
   return s->kernel == 1 || (s->kernel == 0 && (packed_ok(s) || (s->L > 64 && !s->no_planes)));
+}
+
+bool capturing(const potts3d_state *s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s->stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st == hipStreamCaptureStatusActive;
 }
 
 // longest walk that still leaves >= 2048 workgroups to spread over the chip
@@ -296,6 +307,8 @@ int run(potts3d_state *s, const uint32_t thr[6], int64_t nsweeps) {
   if (nsweeps > INT64_MAX - s->t) return fail(POTTS_ERANGE, "sweep counter overflow");
   if (nsweeps == 0) return POTTS_OK;
   const int64_t rl = s->q + 1;
+  // a graph's replays, and the calls after it, sweep such a cube where it is
+  if (!packed_ok(s) && capturing(s)) s->no_planes = true;
   bool packed = use_packed(s);
   int rc = packed ? sync_planes(s) : sync_spins(s);
   if (rc == POTTS_ENOMEM && s->kernel == 0 && !packed_ok(s)) {
@@ -319,7 +332,7 @@ int run(potts3d_state *s, const uint32_t thr[6], int64_t nsweeps) {
     potts::cube::set_groups(l);
     const size_t words = (size_t)l.groups * (l.q + 1u);
     if (2 * words > s->parts_words) {
-      if (s->parts) (void)hipFree(s->parts);
+      if (s->parts) s->old_parts.push_back(s->parts);
       s->parts = nullptr;
       s->parts_words = 0;
       if (hipMalloc(&s->parts, 2 * words * sizeof(uint32_t)) != hipSuccess) {
@@ -349,6 +362,10 @@ int run(potts3d_state *s, const uint32_t thr[6], int64_t nsweeps) {
     }
     HIP_TRY3(potts::launch_record_fold(last, s->stream));
     s->spins_valid = false;
+    if (!packed_ok(s)) {  // current after every call: a captured one works on it in place
+      rc = sync_spins(s);
+      if (rc) return rc;
+    }
   } else {
     CubeSweep p{};
     p.c = cube_of(s);
@@ -356,7 +373,7 @@ int run(potts3d_state *s, const uint32_t thr[6], int64_t nsweeps) {
     const unsigned grid = grid_of(p.c.nchunks, 4096);
     // the first sweep's slot; each colour-1 launch clears the next one
     const int64_t slot = s->t & (s->rec_cap - 1);
-    HIP_TRY3(hipMemsetAsync(s->records + slot * rl, 0, (size_t)rl * 8, s->stream));
+    HIP_TRY3(potts::launch_fill_u64(s->records + slot * rl, (uint64_t)rl, 0ull, s->stream));
     for (int64_t k = 0; k < nsweeps; ++k) {
       const int64_t t = s->t + k;
       p.t_lo = (uint32_t)(uint64_t)t;

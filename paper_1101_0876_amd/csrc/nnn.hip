@@ -60,7 +60,7 @@ struct potts_nnn_state {
   uint8_t *other = nullptr;
   uint32_t *parts = nullptr;
   size_t parts_words = 0;
-  bool no_other = false;  // there was no memory for them
+  bool no_other = false;  // there was no memory for them, or calls were captured
   bool have_thr = false;
   double thr_beta = 0.0, thr_j2 = 0.0;
   uint64_t thr[81] = {};
@@ -624,7 +624,9 @@ int run(potts_nnn_state *s, const uint64_t thr[81], int64_t nsweeps) {
   for (int i = 0; i < 81; ++i)
     if (thr[i] > (1ull << 32)) return fail(POTTS_EINVAL, "table entries must be <= 2^32");
   if (nsweeps == 0) return POTTS_OK;
-  if (s->kernel == 0 && auto_tiles(s->L) && !s->no_other && !capturing(s)) {
+  // a graph's replays, and the calls after it, sweep the lattice where it is
+  if (capturing(s)) s->no_other = true;
+  if (s->kernel == 0 && auto_tiles(s->L) && !s->no_other) {
     const int rc = run_tiles(s, thr, nsweeps);
     if (rc != POTTS_ENOMEM) return rc;
   }

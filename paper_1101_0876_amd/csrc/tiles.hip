@@ -1,4 +1,4 @@
-// tiles.hip -- several Metropolis sweeps per launch on LDS tiles whose halos
+// tiles.hip -- several Metropolis or heat-bath sweeps per launch on LDS tiles whose halos
 // are recomputed (temporal blocking), for lattices of any L % 4 == 0 whose
 // half sweep is too short to hide a kernel boundary.
 //
@@ -46,12 +46,17 @@
 // took 2.0 us, the sixteen half sweeps 0.6 each, the totals 2.0 and the gap to
 // the next launch 2.6; reading the lattice before anything else, 16-byte clears and
 // four lanes per column of counters brought it to 13.4.
+// The heat bath (heatbath_draw.hpp) differs in an item's words and update; an
+// update repeated with the same words draws the same value.  Its chain from
+// table to table is longer and it issues twice the operations: L = 256 2.5 us per
+// sweep (one launch per half sweep: 19), L = 1000 4.7 (31), L = 2048 13 (21).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
 #include <utility>
 
 #include "device.hpp"
+#include "heatbath_draw.hpp"
 #include "kernels.hpp"
 #include "sweep_row.hpp"
 #include "tiles.hpp"
@@ -130,13 +135,17 @@ __device__ __forceinline__ Item item_of(const TileParams &p, const Region &a, ui
   return it;
 }
 
+// The words of an item's four sites: proposals and acceptance words, or (HB) the
+// heat bath's words in a0 .. a3.
 struct Drawn {
   uint32_t k, a0, a1, a2, a3;
 };
 
-__device__ __forceinline__ Drawn draw(const Item &it, const PhiloxHead &h, uint32_t q) {
+template <bool HB>
+__device__ __forceinline__ Drawn draw_words(const Item &it, const PhiloxHead &h, uint32_t q) {
   Words b0, b1;
   philox_tail2(h.a0 ^ it.c0, h.a0 ^ it.c1, h, b0, b1);
+  if (HB) return Drawn{0u, b0.w0, b0.w2, b1.w0, b1.w2};
   return Drawn{pack4(scale_to_q(b0.w0, q), scale_to_q(b0.w2, q), scale_to_q(b1.w0, q), scale_to_q(b1.w2, q)), b0.w1,
                b0.w3, b1.w1, b1.w3};
 }
@@ -153,17 +162,25 @@ struct Ctx {
 // One item of a half sweep with its words w, and the draw of the next half
 // sweep's words (AHEAD; head h) while its loads are in flight.  No branch: halo
 // items count nothing by adding 0.
-template <int COLOUR, int PAR, int CMP, bool PRIV, bool WIDE, bool AHEAD>
+template <int COLOUR, int PAR, int CMP, bool PRIV, bool WIDE, bool AHEAD, bool HB>
 __device__ __forceinline__ void tile_item(const Ctx &x, const Item &it, Drawn &w, const PhiloxHead &h, uint32_t q) {
   constexpr int O = COLOUR ^ PAR;
-  const uint32_t s = x.act[it.i];
+  const uint32_t s = HB ? 0u : x.act[it.i];
   const uint32_t p = x.pas[it.i];
   const uint32_t u = x.pas[it.iu];
   const uint32_t d = x.pas[it.iu + x.W];
   const uint32_t side = O == 0 ? x.pas[(int)it.i - 1] : x.pas[it.i + 1];
   const Drawn now = w;
-  if (AHEAD) w = draw(it, h, q);
-  const Site4 o = update_sites4<COLOUR, O, CMP, WIDE>(s, p, u, d, side, now.k, now.a0, now.a1, now.a2, now.a3, x.table);
+  if (AHEAD) w = draw_words<HB>(it, h, q);
+  Site4 o;
+  if (HB) {
+    const uint32_t over = O == 0 ? alignbyte(p, side, 3) : alignbyte(side, p, 1);
+    const uint32_t lf = O == 0 ? over : p, rt = O == 0 ? p : over;
+    o.ns = draw4<CMP, WIDE>(u, d, lf, rt, now.a0, now.a1, now.a2, now.a3, x.table);
+    o.nz = COLOUR == 1 ? diff_pattern<CMP>(o.ns, u, d, lf, rt) : 0u;
+  } else {
+    o = update_sites4<COLOUR, O, CMP, WIDE>(s, p, u, d, side, now.k, now.a0, now.a1, now.a2, now.a3, x.table);
+  }
   x.act[it.i] = o.ns;
   const uint32_t one = it.mask & 1u, two = (it.mask >> 16) & 1u;
   if (PRIV && CMP == 0) {
@@ -187,11 +204,15 @@ __device__ __forceinline__ void tile_item(const Ctx &x, const Item &it, Drawn &w
 template <int CMP, bool PRIV>
 constexpr uint32_t kStaticHist = PRIV && CMP == 0 ? 64u * 16u * kTileMaxSweeps : 1u;
 
+// bytes of the acceptance table, or of the heat bath's draw table (HB)
+template <bool WIDE, bool HB>
+constexpr uint32_t kTableBytes = !HB ? 2048u : WIDE ? HbTable::kBytes : HbTable::kCut64;
+
 // NI 1: one item per lane, the even rows' items on the first waves, the odd
 // rows' on the others.  NI 2, 4, 6: NI / 2 items of each parity per lane, all
 // on the same wave.  The items' addresses, chunks and masks stay in
 // registers.
-template <int CMP, bool PRIV, bool WIDE, int NI>
+template <int CMP, bool PRIV, bool WIDE, int NI, bool HB>
 __device__ __forceinline__ void tile_body(const TileParams &p, uint32_t tile, uint32_t *table_words, uint32_t *hist16,
                                           uint32_t *lds) {
   const uint32_t ntiles = p.tiles_x * p.tiles_y;
@@ -237,7 +258,13 @@ __device__ __forceinline__ void tile_body(const TileParams &p, uint32_t tile, ui
     raw[2 * n + 1] = src[item[n].c1];
   }
   // while the lattice is on its way
-  fill_accept_table<WIDE>(table, p.thr);
+  if (HB) {
+    const u32x4 *from = reinterpret_cast<const u32x4 *>(p.heatbath->bytes);
+    for (uint32_t i = threadIdx.x; i < kTableBytes<WIDE, HB> / 16u; i += blockDim.x)
+      reinterpret_cast<u32x4 *>(table)[i] = from[i];
+  } else {
+    fill_accept_table<WIDE>(table, p.thr);
+  }
   u32x4 *clear = reinterpret_cast<u32x4 *>(lds);
   for (uint32_t i = threadIdx.x; i < cn.words / 4u; i += blockDim.x) clear[i] = u32x4{0, 0, 0, 0};
   if (PRIV && CMP == 0) {
@@ -254,7 +281,7 @@ __device__ __forceinline__ void tile_body(const TileParams &p, uint32_t tile, ui
   x.W = a.W;
   auto head = [&](uint32_t hs) {
     const uint64_t t = p.t0 + (hs >> 1);
-    return philox_head((uint32_t)t, (uint32_t)(t >> 32), hs & 1u, p.k0, p.k1);
+    return philox_head((uint32_t)t, (uint32_t)(t >> 32), (hs & 1u) + (HB ? 4u : 0u), p.k0, p.k1);
   };
   // the half sweeps that update anything of item n's group: rows hs + 1 ..
   // R - 2 - hs
@@ -264,7 +291,7 @@ __device__ __forceinline__ void tile_body(const TileParams &p, uint32_t tile, ui
   const PhiloxHead first = head(0);
 #pragma unroll
   for (int n = 0; n < NI; ++n) {
-    if (kAhead) w[n] = draw(item[n], first, q);
+    if (kAhead) w[n] = draw_words<HB>(item[n], first, q);
     const uint32_t lo = group_of(n) * 64u / a.W, hi = min(group_of(n) * 64u + 63u, a.H - 1u) / a.W;
     const uint32_t rlo = 2u * lo + par_of(n), rhi = 2u * hi + par_of(n);
     reach[n] = group_of(n) >= a.groups ? 0u : min(rhi, a.R - 1u - rlo);
@@ -277,11 +304,11 @@ __device__ __forceinline__ void tile_body(const TileParams &p, uint32_t tile, ui
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
       if (hs >= reach[n]) continue;
-      if (!kAhead) w[n] = draw(item[n], h, q);
+      if (!kAhead) w[n] = draw_words<HB>(item[n], h, q);
       if (par_of(n) == 0)
-        tile_item<C, 0, CMP, PRIV, WIDE, kAhead>(x, item[n], w[n], h, q);
+        tile_item<C, 0, CMP, PRIV, WIDE, kAhead, HB>(x, item[n], w[n], h, q);
       else
-        tile_item<C, 1, CMP, PRIV, WIDE, kAhead>(x, item[n], w[n], h, q);
+        tile_item<C, 1, CMP, PRIV, WIDE, kAhead, HB>(x, item[n], w[n], h, q);
     }
     __syncthreads();
   };
@@ -335,25 +362,26 @@ __device__ __forceinline__ void tile_body(const TileParams &p, uint32_t tile, ui
 }
 
 #define POTTS_TILE_LDS                                                                  \
-  __shared__ __align__(16) uint32_t table_words[512];                                    \
+  __shared__ __align__(16) uint32_t table_words[kTableBytes<WIDE, HB> / 4u];              \
   /* q <= 16: populations in static LDS, whose address folds into the instructions' */   \
   /* offsets */                                                                          \
   __shared__ __align__(16) uint32_t hist16[kStaticHist<CMP, PRIV>];                      \
   extern __shared__ __align__(16) uint32_t lds[]
 
-template <int CMP, bool PRIV, bool WIDE, int NI>
+template <int CMP, bool PRIV, bool WIDE, int NI, bool HB>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void tile_kernel(TileParams p) {
   POTTS_TILE_LDS;
   const uint32_t ntiles = p.tiles_x * p.tiles_y;
   if (blockIdx.x >= ntiles)
     fold_part(p.fold, blockIdx.x - ntiles, reinterpret_cast<unsigned long long *>(lds));
   else
-    tile_body<CMP, PRIV, WIDE, NI>(p, blockIdx.x, table_words, hist16, lds);
+    tile_body<CMP, PRIV, WIDE, NI, HB>(p, blockIdx.x, table_words, hist16, lds);
 }
 
 // The same for many lattices (TileTable).
 template <int CMP, bool PRIV, bool WIDE, int NI>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void tile_jobs_kernel(TileTable t) {
+  constexpr bool HB = false;
   POTTS_TILE_LDS;
   const TileRef ref = t.refs[blockIdx.x];
   TileParams p = t.jobs[ref.job];
@@ -378,7 +406,7 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4, 4)
     p.src = from;
     p.parts += words;
   }
-  tile_body<CMP, PRIV, WIDE, NI>(p, ref.tile, table_words, hist16, lds);
+  tile_body<CMP, PRIV, WIDE, NI, HB>(p, ref.tile, table_words, hist16, lds);
 }
 #undef POTTS_TILE_LDS
 
@@ -411,7 +439,7 @@ Lanes lanes_of(uint32_t tx, uint32_t ty, uint32_t hx, uint32_t hy) {
   return Lanes{0u, kMaxWaves};
 }
 
-template <int CMP, bool PRIV, bool WIDE>
+template <int CMP, bool PRIV, bool WIDE, bool HB>
 hipError_t launch_n(const TileParams &p, hipStream_t stream) {
   const Lanes n = lanes_of(p.tx, p.ty, p.hx, p.hy);
   const size_t lds = lds_bytes(p, PRIV);
@@ -425,20 +453,20 @@ hipError_t launch_n(const TileParams &p, hipStream_t stream) {
     return hipGetLastError();
   };
   switch (n.ni) {
-    case 1: return go(tile_kernel<CMP, PRIV, WIDE, 1>);
-    case 2: return go(tile_kernel<CMP, PRIV, WIDE, 2>);
-    case 4: return go(tile_kernel<CMP, PRIV, WIDE, 4>);
-    case 6: return go(tile_kernel<CMP, PRIV, WIDE, 6>);
+    case 1: return go(tile_kernel<CMP, PRIV, WIDE, 1, HB>);
+    case 2: return go(tile_kernel<CMP, PRIV, WIDE, 2, HB>);
+    case 4: return go(tile_kernel<CMP, PRIV, WIDE, 4, HB>);
+    case 6: return go(tile_kernel<CMP, PRIV, WIDE, 6, HB>);
     default: return hipErrorInvalidValue;  // tile_fits has refused it
   }
 }
 
-template <bool WIDE>
+template <bool WIDE, bool HB>
 hipError_t launch_w(const TileParams &p, hipStream_t stream) {
-  if (p.q <= 16) return launch_n<0, true, WIDE>(p, stream);
-  if (private_counters(p)) return launch_n<1, true, WIDE>(p, stream);
-  if (p.q <= 128) return launch_n<1, false, WIDE>(p, stream);
-  return launch_n<2, false, WIDE>(p, stream);
+  if (p.q <= 16) return launch_n<0, true, WIDE, HB>(p, stream);
+  if (private_counters(p)) return launch_n<1, true, WIDE, HB>(p, stream);
+  if (p.q <= 128) return launch_n<1, false, WIDE, HB>(p, stream);
+  return launch_n<2, false, WIDE, HB>(p, stream);
 }
 
 }  // namespace
@@ -475,16 +503,20 @@ bool set_tile_shape(TileParams &p, uint32_t tx, uint32_t ty, uint32_t sweeps) {
 // then per half sweep 0.47 us of latency or the issue time of the n items that
 // a SIMD holds (rows that are not updated any more, S / R of them on average,
 // left out); more tiles than the GPU's 256 CUs take turns.  The shapes it picks
-// took 1 % longer than the best measured ones on average, 6 % at most.  0: no
+// took 1 % longer than the best measured ones on average, 6 % at most.  The heat
+// bath's constants are fitted likewise to 66 shapes of L = 256 .. 2048.  0: no
 // launch of this shape exists.
-static float tile_launch_us(uint32_t L, uint32_t tx, uint32_t ty, uint32_t sweeps) {
+static float tile_launch_us(const TileParams &p, uint32_t tx, uint32_t ty, uint32_t sweeps) {
   const uint32_t R = ty + 4u * sweeps;
   const Lanes lanes = lanes_of(tx, ty, tile_halo_x(sweeps), 2u * sweeps);
   if (!lanes.ni) return 0;
+  const bool hb = p.heatbath != nullptr;
   const float n = (float)(lanes.ni * ((lanes.waves + 3u) / 4u));
-  const float issue = 0.2f + 0.2f * n * (1.0f - (float)sweeps / (float)R);
-  const float turns = (float)((((L + tx - 1) / tx) * ((L + ty - 1) / ty) + 255u) / 256u);
-  return (3.5f + 0.4f * n + 2.0f * (float)sweeps * (issue > 0.47f ? issue : 0.47f)) * (turns > 1.0f ? 0.95f * turns : 1.0f);
+  const float issue = (hb ? 0.3f : 0.2f) + (hb ? 0.45f : 0.2f) * n * (1.0f - (float)sweeps / (float)R);
+  const float least = hb ? 0.6f : 0.47f;
+  const float turns = (float)((((p.L + tx - 1) / tx) * ((p.L + ty - 1) / ty) + 255u) / 256u);
+  return ((hb ? 5.0f : 3.5f) + 0.4f * n + 2.0f * (float)sweeps * (issue > least ? issue : least)) *
+         (turns > 1.0f ? 0.95f * turns : 1.0f);
 }
 
 bool auto_tile_shape(TileParams &p, int64_t nsweeps) {
@@ -506,7 +538,7 @@ bool auto_tile_shape(TileParams &p, int64_t nsweeps) {
       for (uint32_t j = 0; j < nsides; ++j) {
         const uint32_t tx = sides[i], ty = sides[j];
         if (tx > 2u * ty || ty > 2u * tx) continue;
-        const float us = launches * tile_launch_us(p.L, tx, ty, s);
+        const float us = launches * tile_launch_us(p, tx, ty, s);
         if (us > 0 && (bs == 0 || us < best)) {
           best = us;
           btx = tx;
@@ -658,7 +690,8 @@ hipError_t launch_tiles(const TileParams &p, hipStream_t stream) {
       !p.parts || (p.fold.nsweeps && (!p.fold.parts || p.fold.n != p.q + 1u)))
     return hipErrorInvalidValue;
   const bool wide = !p.thr.v[0] || !p.thr.v[1] || !p.thr.v[2] || !p.thr.v[3];
-  return wide ? launch_w<true>(p, stream) : launch_w<false>(p, stream);
+  if (p.heatbath) return wide ? launch_w<true, true>(p, stream) : launch_w<false, true>(p, stream);
+  return wide ? launch_w<true, false>(p, stream) : launch_w<false, false>(p, stream);
 }
 
 }  // namespace potts

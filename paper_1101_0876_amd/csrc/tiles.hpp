@@ -14,7 +14,7 @@ namespace potts {
 
 constexpr uint32_t kTileMaxSweeps = 8;
 constexpr uint32_t kTileMaxL = 65520;
-constexpr size_t kTileMaxLds = 158u * 1024u;  // dynamic LDS of one tile (2 KB more are static)
+constexpr size_t kTileMaxLds = 155u * 1024u;  // dynamic LDS of one tile (its update's table, up to 5 KB, is static)
 
 // A launch's totals (fold.hpp): one part of q + 1 words per sweep and tile, or,
 // past kTileMaxParts tiles, that many parts that tiles share (tile b adds to
@@ -29,6 +29,7 @@ struct TileParams {
   uint32_t L, q;
   uint32_t k0, k1;     // Philox key = seed
   Thresholds thr;
+  const HbTable *heatbath;  // device: the heat bath's draw table; null: Metropolis
   uint64_t t0;         // sweep index of the launch's first sweep
   uint32_t nsweeps;    // sweeps of this launch, at most `sweeps`
   // the shape (set_tile_shape)
