@@ -286,13 +286,19 @@ bool strip_ok(const potts_state *s) { return s->L % 16 == 0 && s->L <= 65520; }
 
 bool resident_ok(const potts_state *s) { return potts::resident_fits((uint32_t)s->L, (uint32_t)s->q); }
 
-// single lattices of at most 512 eight-byte items (L <= 64): the resident
-// kernel with its words drawn beforehand by the whole GPU, the automatic
-// choice (the plain method, L = 64, q = 9, 1000 sweeps: 2.40 ms per run with
-// the words drawn in the resident kernel itself)
+// single lattices of L <= 96, L % 16 == 0: the resident kernel with its words
+// drawn beforehand by the whole GPU, the automatic choice (q = 9, us per sweep,
+// 1000 sweeps a call: L = 64 0.59, 80 0.81, 96 1.10, where tiles take 1.5; 112
+// and more than 16 states 2.4)
 bool drawn_ok(const potts_state *s) { return potts::drawn_fits((uint32_t)s->L, (uint32_t)s->q); }
 
-bool use_drawn(const potts_state *s) { return drawn_ok(s) && (s->kernel == 6 || s->kernel == 0); }
+bool capturing(const potts_state *s);
+
+// Under stream capture the words' buffer has to be there already.
+bool use_drawn(const potts_state *s, int64_t nsweeps) {
+  if (!drawn_ok(s) || (s->kernel != 6 && s->kernel != 0)) return false;
+  return s->drawn || potts::drawn_inline((uint32_t)s->L, nsweeps) || !capturing(s);
+}
 
 // kernel 0: under stream capture, where the tiles leave it to this kernel
 bool use_resident(const potts_state *s) {
@@ -303,7 +309,6 @@ bool use_resident(const potts_state *s) {
 bool packed_ok(const potts_state *s) { return strip_ok(s) && s->L % 32 == 0; }
 
 bool auto_tiles(const potts_state *s, int64_t nsweeps);
-bool capturing(const potts_state *s);
 
 // The colour-split kernel with partial items, the automatic choice for L % 32
 // != 0 above the tiles' range (q = 6, us per sweep on MI355X: L = 5000 33.6, the
@@ -564,7 +569,8 @@ int run_resident(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
 // The same with the random words drawn first by a generator kernel over the
 // whole GPU, kDrawnChunk sweeps at a time.
 int run_drawn(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
-  if (!s->drawn) {
+  const bool itself = potts::drawn_inline((uint32_t)s->L, nsweeps);
+  if (!s->drawn && !itself) {
     if (hipMalloc(&s->drawn, potts::drawn_words_bytes((uint32_t)s->L)) != hipSuccess) {
       (void)hipGetLastError();
       return fail(POTTS_ENOMEM, "allocation of the pre-drawn words failed");
@@ -579,12 +585,11 @@ int run_drawn(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   for (int i = 0; i < 4; ++i) j.thr.v[i] = thr[i];
   j.ring = s->records;
   j.cap = (uint64_t)s->rec_cap;
-  const bool wide = wide_table(thr);
   for (int64_t done = 0; done < nsweeps; done += potts::kDrawnChunk) {
     j.t0 = (uint64_t)(s->t + done);
     j.nsweeps = (uint32_t)std::min<int64_t>(potts::kDrawnChunk, nsweeps - done);
-    HIP_TRY(potts::launch_draw_words(j, s->drawn, s->stream));
-    HIP_TRY(potts::launch_resident_drawn(j, s->drawn, wide, s->stream));
+    if (!itself) HIP_TRY(potts::launch_draw_words(j, s->drawn, s->stream));
+    HIP_TRY(potts::launch_resident_drawn(j, itself ? nullptr : s->drawn, s->stream));
   }
   s->t += nsweeps;
   return POTTS_OK;
@@ -961,7 +966,7 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     if (rc) return rc;
     s->planes_valid = false;
   }
-  if (use_drawn(s)) return run_drawn(s, thr, nsweeps);
+  if (use_drawn(s, nsweeps)) return run_drawn(s, thr, nsweeps);
   if (use_tiles(s, nsweeps)) return run_tiles(s, thr, nsweeps);
   if (use_resident(s)) return run_resident(s, thr, nsweeps);
   const int64_t rl = s->q + 1;
@@ -1345,7 +1350,7 @@ int potts_tune(potts_state *s, int32_t kernel, int32_t strip_rows, int32_t max_g
   if (kernel < 0 || kernel > 7) return fail(POTTS_EINVAL, "kernel must be 0 .. 7");
   if (kernel == 7 && !band_ok(s))
     return fail(POTTS_EINVAL, "band kernel needs L % 32 == 0, L <= 16384 and a band shape whose grid fits the GPU");
-  if (kernel == 6 && !drawn_ok(s))
+  if (kernel == 6 && (s->L > 64 || !drawn_ok(s)))
     return fail(POTTS_EINVAL, "pre-drawn resident kernel needs L % 16 == 0 and L*L <= 4096");
   if (kernel == 5 && (s->L % 16 || !tiles_ok(s))) return fail(POTTS_EINVAL, "tile kernel needs L % 16 == 0 and a tile shape");
   if (kernel == 4 && !packed_ok(s))
