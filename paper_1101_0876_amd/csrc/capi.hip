@@ -75,6 +75,11 @@ struct potts_state {
   size_t tparts_words = 0;
   std::vector<uint32_t *> old_tparts;      // outgrown, named by captured launches
   uint32_t last_tx = 0, last_ty = 0, last_sweeps = 0;  // automatic shape of the call before
+  // pinned host memory, from the first potts_observables on, that takes the last
+  // sweep's record with the ring (kernels 5 and 6): sweep mirror_t's once the
+  // stream has been synchronized, -1: none
+  unsigned long long *mirror = nullptr;
+  int64_t mirror_t = -1;
   // pre-drawn random words of a chunk of sweeps (drawn.hpp), allocated on first use
   uint32_t *drawn = nullptr;
   // persistent sweeps on LDS bands (band.hip): the shape asked for (0 =
@@ -164,6 +169,7 @@ void release(potts_state *s) {
   if (s->g_graph) (void)hipGraphDestroy(s->g_graph);
   if (s->g_desc) (void)hipFree(s->g_desc);
   for (uint32_t *p : s->old_tparts) (void)hipFree(p);
+  if (s->mirror) (void)hipHostFree(s->mirror);
   if (s->g_tiles) (void)hipFree(s->g_tiles);
   if (s->hb_dev) (void)hipFree(s->hb_dev);
   if (s->tparts) (void)hipFree(s->tparts);
@@ -566,6 +572,11 @@ int run_resident(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   return POTTS_OK;
 }
 
+// The host copy of the last record that a call's launches may write (not under
+// stream capture: a replay would write it again later), and its sweep.
+unsigned long long *mirror_of(const potts_state *s) { return capturing(s) ? nullptr : s->mirror; }
+void note_mirror(potts_state *s) { s->mirror_t = mirror_of(s) ? s->t - 1 : -1; }
+
 // The same with the random words drawn first by a generator kernel over the
 // whole GPU, kDrawnChunk sweeps at a time.
 int run_drawn(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
@@ -589,9 +600,11 @@ int run_drawn(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     j.t0 = (uint64_t)(s->t + done);
     j.nsweeps = (uint32_t)std::min<int64_t>(potts::kDrawnChunk, nsweeps - done);
     if (!itself) HIP_TRY(potts::launch_draw_words(j, s->drawn, s->stream));
-    HIP_TRY(potts::launch_resident_drawn(j, itself ? nullptr : s->drawn, s->stream));
+    unsigned long long *mirror = done + potts::kDrawnChunk >= nsweeps ? mirror_of(s) : nullptr;
+    HIP_TRY(potts::launch_resident_drawn(j, itself ? nullptr : s->drawn, mirror, s->stream));
   }
   s->t += nsweeps;
+  note_mirror(s);
   return POTTS_OK;
 }
 
@@ -812,6 +825,7 @@ int run_tiles(potts_state *s, const uint32_t thr[4], int64_t nsweeps, const pott
     last.nsweeps = p.nsweeps;
     std::swap(cur, other);
   }
+  last.mirror = mirror_of(s);
   HIP_TRY(potts::launch_record_fold(last, s->stream));
   if (cur != s->spins) {
     if (s->owns_spins && !s->captured) {
@@ -823,6 +837,7 @@ int run_tiles(potts_state *s, const uint32_t thr[4], int64_t nsweeps, const pott
     }
   }
   s->t += nsweeps;
+  note_mirror(s);
   return POTTS_OK;
 }
 
@@ -955,6 +970,7 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   }
   if (nsweeps == 0) return POTTS_OK;
   note_capture(s);
+  s->mirror_t = -1;
   const bool band = use_band(s);
   if (band) return run_band(s, thr, nsweeps);
   const bool rag = use_rag(s, nsweeps) && rag_ready(s);
@@ -1118,6 +1134,7 @@ int run_heatbath(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   if (nsweeps > INT64_MAX - s->t) return fail(POTTS_ERANGE, "sweep counter overflow");
   if (nsweeps == 0) return POTTS_OK;
   note_capture(s);
+  s->mirror_t = -1;
   const int64_t rl = s->q + 1;
   const bool tiles = heatbath_tiles(s, nsweeps);
   if (!tiles && ((packed_ok(s) && (s->kernel == 0 || s->kernel == 4 || s->kernel == 7)) || (heatbath_rag(s) && rag_ready(s)))) {
@@ -1392,10 +1409,22 @@ int potts_measure(potts_state *s, potts_obs *out) {
 int potts_observables(potts_state *s, potts_obs *out) {
   if (!s || !out) return fail(POTTS_EINVAL, "NULL argument");
   if (s->t == 0 || s->rec_from >= s->t) return potts_measure(s, out);
+  int rc;
+  if (s->mirror_t == s->t - 1) {  // a copy would take longer than the sweeps of a short call
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    rc = band_check(s);
+    if (!rc) fill_obs(s, reinterpret_cast<const int64_t *>(s->mirror), out);
+    return rc;
+  }
   std::vector<int64_t> rec((size_t)(s->q + 1));
-  int rc = copy_records(s, s->t - 1, 1, rec.data());
+  rc = copy_records(s, s->t - 1, 1, rec.data());
   if (rc) return rc;
   fill_obs(s, rec.data(), out);
+  if (!s->mirror && hipHostMalloc(reinterpret_cast<void **>(&s->mirror), (size_t)(s->q + 1) * 8,
+                                  hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    s->mirror = nullptr;
+  }
   return POTTS_OK;
 }
 
@@ -1575,6 +1604,7 @@ int potts_set_spins(potts_state *s, const uint8_t *host_in, int64_t t) {
   s->planes_valid = false;
   s->t = t;
   s->rec_from = t;
+  s->mirror_t = -1;
   return POTTS_OK;
 }
 

@@ -43,7 +43,9 @@ size_t drawn_words_bytes(uint32_t L);
 hipError_t launch_draw_words(const ResidentJob &j, uint32_t *words, hipStream_t stream);
 // Runs sweeps j.t0 .. j.t0 + j.nsweeps - 1 of the single lattice j with the
 // words launch_draw_words wrote for the same j; null: at most kDrawnInline
-// sweeps, drawn by the kernel itself.
-hipError_t launch_resident_drawn(const ResidentJob &j, const uint32_t *words, hipStream_t stream);
+// sweeps, drawn by the kernel itself.  mirror: null, or host memory that takes
+// the last sweep's record too.
+hipError_t launch_resident_drawn(const ResidentJob &j, const uint32_t *words, unsigned long long *mirror,
+                                 hipStream_t stream);
 
 }  // namespace potts

@@ -26,6 +26,7 @@ struct RecordFold {
   unsigned long long *ring;
   uint64_t cap;              // a power of two, at least nsweeps
   uint64_t bonds;
+  unsigned long long *mirror;  // host memory: the last sweep's record once more, or null
 };
 
 // Words of one sweep that a workgroup of the fold sums: 8 lanes side by side (4
@@ -59,8 +60,11 @@ __device__ __forceinline__ void fold_part(const RecordFold &f, uint32_t g, unsig
     if (sum) atomicAdd(&acc[lane], sum);
   }
   __syncthreads();
-  if (row == 0 && w < n)
-    f.ring[((f.t0 + s) & (f.cap - 1)) * (uint64_t)n + w] = w < f.comp ? f.bonds - acc[lane] : acc[lane];
+  if (row == 0 && w < n) {
+    const unsigned long long total = w < f.comp ? f.bonds - acc[lane] : acc[lane];
+    f.ring[((f.t0 + s) & (f.cap - 1)) * (uint64_t)n + w] = total;
+    if (f.mirror && s + 1 == f.nsweeps) f.mirror[w] = total;
+  }
 }
 
 // The fold as a launch of its own, after the last sweep of a call.

@@ -322,7 +322,8 @@ __host__ __device__ inline uint32_t drawn_set_words(uint32_t q, bool priv) {
 // meanwhile: sixteen half sweeps ahead, since one takes less than a fifth of
 // the time of an access to memory.
 template <int CMP, bool PRIV, bool MONO, bool INLINE, int D>
-__global__ __launch_bounds__(1024) void drawn_kernel(ResidentJob j, const uint2 *words) {
+__global__ __launch_bounds__(1024) void drawn_kernel(ResidentJob j, const uint2 *words,
+                                                      unsigned long long *mirror) {
   struct Group {
     uint32_t v[D];
   };
@@ -419,13 +420,16 @@ __global__ __launch_bounds__(1024) void drawn_kernel(ResidentJob j, const uint2 
       sum += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sum, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
       unsigned long long *rec = j.ring + ((j.t0 + s0 + s) & (j.cap - 1)) * (uint64_t)n1;
       // each colour-1 site has 4 bonds; e_sat = 4 * (N/2) - differing neighbours
-      if ((c4 & 3u) == 0) rec[v] = v == 0 ? (unsigned long long)(2u * L * L - (sum >> 4)) : sum;
+      const uint32_t total = v == 0 ? 2u * L * L - (sum >> 4) : sum;
+      if ((c4 & 3u) == 0) rec[v] = total;
+      if ((c4 & 3u) == 0 && mirror && s0 + s + 1 == j.nsweeps) mirror[v] = total;
     }
     if (!PRIV)
       for (uint32_t c = threadIdx.x; c < m * q; c += blockDim.x) {
         const uint32_t s = c / q, v = c - s * q;
         uint32_t *bin = lds + s * set + 64u + v;
         j.ring[((j.t0 + s0 + s) & (j.cap - 1)) * (uint64_t)n1 + 1u + v] = *bin;
+        if (mirror && s0 + s + 1 == j.nsweeps) mirror[1u + v] = *bin;
         *bin = 0;
       }
   };
@@ -530,7 +534,7 @@ hipError_t launch_draw_words(const ResidentJob &j, uint32_t *words, hipStream_t 
 }
 
 template <int CMP, bool PRIV, bool MONO>
-static hipError_t launch_d(const ResidentJob &j, const uint32_t *words, hipStream_t stream) {
+static hipError_t launch_d(const ResidentJob &j, const uint32_t *words, unsigned long long *mirror, hipStream_t stream) {
   const int D = j.L * j.L <= 8192u ? 1 : 2;
   const uint32_t items = (j.L * j.L >> 3) / D, block = (items + 63u) & ~63u;
   const size_t lds = 4u * ((size_t)kDrawnGroup * drawn_set_words(j.q, PRIV) + 2u * D * items);
@@ -541,21 +545,22 @@ static hipError_t launch_d(const ResidentJob &j, const uint32_t *words, hipStrea
         hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kernel, dim3(1), dim3(block), lds, stream, j, w);
+  hipLaunchKernelGGL(kernel, dim3(1), dim3(block), lds, stream, j, w, mirror);
   return hipGetLastError();
 }
 
 template <bool MONO>
-static hipError_t launch_dm(const ResidentJob &j, const uint32_t *words, hipStream_t stream) {
-  if (j.q <= 16) return launch_d<0, true, MONO>(j, words, stream);
-  if (j.q <= 128) return launch_d<1, false, MONO>(j, words, stream);
-  return launch_d<2, false, MONO>(j, words, stream);
+static hipError_t launch_dm(const ResidentJob &j, const uint32_t *words, unsigned long long *mirror, hipStream_t stream) {
+  if (j.q <= 16) return launch_d<0, true, MONO>(j, words, mirror, stream);
+  if (j.q <= 128) return launch_d<1, false, MONO>(j, words, mirror, stream);
+  return launch_d<2, false, MONO>(j, words, mirror, stream);
 }
 
-hipError_t launch_resident_drawn(const ResidentJob &j, const uint32_t *words, hipStream_t stream) {
+hipError_t launch_resident_drawn(const ResidentJob &j, const uint32_t *words, unsigned long long *mirror,
+                                 hipStream_t stream) {
   if (j.nsweeps == 0) return hipSuccess;
   if (!drawn_fits(j.L, j.q) || j.nsweeps > (words ? kDrawnChunk : kDrawnInline)) return hipErrorInvalidValue;
-  return falls(j.thr) ? launch_dm<true>(j, words, stream) : launch_dm<false>(j, words, stream);
+  return falls(j.thr) ? launch_dm<true>(j, words, mirror, stream) : launch_dm<false>(j, words, mirror, stream);
 }
 
 hipError_t launch_resident(const ResidentLaunch &p, unsigned njobs, uint32_t max_L, uint32_t max_q,

@@ -66,3 +66,29 @@ def test_captured_after_a_short_call(potts, oracle_lib, L, k):
             torch.cuda.synchronize()
             oracle_lib.sweeps(s, q, 9, 1, k, thr)
             assert np.array_equal(lat.spins(), s)
+
+
+@pytest.mark.parametrize("L,q", [(16, 5), (64, 200), (100, 9), (1000, 40), (4740, 3)])
+def test_observables_after_every_kind_of_call(potts, oracle_lib, L, q):
+    """The last record's host copy belongs to the last call, whichever kernel
+    took it, and to none after the lattice has been replaced."""
+    thr = oracle_lib.threshold_table(beta_c(q))
+    s = oracle_lib.init(L, q, 4, 1)
+    t = 0
+    with potts.Lattice(L, q, 4, 1) as lat:
+        for kind, n in (("m", 1), ("m", 2), ("h", 1), ("m", 9), ("set", 0), ("m", 1), ("chunk", 1), ("m", 1)):
+            if L > 4000 and n > 2:
+                continue
+            if kind == "set":
+                lat.set_spins(s, t)
+                continue
+            if kind == "chunk":
+                lat.tune(2)
+            (lat.sweep_heatbath_thr if kind == "h" else lat.sweep_thr)(thr, n)
+            rec = (oracle_lib.heatbath_sweeps if kind == "h" else oracle_lib.sweeps)(s, q, 4, t, n, thr)
+            t += n
+            lat.tune(0)
+            for _ in range(2):
+                o = lat.observables()
+                assert (o["t"], o["e_sat"]) == (t, rec[-1][0])
+                assert np.array_equal(o["hist"], rec[-1][1:])
