@@ -168,16 +168,18 @@ int potts_sweep_heatbath_thr(potts_state *s, const uint32_t thr[4], int64_t nswe
  * roles, so potts_device_spins may return the other one afterwards; shape
  * from potts_tune_tiles), 6 = the LDS-resident kernel with its random words
  * drawn beforehand (L % 16 == 0, L <= 64: a generator kernel over the whole
- * GPU writes each site's proposal and acceptance word for up to 1024 sweeps
- * into a device buffer of about 20 bytes per site and sweep, allocated on
- * first use and held until potts_free, and the one-workgroup kernel reads
- * them instead of computing them; the automatic choice for such L),
+ * GPU writes each site's proposal and what its acceptance word accepts for up
+ * to 1024 sweeps into a device buffer of 2 bytes per site and sweep, allocated
+ * on first use and held until potts_free, and the one-workgroup kernel reads
+ * them instead of computing them; calls of up to 4 sweeps draw them in that
+ * kernel; the automatic choice for such L, and for L = 80 and 96),
  * 7 = persistent sweeps on LDS bands (L % 32 == 0, L <= 16384, a band shape
  * from potts_tune_band whose grid the GPU holds at once; the automatic choice
- * for 4032 < L <= 4096 when it can take the lattice): each workgroup keeps
+ * for 4032 < L <= 4096, and for calls of 16 sweeps and more at L = 2048, when
+ * it can take the lattice): each workgroup keeps
  * a band of whole rows of the colour-split lattice in LDS for up to 64 sweeps
  * per cooperative launch and trades its two edge rows with the neighbouring
- * bands after every half sweep (an exchange buffer of 2 x L x L / rows bytes,
+ * bands after every half sweep (an exchange buffer of 4 x L x L / rows bytes,
  * held until potts_free); every wait on a neighbour is bounded (0.25 s, or
  * the microseconds in the environment variable POTTS_BAND_WAIT_US, read at
  * each sweep call), and one that expires, possible only if the grid was not

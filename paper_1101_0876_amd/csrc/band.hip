@@ -13,34 +13,43 @@
 // (Sec. 3.2, counter-based here), so the result is the same bit pattern as
 // every other kernel's.
 //
-// Publication: the waves holding the edge rows update them first, at raised
-// priority, store them into the exchange buffer, wait until those stores
-// have completed and raise one flag per wave.  Wave 0 then waits for the
-// neighbours' flags and copies their edges into its halo rows while the
-// other waves are still updating the interior; a workgroup barrier ends the
-// half sweep.  Flags count half sweeps from an epoch the host advances by
-// 2 x sweeps per launch, so they are never cleared.  Every wait is bounded
+// Publication: the waves holding the edge rows run at raised priority and begin
+// with these; each lane stores its dwords of the edge into the exchange buffer
+// beside the number of the half sweep, in 8-byte words: a reader that finds the
+// number has the value, so no flag has to wait for the stores, and no reader for
+// a flag.  When these waves are done with their items they read the neighbours'
+// edges into the band's halo rows, again until every number is there, while the
+// other waves are still updating. A workgroup barrier ends the half sweep.  Numbers count half sweeps from an epoch the host advances by
+// 2 x sweeps per launch, so the buffer is never cleared.  A word is written
+// again two half sweeps later: by then both neighbours have published the half
+// sweep between, which they began after they had read it.  Every wait is bounded
 // in time: on expiry the workgroup stops and raises a host-visible error
 // word, and the neighbours waiting on it stop the same way, so the grid
 // always drains.  All workgroups must be resident at once (a neighbour wait
 // on a workgroup that has not started would never end): the launch is
 // cooperative, which the runtime refuses when the grid cannot be resident.
 //
-// Ordering without L2 fences: every exchanged word (edge rows and flags) is
-// written and read only with agent-scope atomic accesses, which gfx950
-// performs coherently across its XCDs instead of in an XCD's own L2; a
-// store has completed (vmcnt) once it is visible at that scope.  So edge
-// stores, then a wait for their completion, then the flag store, read in the
-// opposite order with agent-scope loads, hand over the edge rows exactly.
-// An agent-scope release / acquire pair would instead write back and
-// invalidate the whole L2 of the XCD at every publication and every fetch:
-// measured on MI355X at L = 4096, 2.63 against 1.08 ps per site update.
+// Ordering without L2 fences: the exchanged words are written and read only
+// with agent-scope atomic accesses, which gfx950 performs coherently across its
+// XCDs instead of in an XCD's own L2.  An agent-scope release / acquire pair
+// would instead write back and invalidate the whole L2 of the XCD at every
+// publication and every fetch: measured on MI355X at L = 4096, 2.63 against
+// 1.08 ps per site update.
 //
 // Records: the colour-0 pass counts the band's new colour-0 values, the
 // colour-1 pass its new colour-1 values and the differing neighbours of its
 // colour-1 sites (every bond once); per sweep the workgroup adds them into
 // partial-record set s (striped by workgroup), which fold_sets_kernel turns
-// into the ring slot of sweep t0 + s after the launch.
+// into the ring slot of sweep t0 + s after the launch.  There are two sets of
+// counters, so that a sweep's are summed during the colour-0 pass after it
+// (one set, between two barriers, where two would not leave the band its LDS).
+//
+// Measured on MI355X (q = 6, us per sweep, 128 sweeps a call): L = 4096 16.3 (a flag
+// per edge wave raised after its stores had completed, and records summed
+// between two barriers: 17.6), 2048 5.8 (8.4).  Edge rows updated a dword a lane by all waves,
+// the edges fetched by the waves with the fewest items: 16.8 and 6.7.  What is
+// left above the large lattices' 0.82 ps per site update (13.7 us) are the 32
+// LDS-fed items of a SIMD ending together at the barrier.
 #include <hip/hip_runtime.h>
 
 #include "device.hpp"
@@ -66,18 +75,25 @@ struct BandCtx {
   uint32_t prow;         // 16-byte items per plane row: L / 32
   uint32_t prow_magic;   // ceil(2^32 / prow): item -> row by one multiply
   uint32_t R, nitems, nedge;
+  uint32_t parts;        // waves holding edge items
   uint32_t b, up, dn;    // this band, the band above, the band below
   uint32_t y0;           // global row of local row 1
   uint32_t lane, wave, lane_off;
 };
 
+// Dword k of the top or bottom edge row of a band's plane in the exchange buffer.
+__device__ __forceinline__ uint64_t *edge_at(const BandParams &p, const BandCtx &x, uint32_t plane, uint32_t band,
+                                             bool bottom, uint32_t k) {
+  return p.xbuf + ((size_t)(plane * p.bands + band) * 2u + bottom) * (x.half >> 2) + k;
+}
+
 // One 16-byte item: active bytes of local row j at byte column col, updated
 // from the passive rows j-1, j, j+1 (and the passive dword beside the item)
 // exactly as packed_row does from HBM.  edge: exchange-buffer address of the
-// item when row j is an edge row, else null.
+// item when row j is an edge row, else null; tag: the half sweep's number.
 template <int COLOUR, int O, int CMP, bool PRIV, bool WIDE>
 __device__ __forceinline__ uint32_t band_item(const BandCtx &x, uint32_t q, const PhiloxHead &h, uint32_t j,
-                                              uint32_t col, uint32_t ctr, uint8_t *edge) {
+                                              uint32_t col, uint32_t ctr, uint64_t *edge, uint32_t tag) {
   uint8_t *act = x.lds + COLOUR * x.plane + j * x.half;
   const uint8_t *pas = x.lds + (COLOUR ^ 1) * x.plane + j * x.half;
   const u32x4 a = lds16(act + col);
@@ -97,11 +113,10 @@ __device__ __forceinline__ uint32_t band_item(const BandCtx &x, uint32_t q, cons
   out.w = r1.ns_hi;
   *reinterpret_cast<u32x4 *>(act + col) = out;
   if (edge) {
-    uint32_t *e = reinterpret_cast<uint32_t *>(edge);
-    __hip_atomic_store(e + 0, out.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(e + 1, out.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(e + 2, out.z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(e + 3, out.w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t v[4] = {out.x, out.y, out.z, out.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      __hip_atomic_store(edge + k, (uint64_t)tag << 32 | v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (PRIV) {
     count_active_private(x.hist, x.lane_off, r0.ns_lo, r0.ns_hi);
@@ -120,7 +135,7 @@ __device__ __forceinline__ uint32_t band_item(const BandCtx &x, uint32_t q, cons
 // edge row's, then the interior rows 2 .. R-1 in order.
 template <int COLOUR, int CMP, bool PRIV, bool WIDE>
 __device__ __forceinline__ uint32_t band_step(const BandParams &p, const BandCtx &x, const PhiloxHead &h,
-                                              uint32_t i) {
+                                              uint32_t i, uint32_t tag) {
   uint32_t j, k;
   if (i < x.nedge) {
     const uint32_t bottom = i >= x.prow;
@@ -134,90 +149,69 @@ __device__ __forceinline__ uint32_t band_step(const BandParams &p, const BandCtx
   const uint32_t y = x.y0 + j - 1u;  // global row; y0 is even
   const uint32_t col = 16u * k;
   const uint32_t ctr = y * (p.L >> 2) + (col >> 1);
-  uint8_t *edge = nullptr;
-  if (i < x.nedge)
-    edge = p.xbuf + ((size_t)(COLOUR * p.bands + x.b) * 2u + (j == 1u ? 0u : 1u)) * x.half + col;
+  uint64_t *edge = nullptr;
+  if (i < x.nedge) edge = edge_at(p, x, COLOUR, x.b, j != 1u, 4u * k);
   if (((COLOUR + j - 1u) & 1u) == 0)
-    return band_item<COLOUR, 0, CMP, PRIV, WIDE>(x, p.q, h, j, col, ctr, edge);
-  return band_item<COLOUR, 1, CMP, PRIV, WIDE>(x, p.q, h, j, col, ctr, edge);
+    return band_item<COLOUR, 0, CMP, PRIV, WIDE>(x, p.q, h, j, col, ctr, edge, tag);
+  return band_item<COLOUR, 1, CMP, PRIV, WIDE>(x, p.q, h, j, col, ctr, edge, tag);
 }
 
-// Wave 0: waits until both neighbours have published half sweep hs (all
-// their flag words reach epoch + hs + 1), then copies the edge rows of plane
-// COLOUR they published into this band's halo rows of that plane (the band
-// above's bottom row into local row 0, the band below's top row into local
-// row R + 1).  Those rows are read by no item of the current half sweep.
-// Returns false when the wait outlived its bound.
+// Thread i < nedge: reads its item of the edge rows of plane COLOUR that the
+// neighbours published with number tag (the band above's bottom row for local
+// row 0, the band below's top row for local row R + 1) into the halo row, which
+// no item of the current half sweep reads.  Whole waves call it; false when the
+// wait outlived its bound.
 template <int COLOUR>
-__device__ __forceinline__ bool band_fetch(const BandParams &p, const BandCtx &x, uint32_t hs) {
-  const uint32_t target = p.epoch + hs + 1u;
-  const uint32_t np = 2u * p.parts;
-  const uint32_t *f =
-      p.flags + (x.lane < p.parts ? x.up * p.parts + x.lane : x.dn * p.parts + (x.lane - p.parts) % p.parts);
+__device__ __forceinline__ bool band_fetch(const BandParams &p, const BandCtx &x, uint32_t tag) {
+  const uint32_t i = threadIdx.x;
+  const bool mine = i < x.nedge;
+  const bool below = i >= x.prow;
+  const uint32_t k = mine ? i - (below ? x.prow : 0u) : 0u;
+  const uint64_t *e = edge_at(p, x, COLOUR, below ? x.dn : x.up, !below, 4u * k);
   const uint64_t start = wall_clock64();
-  bool ok = true;
+  uint32_t v[4];
   for (;;) {
     bool seen = true;
-    if (x.lane < np)
-      seen = (int32_t)(__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) >= 0;
-    if (__all(seen)) break;
-    if (wall_clock64() - start > p.wait_ticks) {
-      ok = false;
-      break;
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const uint64_t word = __hip_atomic_load(e + n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      v[n] = (uint32_t)word;
+      seen = seen && (uint32_t)(word >> 32) == tag;
     }
+    if (__all(seen || !mine)) break;
+    if (wall_clock64() - start > p.wait_ticks) return false;
     __builtin_amdgcn_s_sleep(1);
   }
-  // the edge loads stay after the flag loads (the loop exit depends on them)
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  if (!ok) return false;
-  uint8_t *act = x.lds + COLOUR * x.plane;
-  for (uint32_t k = x.lane; k < 2u * x.prow; k += 64u) {
-    const uint32_t below = k >= x.prow;  // the band below's top row -> local row R + 1
-    const uint32_t kk = k - below * x.prow;
-    const uint8_t *src =
-        p.xbuf + ((size_t)(COLOUR * p.bands + (below ? x.dn : x.up)) * 2u + (below ? 0u : 1u)) * x.half + 16u * kk;
-    const uint32_t *e = reinterpret_cast<const uint32_t *>(src);
-    u32x4 v;
-    v.x = __hip_atomic_load(e + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    v.y = __hip_atomic_load(e + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    v.z = __hip_atomic_load(e + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    v.w = __hip_atomic_load(e + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *reinterpret_cast<u32x4 *>(act + (below ? (x.R + 1u) * x.half : 0u) + 16u * kk) = v;
-  }
+  if (mine)
+    *reinterpret_cast<u32x4 *>(x.lds + COLOUR * x.plane + (below ? (x.R + 1u) * x.half : 0u) + 16u * k) =
+        u32x4{v[0], v[1], v[2], v[3]};
   return true;
 }
 
-// Half sweep hs (colour COLOUR of sweep t) of the band.  Ends with a
-// workgroup barrier; sets stop[hs & 1] when a neighbour wait failed (two
-// words: a wave still reading the word of half sweep hs after the barrier
-// cannot see a write of half sweep hs + 1, which only wave 0 makes, before
-// every wave reached the next barrier).
-template <int COLOUR, int CMP, bool PRIV, bool WIDE, int BLOCK>
-__device__ __forceinline__ uint32_t band_half(const BandParams &p, const BandCtx &x, uint32_t hs, uint64_t t,
-                                              uint32_t *stop) {
+// Half sweep hs (colour COLOUR of sweep t) of the band; `then`: what a wave does
+// when its items are done, given its differing neighbours (colour 1).  Ends with
+// a workgroup barrier; sets stop[hs & 1] when a neighbour wait failed (two words:
+// a wave still reading the word of half sweep hs after the barrier cannot see a
+// write of half sweep hs + 1, nor of hs + 2, which comes after the next barrier).
+template <int COLOUR, int CMP, bool PRIV, bool WIDE, int BLOCK, class Then>
+__device__ __forceinline__ void band_half(const BandParams &p, const BandCtx &x, uint32_t hs, uint64_t t,
+                                              uint32_t *stop, Then then) {
   const PhiloxHead h = philox_head((uint32_t)t, (uint32_t)(t >> 32), (uint32_t)COLOUR, p.k0, p.k1);
+  const uint32_t tag = p.epoch + hs + 1u;
   uint32_t nz = 0;
   // round 0 holds every edge item (nedge <= BLOCK); their waves go first
-  const bool edge_wave = x.wave < p.parts;
+  const bool edge_wave = x.wave < x.parts;
   if (edge_wave) __builtin_amdgcn_s_setprio(2);
-  if (threadIdx.x < x.nitems) nz += band_step<COLOUR, CMP, PRIV, WIDE>(p, x, h, threadIdx.x);
-  if (edge_wave) {
-    // the wave's edge stores complete before its flag is raised
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (x.lane == 0)
-      __hip_atomic_store(p.flags + x.b * p.parts + x.wave, p.epoch + hs + 1u, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-    __builtin_amdgcn_s_setprio(0);
-  }
-  if (x.wave == 0 && hs + 1u < 2u * p.nsweeps && !band_fetch<COLOUR>(p, x, hs)) {
+  for (uint32_t i = threadIdx.x; i < x.nitems; i += BLOCK) nz += band_step<COLOUR, CMP, PRIV, WIDE>(p, x, h, i, tag);
+  if (edge_wave) __builtin_amdgcn_s_setprio(0);
+  then(nz);
+  if (edge_wave && hs + 1u < 2u * p.nsweeps && !band_fetch<COLOUR>(p, x, tag)) {
     if (x.lane == 0) {
       stop[hs & 1u] = 1u;
       __hip_atomic_store(p.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
-  for (uint32_t i = threadIdx.x + BLOCK; i < x.nitems; i += BLOCK) nz += band_step<COLOUR, CMP, PRIV, WIDE>(p, x, h, i);
   __syncthreads();
-  return nz;
 }
 
 template <int CMP, bool PRIV, bool WIDE, int BLOCK>
@@ -225,15 +219,15 @@ __global__ __launch_bounds__(BLOCK) void band_kernel(BandParams p) {
   constexpr uint32_t kWaves = BLOCK / 64;
   __shared__ __align__(16) uint32_t table_words[512];
   constexpr uint32_t kHistWords = PRIV ? 64u * (CMP == 0 ? 16u : kPrivateHistMaxQ) : 256u;
-  __shared__ __align__(16) uint32_t hist[kHistWords];
-  __shared__ uint32_t partial[256 + kWaves];
+  constexpr uint32_t kSets = PRIV && CMP != 0 ? 1 : 2;
+  __shared__ __align__(16) uint32_t hist[kSets][kHistWords];
+  __shared__ uint32_t nzw[kSets][kWaves];  // differing neighbours, per wave
   __shared__ uint32_t stop[2];
   extern __shared__ __align__(16) uint32_t lds_words[];
 
   BandCtx x;
   x.lds = reinterpret_cast<uint8_t *>(lds_words);
   x.table = reinterpret_cast<const uint8_t *>(table_words);
-  x.hist = reinterpret_cast<uint8_t *>(hist);
   const uint32_t L = p.L, q = p.q, R = p.rows;
   x.half = L >> 1;
   x.prow = L >> 5;
@@ -242,6 +236,7 @@ __global__ __launch_bounds__(BLOCK) void band_kernel(BandParams p) {
   x.R = R;
   x.nitems = R * x.prow;
   x.nedge = 2u * x.prow;
+  x.parts = (x.nedge + 63u) >> 6;
   x.b = blockIdx.x;
   x.up = x.b == 0 ? p.bands - 1u : x.b - 1u;
   x.dn = x.b + 1u == p.bands ? 0u : x.b + 1u;
@@ -253,7 +248,8 @@ __global__ __launch_bounds__(BLOCK) void band_kernel(BandParams p) {
 
   fill_accept_table<WIDE>(reinterpret_cast<uint8_t *>(table_words), p.thr);
   const uint32_t nh = PRIV ? 64u * q : q;
-  for (uint32_t i = threadIdx.x; i < nh; i += BLOCK) hist[i] = 0;
+  for (uint32_t k = 0; k < kSets; ++k)
+    for (uint32_t i = threadIdx.x; i < nh; i += BLOCK) hist[k][i] = 0;
   if (threadIdx.x == 0) stop[0] = stop[1] = 0;
   // both planes, local rows 0 .. R+1 = global rows y0-1 .. y0+R (mod L)
   const uint32_t rows2 = R + 2u;
@@ -272,40 +268,54 @@ __global__ __launch_bounds__(BLOCK) void band_kernel(BandParams p) {
 
   const uint32_t sw = stripe_words(q);
   const unsigned long long bonds = 2ull * R * L;  // 4 bonds per colour-1 site of the band
+  // the counters of sweep s, summed into its partial record and cleared, by the
+  // waves from `first` on
+  auto record = [&](uint32_t s, uint32_t first) {
+    if (x.wave < first) return;
+    uint32_t *pops = hist[s % kSets];
+    unsigned long long *dst =
+        p.stripes + ((uint64_t)s * p.nstripes + (x.b & (p.nstripes - 1u))) * (uint64_t)sw;
+    if (PRIV) {
+      for (uint32_t v = x.wave - first; v < q; v += kWaves - first) {
+        const uint32_t c = wave_sum(pops[v * 64u + x.lane]);
+        pops[v * 64u + x.lane] = 0;
+        if (x.lane == 0 && c) atomicAdd(&dst[1 + v], (unsigned long long)c);
+      }
+    } else {
+      for (uint32_t v = threadIdx.x - 64u * first; v < q; v += BLOCK - 64u * first) {
+        const uint32_t c = pops[v];
+        pops[v] = 0;
+        if (c) atomicAdd(&dst[1 + v], (unsigned long long)c);
+      }
+    }
+    if (threadIdx.x == BLOCK - 1u) {
+      unsigned long long nzt = 0;
+      for (uint32_t w = 0; w < kWaves; ++w) nzt += nzw[s % kSets][w];
+      atomicAdd(&dst[0], bonds - nzt);
+    }
+  };
+  const uint32_t others = x.parts < kWaves ? x.parts : 0u;  // the first wave without edges
   bool failed = false;
   for (uint32_t s = 0; s < p.nsweeps; ++s) {
     const uint64_t t = p.t0 + s;
-    band_half<0, CMP, PRIV, WIDE, BLOCK>(p, x, 2u * s, t, stop);
+    x.hist = reinterpret_cast<uint8_t *>(hist[s % kSets]);
+    band_half<0, CMP, PRIV, WIDE, BLOCK>(p, x, 2u * s, t, stop, [&](uint32_t) {
+      if (kSets == 2 && s > 0) record(s - 1u, others);
+    });
     failed = stop[0] != 0;
     if (failed) break;
-    const uint32_t nz = band_half<1, CMP, PRIV, WIDE, BLOCK>(p, x, 2u * s + 1u, t, stop);
+    band_half<1, CMP, PRIV, WIDE, BLOCK>(p, x, 2u * s + 1u, t, stop, [&](uint32_t nz) {
+      const uint32_t nz_w = wave_sum(nz);
+      if (x.lane == 0) nzw[s % kSets][x.wave] = nz_w;
+    });
     failed = stop[1] != 0;
     if (failed) break;
-    const uint32_t nz_w = wave_sum(nz);
-    if (PRIV) {
-      for (uint32_t v = x.wave; v < q; v += kWaves) {
-        const uint32_t c = wave_sum(hist[v * 64u + x.lane]);
-        hist[v * 64u + x.lane] = 0;
-        if (x.lane == 0) partial[v] = c;
-      }
-    } else {
-      for (uint32_t v = threadIdx.x; v < q; v += BLOCK) {
-        partial[v] = hist[v];
-        hist[v] = 0;
-      }
-    }
-    if (x.lane == 0) partial[q + x.wave] = nz_w;
-    __syncthreads();
-    unsigned long long *dst =
-        p.stripes + ((uint64_t)s * p.nstripes + (x.b & (p.nstripes - 1u))) * (uint64_t)sw;
-    for (uint32_t v = threadIdx.x; v < q; v += BLOCK)
-      if (partial[v]) atomicAdd(&dst[1 + v], (unsigned long long)partial[v]);
-    if (threadIdx.x == 0) {
-      unsigned long long nzt = 0;
-      for (uint32_t w = 0; w < kWaves; ++w) nzt += partial[q + w];
-      atomicAdd(&dst[0], bonds - nzt);
+    if (kSets == 1) {
+      record(s, 0u);
+      __syncthreads();
     }
   }
+  if (kSets == 2 && !failed) record(p.nsweeps - 1u, 0u);
   if (failed) return;
   // the band's rows of both planes back to the lattice
   for (uint32_t i = threadIdx.x; i < 2u * R * x.prow; i += BLOCK) {
@@ -366,13 +376,10 @@ const void *pick(uint32_t q, bool wide, uint32_t block) {
 
 size_t band_lds_bytes(uint32_t L, uint32_t rows) { return (size_t)(rows + 2u) * L; }
 
-uint32_t band_parts(uint32_t L) { return (L / 16u + 63u) / 64u; }
-
 bool band_shape_ok(uint32_t L, uint32_t rows, uint32_t block) {
   if (L % 32 || L < 64 || rows < 2 || rows % 2 || L % rows || L / rows < 2) return false;
   if (block != 256 && block != 512 && block != 1024) return false;
-  // every edge item in round 0; parts flags per neighbour polled by one wave
-  if (L / 16u > block || 2u * band_parts(L) > 64u) return false;
+  if (L / 16u > block) return false;  // every edge item in round 0
   // item -> row by a multiply with ceil(2^32 / prow): exact below 2^32 / prow^2
   const uint64_t prow = L / 32u;
   if (2ull * (rows + 2u) * prow * prow >= (1ull << 32)) return false;
@@ -404,8 +411,8 @@ hipError_t band_resident(uint32_t L, uint32_t q, uint32_t rows, uint32_t block, 
 
 hipError_t launch_band(const BandParams &p, uint32_t block, hipStream_t stream) {
   if (p.nsweeps == 0) return hipSuccess;
-  if (!band_shape_ok(p.L, p.rows, block) || p.bands != p.L / p.rows || p.parts != band_parts(p.L) ||
-      p.nsweeps > kBandMaxSweeps || !p.planes || !p.xbuf || !p.flags || !p.err || !p.stripes ||
+  if (!band_shape_ok(p.L, p.rows, block) || p.bands != p.L / p.rows || p.nsweeps > kBandMaxSweeps || !p.planes ||
+      !p.xbuf || !p.err || !p.stripes ||
       (p.nstripes & (p.nstripes - 1)) || p.q < 2 || p.q > 256)
     return hipErrorInvalidValue;
   const bool wide = !p.thr.v[0] || !p.thr.v[1] || !p.thr.v[2] || !p.thr.v[3];

@@ -83,15 +83,13 @@ struct potts_state {
   // pre-drawn random words of a chunk of sweeps (drawn.hpp), allocated on first use
   uint32_t *drawn = nullptr;
   // persistent sweeps on LDS bands (band.hip): the shape asked for (0 =
-  // automatic), the edge-row exchange buffer, the flags with their epoch, the
+  // automatic), the edge-row exchange buffer, the epoch of its numbers, the
   // partial records of a launch and the host-visible error word
   uint32_t band_rows = 0, band_block = 0;
   uint32_t band_auto_rows = 0, band_auto_block = 0;  // the automatic shape, once found
   bool band_auto_tried = false;
-  uint8_t *bxbuf = nullptr;
-  size_t bxbytes = 0;
-  uint32_t *bflags = nullptr;
-  size_t bflag_words = 0;
+  uint64_t *bxbuf = nullptr;
+  size_t bxwords = 0;
   uint32_t bepoch = 0;
   unsigned long long *bstripes = nullptr;
   uint32_t *berr = nullptr;
@@ -176,7 +174,6 @@ void release(potts_state *s) {
   if (s->rag_planes) (void)hipFree(s->rag_planes);
   if (s->drawn) (void)hipFree(s->drawn);
   if (s->bxbuf) (void)hipFree(s->bxbuf);
-  if (s->bflags) (void)hipFree(s->bflags);
   if (s->bstripes) (void)hipFree(s->bstripes);
   if (s->berr) (void)hipHostFree(s->berr);
   if (s->hb_host) (void)hipHostFree(s->hb_host);
@@ -474,15 +471,21 @@ bool band_ok(potts_state *s) {
   return s->L % 32 == 0 && s->L <= 16384 && band_shape(s, &rows, &block);
 }
 
-// The automatic choice for 4032 < L <= 4096: L = 4096 takes 18.0 us per sweep
-// (q = 6; the colour-split kernel 25.4, the tile kernel 21.9).  Below, bands
-// leave CUs idle (L = 3968, 124 bands of 32 rows: 25.8, tiles 21.4) or their
-// exchange of edge rows (4 us per half sweep, whatever the size) costs more
-// than the tiles' halos, and from L = 8192 no band of whole rows whose grid
-// the GPU holds at once fits in LDS.
-bool auto_band(potts_state *s) { return s->L > 4032 && s->L <= 4096 && band_ok(s); }
+// The automatic choice for 4032 < L <= 4096 (L = 4096 16.3 us per sweep, q = 6;
+// tiles 21.9, the colour-split kernel 25.4) and, for calls of 16 sweeps and more
+// outside stream capture, at L = 2048 (5.8, tiles 7.3; calls of 8 8.9 against
+// 10.2, of 4 12.4 against 12.0): there the bands of 8 rows give every CU the same
+// whole number of items per lane.  Between, bands leave CUs or lanes idle (L =
+// 1984 8.5, tiles 7.0; 3072 14.9, 12.7; 3968 25, 21.4), and from L = 8192 no band
+// of whole rows whose grid the GPU holds at once fits in LDS.
+bool auto_band(potts_state *s, int64_t nsweeps) {
+  const bool size = (s->L > 4032 && s->L <= 4096) || (s->L == 2048 && nsweeps >= 16 && !capturing(s));
+  return size && band_ok(s);
+}
 
-bool use_band(potts_state *s) { return s->kernel == 7 ? band_ok(s) : s->kernel == 0 && auto_band(s); }
+bool use_band(potts_state *s, int64_t nsweeps) {
+  return s->kernel == 7 ? band_ok(s) : s->kernel == 0 && auto_band(s, nsweeps);
+}
 
 }  // namespace
 
@@ -843,12 +846,12 @@ int run_tiles(potts_state *s, const uint32_t thr[4], int64_t nsweeps, const pott
 
 // A neighbour wait of the band kernel that outlived its bound (possible only
 // if its grid was not resident at once) leaves the error word set; the next
-// call that sweeps or reads results reports it, and the flags start over.
+// call that sweeps or reads results reports it, and the numbers start over.
 int band_check(potts_state *s) {
   if (!s->berr || !__atomic_load_n(s->berr, __ATOMIC_ACQUIRE)) return POTTS_OK;
   __atomic_store_n(s->berr, 0u, __ATOMIC_RELEASE);
-  if (s->bflags) HIP_TRY(potts::launch_fill_u64(reinterpret_cast<unsigned long long *>(s->bflags),
-                                                (s->bflag_words + 1) / 2, 0ull, s->stream));
+  if (s->bxbuf)
+    HIP_TRY(potts::launch_fill_u64(reinterpret_cast<unsigned long long *>(s->bxbuf), s->bxwords, 0ull, s->stream));
   s->bepoch = 0;
   return fail(POTTS_EDEVICE, "band sweeps: a wait on a neighbouring band outlived its bound; "
                              "the sweeps since the last successful read are invalid");
@@ -860,30 +863,19 @@ int run_band(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   uint32_t rows, block;
   if (!band_shape(s, &rows, &block)) return fail(POTTS_EINVAL, "no band shape fits this lattice");
   const uint32_t L = (uint32_t)s->L, q = (uint32_t)s->q;
-  const uint32_t bands = L / rows, parts = potts::band_parts(L);
-  const size_t xbytes = (size_t)2 * bands * L;  // [plane][band][top, bottom][L/2]
-  const size_t fwords = (size_t)bands * parts;
-  if (xbytes > s->bxbytes) {
+  const uint32_t bands = L / rows;
+  const size_t xwords = potts::band_xbuf_words(L, bands);
+  if (xwords > s->bxwords) {
     if (s->bxbuf) (void)hipFree(s->bxbuf);
     s->bxbuf = nullptr;
-    s->bxbytes = 0;
-    if (hipMalloc(&s->bxbuf, xbytes) != hipSuccess) {
+    s->bxwords = 0;
+    if (hipMalloc(&s->bxbuf, xwords * sizeof(uint64_t)) != hipSuccess) {
       (void)hipGetLastError();
       return fail(POTTS_ENOMEM, "allocation of the band exchange buffer failed");
     }
-    s->bxbytes = xbytes;
-  }
-  if (fwords != s->bflag_words) {
-    if (s->bflags) (void)hipFree(s->bflags);
-    s->bflags = nullptr;
-    s->bflag_words = 0;
-    if (hipMalloc(&s->bflags, (fwords + 1) / 2 * 8) != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(POTTS_ENOMEM, "allocation of the band flags failed");
-    }
-    HIP_TRY(potts::launch_fill_u64(reinterpret_cast<unsigned long long *>(s->bflags), (fwords + 1) / 2, 0ull,
-                                   s->stream));
-    s->bflag_words = fwords;
+    // no number of an earlier half sweep
+    HIP_TRY(potts::launch_fill_u64(reinterpret_cast<unsigned long long *>(s->bxbuf), xwords, 0ull, s->stream));
+    s->bxwords = xwords;
     s->bepoch = 0;
   }
   const uint32_t sw = potts::stripe_words(q);
@@ -925,7 +917,6 @@ int run_band(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   potts::BandParams p{};
   p.planes = s->spins2;
   p.xbuf = s->bxbuf;
-  p.flags = s->bflags;
   p.err = s->berr;
   p.stripes = s->bstripes;
   p.nstripes = kStripes;
@@ -933,7 +924,6 @@ int run_band(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   p.q = q;
   p.rows = rows;
   p.bands = bands;
-  p.parts = parts;
   p.prow_magic = (uint32_t)(((1ull << 32) + L / 32 - 1) / (L / 32));
   p.k0 = (uint32_t)s->seed;
   p.k1 = (uint32_t)(s->seed >> 32);
@@ -971,7 +961,7 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   if (nsweeps == 0) return POTTS_OK;
   note_capture(s);
   s->mirror_t = -1;
-  const bool band = use_band(s);
+  const bool band = use_band(s, nsweeps);
   if (band) return run_band(s, thr, nsweeps);
   const bool rag = use_rag(s, nsweeps) && rag_ready(s);
   if (!rag && (use_resident(s) || !use_packed(s, nsweeps))) {
