@@ -360,32 +360,39 @@ bool grow(void **p, size_t *cap, size_t n, size_t size) {
   return true;
 }
 
-// The resident jobs' remaining sweeps as multi-sweep tile launches, while
-// their lattices hold at most kTileSites sites together: one workgroup sweeps
+// Jobs' remaining sweeps as multi-sweep tile launches: the resident jobs',
+// while their lattices hold at most kTileSites sites together, or all (`all`): one workgroup sweeps
 // an L = 256 lattice in 27 us and leaves the other CUs idle.  Measured on MI355X
 // (100 sweeps of L = 64 .. 256, the whole run): 4 jobs 1.7 ms (resident launches
 // 3.9), 24 jobs 2.2 (4.2), 96 jobs 3.7 (5.2).  With more sites the
 // GPU is full either way, and one workgroup per lattice recomputes no halos.
-// Empty: the resident launches take them (also without memory for the tiles).
+// Empty: the other launches take them (also without memory for the tiles).
 constexpr uint64_t kTileSites = 1ull << 23;
 
-std::vector<potts::TileRun> tile_runs(potts_batch *b, std::vector<std::vector<int>> &run_jobs) {
+std::vector<potts::TileRun> tile_runs(potts_batch *b, bool all, std::vector<std::vector<int>> &run_jobs) {
   std::vector<potts::TileRun> runs;
+  std::map<std::pair<int, bool>, std::vector<int>> groups;
+  for (const ResidentGroup &g : b->res_groups) groups[{g.qc, g.wide}] = g.jobs;
+  if (all)
+    for (const StripGroup &g : b->strip_groups) {
+      std::vector<int> &to = groups[{g.qc, g.wide}];
+      to.insert(to.end(), g.jobs.begin(), g.jobs.end());
+    }
   uint64_t sites = 0;
   size_t njobs = 0;
-  for (const ResidentGroup &g : b->res_groups)
-    for (int j : g.jobs) {
+  for (const auto &g : groups)
+    for (int j : g.second) {
       sites += (uint64_t)b->jobs[j].L * b->jobs[j].L;
       ++njobs;
     }
-  if (sites == 0 || sites > kTileSites || !grow((void **)&b->other, &b->other_cap, (size_t)sites, 1)) return {};
+  if (sites == 0 || (!all && sites > kTileSites) || !grow((void **)&b->other, &b->other_cap, (size_t)sites, 1)) return {};
   size_t at = 0;
-  for (const ResidentGroup &g : b->res_groups) {
+  for (const auto &g : groups) {
     potts::TileRun r;
-    r.qc = (uint32_t)g.qc;
-    r.wide = g.wide;
+    r.qc = (uint32_t)g.first.first;
+    r.wide = g.first.second;
     std::vector<int> mine;
-    for (int j : g.jobs) {
+    for (int j : g.second) {
       const potts_job &job = b->jobs[j];
       const int64_t left = b->target[j] - b->done[j];
       if (left <= 0) continue;
@@ -417,9 +424,23 @@ std::vector<potts::TileRun> tile_runs(potts_batch *b, std::vector<std::vector<in
   return runs;
 }
 
+// Whether tile launches take every job of the batch: lattices of L <= 2048 with
+// at most kTileSites sites together, where the caller asked for no tuning of the
+// strip launches, which take 20 us a sweep however few the sites.  Measured on
+// MI355X (60 sweeps, ms a run, strip launches for L > 256 in brackets): 24 jobs of
+// L = 128 .. 1024 (5.5 M sites) 0.96 (1.5), 24 of L = 64 .. 2048 (13.4 M) 1.89
+// (2.27), 48 of L = 512 (12.6 M) 2.06 (1.88).
+bool tiles_take_all(const potts_batch *b) {
+  if (b->opts.tune || b->opts.strip_rows || b->opts.tune_cache) return false;
+  uint64_t sites = 0;
+  for (const potts_job &j : b->jobs) sites += j.L <= 2048 ? (uint64_t)j.L * j.L : 1ull << 32;
+  return sites <= kTileSites;
+}
+
 // Queues the rest of the run (every job to its nsweeps) on the stream, as a
-// graph when asked.
-int queue_rest(potts_batch *b) {
+// graph when asked; runs: all of it, when they are not empty.
+int queue_rest(potts_batch *b, std::vector<potts::TileRun> runs, std::vector<std::vector<int>> run_jobs) {
+  const bool all = !runs.empty();
   // strip tables for the remaining sweeps
   std::vector<potts::StripParams> all_desc;
   std::vector<potts::StripTile> all_tiles, all_rev;
@@ -430,7 +451,7 @@ int queue_rest(potts_batch *b) {
   for (const StripGroup &g : b->strip_groups) {
     std::vector<potts::StripParams> desc;
     std::vector<potts::StripTile> tiles;
-    build_strip_tables(b, g, b->shape[b->strip_desc_off.size()], desc, tiles);
+    if (!all) build_strip_tables(b, g, b->shape[b->strip_desc_off.size()], desc, tiles);
     b->strip_desc_off.push_back(all_desc.size());
     b->tile_off.push_back(all_tiles.size());
     b->tile_count.push_back(tiles.size());
@@ -448,8 +469,7 @@ int queue_rest(potts_batch *b) {
 
   // the resident jobs: tiles, queued beside the graph (a long run has many
   // turns), or resident launches within it
-  std::vector<std::vector<int>> run_jobs;
-  const std::vector<potts::TileRun> runs = tile_runs(b, run_jobs);
+  if (!all) runs = tile_runs(b, false, run_jobs);
   {
     std::vector<potts::TileParams> tjobs;
     std::vector<potts::TileRef> trefs;
@@ -658,6 +678,14 @@ int potts_batch_create(const potts_job *jobs, int32_t n, const potts_batch_opts 
   }
   B_TRY(potts::launch_fill_u64(b->rec_arena, rec_words, 0ull, b->stream));
 
+  // Rows per strip item, by the sites that share a launch.  Measured on MI355X
+  // (60 sweeps, ms a run with 2 / 4 / 8 / 16 rows): 33 M sites in 8 lattices
+  // 3.27 / 2.93 / 3.11 / 3.98, 104 M in 96 of L = 128 .. 2048 7.82 / 7.07 / 7.41 / 8.66,
+  // 201 M in 48 12.7 / 11.4 / 11.1 / 11.6, 12.6 M in 48 of L = 512 1.80 / 2.08 / 2.49 / 3.88.
+  uint64_t strip_sites = 0;
+  for (int32_t i = 0; i < n; ++i)
+    if (!resident_job(jobs[i])) strip_sites += (uint64_t)jobs[i].L * jobs[i].L;
+  const uint32_t want_rows = strip_sites <= 1ull << 24 ? 2u : strip_sites <= 1ull << 27 ? 4u : 8u;
   // partition and groups
   std::map<std::pair<int, bool>, size_t> sg, rg;
   size_t nstrip_desc = 0, ntiles_max = 0;
@@ -685,7 +713,7 @@ int potts_batch_create(const potts_job *jobs, int32_t n, const potts_batch_opts 
       b->strip_groups[sg[key]].jobs.push_back(i);
       b->rows[i] = b->opts.strip_rows && j.L % b->opts.strip_rows == 0 && b->opts.strip_rows % 2 == 0
                        ? (uint32_t)b->opts.strip_rows
-                       : potts::auto_strip_rows((uint32_t)j.L, (uint32_t)j.L, 64 * 256);
+                       : want_rows;
       ++nstrip_desc;
       ntiles_max += ((size_t)j.L / 2) * ((size_t)j.L / 16) / 128 + 1;  // rows = 2, 128 lanes: the most tiles
     }
@@ -737,10 +765,14 @@ int potts_batch_run(potts_batch *b) {
   hipEvent_t mark = nullptr;
   HIP_TRY(hipEventCreate(&mark));
   HIP_TRY(hipEventRecord(mark, b->stream));
-  int rc = convert_packed(b, true);
-  if (!rc) rc = autotune(b, b->opts.tune != 0);
-  if (!rc) rc = queue_rest(b);
-  if (!rc) rc = convert_packed(b, false);
+  std::vector<potts::TileRun> runs;
+  std::vector<std::vector<int>> run_jobs;
+  if (tiles_take_all(b)) runs = tile_runs(b, true, run_jobs);
+  const bool all = !runs.empty();
+  int rc = all ? POTTS_OK : convert_packed(b, true);
+  if (!rc && !all) rc = autotune(b, b->opts.tune != 0);
+  if (!rc) rc = queue_rest(b, std::move(runs), std::move(run_jobs));
+  if (!rc && !all) rc = convert_packed(b, false);
   if (!rc) {
     hipError_t e = hipEventRecord(b->ev_t1, b->stream);
     if (e == hipSuccess) e = hipEventSynchronize(b->ev_t1);

@@ -82,3 +82,27 @@ def test_served_ramps(potts, oracle_lib, quantum, large):
             assert np.array_equal(got["spins"], s)
     finally:
         srv.stop()
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("Ls", [(512, 560, 64), (1024, 528), (2048, 16), (320, 272, 608, 304)])
+def test_batches_whole_on_tiles(potts, oracle_lib, Ls, graph):
+    """Small batches with lattices beyond the LDS-resident sizes, of both strip
+    layouts: tiles take all of it, unless the sites are too many or the caller
+    asks for a strip height, and give the same bits; twice, so that the second
+    run continues from the first."""
+    jobs = [dict(L=L, q=q, seed=40 + i, start=i % 2, beta=beta_c(q), nsweeps=n)
+            for i, (L, q, n) in enumerate(zip(Ls, (6, 40, 3, 200), (5, 9, 8, 3)))]
+    want = []
+    for j in jobs:
+        s = oracle_lib.init(j["L"], j["q"], j["seed"], j["start"])
+        rec = oracle_lib.sweeps(s, j["q"], j["seed"], 0, 2 * j["nsweeps"], oracle_lib.threshold_table(j["beta"]))
+        want.append((s, rec))
+    for rows in (0, 4):
+        with potts.Batch(jobs, graph=graph, tune=False, strip_rows=rows) as b:
+            b.run()
+            b.run()
+            for i, (j, (s, rec)) in enumerate(zip(jobs, want)):
+                assert np.array_equal(b.spins(i), s)
+                n = j["nsweeps"]
+                assert np.array_equal(b.records(i, n, n), rec[n:])
