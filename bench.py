@@ -39,10 +39,12 @@ HBM_PEAK_GBS = 8000.0
 ALGO_OPS_PER_SITE = 20.0
 # a sweep reads and writes every uint8 spin once: 2 bytes per site update
 ALGO_BYTES_PER_SITE = 2.0
-KERNEL_SOURCES = ["paper_1101_0876_amd/csrc/packed.hip", "paper_1101_0876_amd/csrc/sweep_row.hpp",
-                  "paper_1101_0876_amd/csrc/device.hpp", "paper_1101_0876_amd/csrc/kernels.hpp"]
+KERNEL_SOURCES = ["paper_1101_0876_amd/csrc/packed.hip", "paper_1101_0876_amd/csrc/edge.hpp",
+                  "paper_1101_0876_amd/csrc/sweep_row.hpp", "paper_1101_0876_amd/csrc/device.hpp",
+                  "paper_1101_0876_amd/csrc/kernels.hpp"]
 # the simple-cubic workload's dominant kernel
 CUBE_SOURCES = ["paper_1101_0876_amd/csrc/cubic_packed.hip", "paper_1101_0876_amd/csrc/cubic.hpp",
+                "paper_1101_0876_amd/csrc/edge.hpp", "paper_1101_0876_amd/csrc/fold.hpp",
                 "paper_1101_0876_amd/csrc/sweep_row.hpp", "paper_1101_0876_amd/csrc/device.hpp",
                 "paper_1101_0876_amd/csrc/kernels.hpp"]
 # the first-plus-second-neighbour workload's kernels (one sweep)

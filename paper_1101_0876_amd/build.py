@@ -19,7 +19,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ["capi.hip", "kernels.hip", "strip.hip", "packed.hip", "resident.hip", "stats.hip", "batch.hip",
            "server.hip", "cubic.hip", "cubic_packed.hip", "nnn.hip", "tune_cache.hip", "heatbath_packed.hip", "noalloc.hip", "tiles.hip", "band.hip", "nnn_tiles.hip"]
 # the kernels whose launch shapes the tuners pick
-TUNED = ["strip.hip", "packed.hip", "sweep_row.hpp", "device.hpp", "kernels.hpp"]
+TUNED = ["strip.hip", "packed.hip", "edge.hpp", "sweep_row.hpp", "device.hpp", "kernels.hpp"]
 LIB_PATH = os.path.join(_HERE, "libpotts.so")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wall"]

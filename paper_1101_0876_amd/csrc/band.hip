@@ -44,12 +44,13 @@
 // counters, so that a sweep's are summed during the colour-0 pass after it
 // (one set, between two barriers, where two would not leave the band its LDS).
 //
-// Measured on MI355X (q = 6, us per sweep, 128 sweeps a call): L = 4096 16.3 (a flag
-// per edge wave raised after its stores had completed, and records summed
-// between two barriers: 17.6), 2048 5.8 (8.4).  Edge rows updated a dword a lane by all waves,
-// the edges fetched by the waves with the fewest items: 16.8 and 6.7.  What is
-// left above the large lattices' 0.82 ps per site update (13.7 us) are the 32
-// LDS-fed items of a SIMD ending together at the barrier.
+// Measured on MI355X (q = 6, us per sweep, 128 sweeps a call): L = 4096 16.3 (a
+// flag per edge wave raised after its stores had completed, and records summed
+// between two barriers: 17.6), 2048 5.8 (8.4).  With the edge rows updated a
+// dword a lane by all waves and the edges fetched by the waves with the fewest
+// items: 16.8 and 6.7.  What is left above the large lattices' 0.82 ps per site
+// update (13.7 us) is the barrier of each half sweep: the waves of a SIMD start
+// and end together, and nothing covers their first reads and last items.
 #include <hip/hip_runtime.h>
 
 #include "device.hpp"

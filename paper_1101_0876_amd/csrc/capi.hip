@@ -474,8 +474,8 @@ bool band_ok(potts_state *s) {
 // The automatic choice for 4032 < L <= 4096 (L = 4096 16.3 us per sweep, q = 6;
 // tiles 21.9, the colour-split kernel 25.4) and, for calls of 16 sweeps and more
 // outside stream capture, at L = 2048 (5.8, tiles 7.3; calls of 8 8.9 against
-// 10.2, of 4 12.4 against 12.0): there the bands of 8 rows give every CU the same
-// whole number of items per lane.  Between, bands leave CUs or lanes idle (L =
+// 10.2, of 4 12.4 against 12.0): there bands of 16 and 8 rows give every CU the
+// same whole number of items per lane.  Between, bands leave CUs or lanes idle (L =
 // 1984 8.5, tiles 7.0; 3072 14.9, 12.7; 3968 25, 21.4), and from L = 8192 no band
 // of whole rows whose grid the GPU holds at once fits in LDS.
 bool auto_band(potts_state *s, int64_t nsweeps) {
