@@ -385,7 +385,7 @@ bool tiles_ok(const potts_state *s) {
 // us per sweep, 200 sweeps a call; in brackets what else takes the size): L =
 // 100 1.6 (one launch per half sweep 5.6), 256 1.6 (LDS-resident 21.9), 512
 // 1.8 (colour-split 12.1), 1000 3.2 (chunk 29.8), 1024 3.2 (colour-split
-// 12.0), 2048 7.3 (bands 8.0), 2560 10.1 (bands 16.9), 3584 18.2 (bands 19.8),
+// 12.0), 2048 7.3 (bands 5.8, see auto_band), 2560 10.1 (bands 14.5), 3584 17.4 (bands 17.8),
 // 3968 21.4 (bands 25.8), 4224 23.1 (colour-split 32.2), 4608 27.8 (31.1), 4864
 // 32.6 (31.4).  A call of one sweep recomputes its halo for nothing: there the
 // colour-split kernel takes over above 3584 (41 against 47 us a call at L =
@@ -472,14 +472,15 @@ bool band_ok(potts_state *s) {
 }
 
 // The automatic choice for 4032 < L <= 4096 (L = 4096 16.3 us per sweep, q = 6;
-// tiles 21.9, the colour-split kernel 25.4) and, for calls of 16 sweeps and more
-// outside stream capture, at L = 2048 (5.8, tiles 7.3; calls of 8 8.9 against
-// 10.2, of 4 12.4 against 12.0): there bands of 16 and 8 rows give every CU the
+// tiles 21.9, the colour-split kernel 25.4) and, for calls of 48 sweeps and more
+// outside stream capture, at L = 2048 (5.8, tiles 7.3; on a new state, which has
+// the exchange buffer and the planes to set up, 47 sweeps 335 us against 377, 16
+// sweeps 178 against 150): there bands of 16 and 8 rows give every CU the
 // same whole number of items per lane.  Between, bands leave CUs or lanes idle (L =
 // 1984 8.5, tiles 7.0; 3072 14.9, 12.7; 3968 25, 21.4), and from L = 8192 no band
 // of whole rows whose grid the GPU holds at once fits in LDS.
 bool auto_band(potts_state *s, int64_t nsweeps) {
-  const bool size = (s->L > 4032 && s->L <= 4096) || (s->L == 2048 && nsweeps >= 16 && !capturing(s));
+  const bool size = (s->L > 4032 && s->L <= 4096) || (s->L == 2048 && nsweeps >= 48 && !capturing(s));
   return size && band_ok(s);
 }
 
