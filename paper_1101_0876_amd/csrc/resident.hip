@@ -404,8 +404,11 @@ __global__ __launch_bounds__(1024) void drawn_kernel(ResidentJob j, const uint2 
     __syncthreads();
   };
   // the records of sweeps s0 .. s0 + m - 1 from the counter sets, which are
-  // cleared; four lanes per 64-lane column
+  // cleared; four lanes per 64-lane column.  On a ring of fewer slots only the
+  // last `cap` of them are stored: two sweeps of the group that share a slot are
+  // written by different lanes, in no order.
   auto records = [&](uint32_t s0, uint32_t m) {
+    const uint32_t skip = j.cap < m ? m - (uint32_t)j.cap : 0u;
     count(own[1], m - 1u);
     atomicAdd(&lds[(m - 1u) * set + lane], nz * has);
     __syncthreads();
@@ -421,14 +424,14 @@ __global__ __launch_bounds__(1024) void drawn_kernel(ResidentJob j, const uint2 
       unsigned long long *rec = j.ring + ((j.t0 + s0 + s) & (j.cap - 1)) * (uint64_t)n1;
       // each colour-1 site has 4 bonds; e_sat = 4 * (N/2) - differing neighbours
       const uint32_t total = v == 0 ? 2u * L * L - (sum >> 4) : sum;
-      if ((c4 & 3u) == 0) rec[v] = total;
+      if ((c4 & 3u) == 0 && s >= skip) rec[v] = total;
       if ((c4 & 3u) == 0 && mirror && s0 + s + 1 == j.nsweeps) mirror[v] = total;
     }
     if (!PRIV)
       for (uint32_t c = threadIdx.x; c < m * q; c += blockDim.x) {
         const uint32_t s = c / q, v = c - s * q;
         uint32_t *bin = lds + s * set + 64u + v;
-        j.ring[((j.t0 + s0 + s) & (j.cap - 1)) * (uint64_t)n1 + 1u + v] = *bin;
+        if (s >= skip) j.ring[((j.t0 + s0 + s) & (j.cap - 1)) * (uint64_t)n1 + 1u + v] = *bin;
         if (mirror && s0 + s + 1 == j.nsweeps) mirror[1u + v] = *bin;
         *bin = 0;
       }
