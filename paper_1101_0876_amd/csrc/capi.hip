@@ -17,6 +17,12 @@
 #include "kernels.hpp"
 #include "tiles.hpp"
 
+// Where the lattice is between calls: wherever the last one left it, or, since a
+// call was captured, where that call swept it.  Replays are not seen by the
+// host, so from then on every call, captured or not, starts from there and ends
+// there, and reading the lattice starts from there too.
+enum potts_home { kAnywhere, kRows, kPlanes };
+
 struct potts_state {
   int32_t L = 0, q = 0;
   uint64_t seed = 0;
@@ -49,8 +55,9 @@ struct potts_state {
   uint8_t *rag_planes = nullptr;
   bool no_rag = false;
   // a sweep call of the state was captured into a graph: its replays find the
-  // lattice and the totals where they were then
+  // lattice (home) and the totals where they were then
   bool captured = false;
+  potts_home home = kAnywhere;
   // heat-bath draw table of the colour-split kernel (device copy, and the host
   // copy it was uploaded from, valid for hb_thr and q)
   potts::HbTable *hb_dev = nullptr;
@@ -133,7 +140,29 @@ uint8_t *planes_of(const potts_state *s) { return s->L % 32 ? s->rag_planes : s-
 int sync_spins(potts_state *s) {
   if (s->spins_valid) return POTTS_OK;
   HIP_TRY(potts::launch_unpack(planes_of(s), s->spins, (uint32_t)s->L, s->stream));
-  s->spins_valid = true;
+  // (at home on the planes, the next replay makes it stale)
+  s->spins_valid = s->home != kPlanes;
+  return POTTS_OK;
+}
+
+// Queued after the sweeps of a call: the lattice is where the next call and a
+// replay look for it.  Caller-owned buffers: the row-major lattice is current
+// after every call, and the next call packs it again, so writes between calls
+// are seen.  L % 32 != 0: it is current too, since a captured call works on it
+// in place.
+int settle(potts_state *s) {
+  if (s->home == kPlanes) {
+    if (!s->planes_valid) HIP_TRY(potts::launch_pack(s->spins, planes_of(s), (uint32_t)s->L, s->stream));
+    s->planes_valid = true;
+    s->spins_valid = false;
+    return POTTS_OK;
+  }
+  if (s->owns_spins && s->home != kRows && s->L % 32 == 0) return POTTS_OK;
+  if (!s->spins_valid) {
+    HIP_TRY(potts::launch_unpack(planes_of(s), s->spins, (uint32_t)s->L, s->stream));
+    s->spins_valid = true;
+  }
+  s->planes_valid = s->planes_valid && s->owns_spins && s->home != kRows;
   return POTTS_OK;
 }
 
@@ -336,10 +365,9 @@ bool rag_ready(potts_state *s) {
 }
 
 bool use_packed(const potts_state *s, int64_t nsweeps) {
-  // (a captured call leaves the lattice where it is)
   return packed_ok(s) &&
          (s->kernel == 4 ||
-          (s->kernel == 0 && !drawn_ok(s) && (!auto_tiles(s, nsweeps) || (!s->spins_valid && capturing(s)))));
+          (s->kernel == 0 && (s->home == kPlanes || (!drawn_ok(s) && !auto_tiles(s, nsweeps)))));
 }
 
 bool use_strip(const potts_state *s) { return strip_ok(s) && (s->kernel == 1 || s->kernel == 0); }
@@ -406,17 +434,19 @@ bool capturing(const potts_state *s) {
   return st == hipStreamCaptureStatusActive;
 }
 
-// A call that is being captured: its replays work on the lattice in place, and
-// so do the calls after it on lattices that would leave it for other planes.
-void note_capture(potts_state *s) {
+// A call that is being captured fixes the lattice's home: the planes if only
+// they hold it, or if they do and the call sweeps on them (on_planes), else the
+// rows.  L % 32 != 0, whose planes are never the only copy, is swept in place.
+void note_capture(potts_state *s, bool on_planes) {
   if (!capturing(s)) return;
   s->captured = true;
   s->no_rag = true;
+  if (s->home == kAnywhere) s->home = !s->spins_valid || (s->planes_valid && on_planes) ? kPlanes : kRows;
 }
 
 bool use_tiles(const potts_state *s, int64_t nsweeps) {
   if (s->kernel == 5) return tiles_ok(s);
-  if (s->kernel != 0 || !auto_tiles(s, nsweeps)) return false;
+  if (s->kernel != 0 || s->home == kPlanes || !auto_tiles(s, nsweeps)) return false;
   return !capturing(s) || (s->L > 256 && s->L < 2048 && s->L % 16 == 0 && s->spins_valid);
 }
 
@@ -704,19 +734,6 @@ int capture_graph(potts_state *s, const potts::StripParams &p, int32_t K, bool w
   return POTTS_OK;
 }
 
-// After sweeps on the colour-split copy.  Caller-owned buffers: the row-major
-// lattice is current after every call, and the next call packs it again, so
-// writes between calls are seen.  L % 32 != 0: it is current too, since a
-// captured call works on it in place.
-int end_planes(potts_state *s) {
-  if (!s->owns_spins || s->L % 32) {
-    HIP_TRY(potts::launch_unpack(planes_of(s), s->spins, (uint32_t)s->L, s->stream));
-    s->spins_valid = true;
-    s->planes_valid = s->owns_spins;
-  }
-  return POTTS_OK;
-}
-
 // Sweeps on the colour-split copy in the second buffer (packed.hip): pack,
 // sweep, unpack; records as the strip path (striped partial records).
 int run_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
@@ -767,7 +784,7 @@ int run_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     HIP_TRY(potts::launch_fold_stripes(p, p.t0 + (uint64_t)count - 1, s->stream));
   }
   s->t += nsweeps;
-  return end_planes(s);
+  return POTTS_OK;
 }
 
 // Sweeps on LDS tiles, several per launch (tiles.hip), ping-ponging the
@@ -943,27 +960,12 @@ int run_band(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     done += K;
   }
   s->t += nsweeps;
-  if (!s->owns_spins) {
-    HIP_TRY(potts::launch_unpack(s->spins2, s->spins, L, s->stream));
-    s->spins_valid = true;
-    s->planes_valid = false;
-  }
   return POTTS_OK;
 }
 
-int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
-  if (!s) return fail(POTTS_EINVAL, "state is NULL");
-  if (nsweeps < 0) return fail(POTTS_EINVAL, "nsweeps must be >= 0");
-  if (nsweeps > INT64_MAX - s->t) return fail(POTTS_ERANGE, "sweep counter overflow");
-  {
-    const int rc = band_check(s);
-    if (rc) return rc;
-  }
-  if (nsweeps == 0) return POTTS_OK;
-  note_capture(s);
-  s->mirror_t = -1;
-  const bool band = use_band(s, nsweeps);
-  if (band) return run_band(s, thr, nsweeps);
+// The sweeps of a call, by the kernel that takes them.
+int dispatch_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
+  if (use_band(s, nsweeps)) return run_band(s, thr, nsweeps);
   const bool rag = use_rag(s, nsweeps) && rag_ready(s);
   if (!rag && (use_resident(s) || !use_packed(s, nsweeps))) {
     // every other kernel sweeps the row-major lattice (the LDS-resident one
@@ -971,6 +973,7 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     // sweeps)
     const int rc = sync_spins(s);
     if (rc) return rc;
+    s->spins_valid = true;
     s->planes_valid = false;
   }
   if (use_drawn(s, nsweeps)) return run_drawn(s, thr, nsweeps);
@@ -1030,6 +1033,21 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   return POTTS_OK;
 }
 
+int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
+  if (!s) return fail(POTTS_EINVAL, "state is NULL");
+  if (nsweeps < 0) return fail(POTTS_EINVAL, "nsweeps must be >= 0");
+  if (nsweeps > INT64_MAX - s->t) return fail(POTTS_ERANGE, "sweep counter overflow");
+  {
+    const int rc = band_check(s);
+    if (rc) return rc;
+  }
+  if (nsweeps == 0) return POTTS_OK;
+  note_capture(s, use_band(s, nsweeps) || use_packed(s, nsweeps));
+  s->mirror_t = -1;
+  const int rc = dispatch_sweeps(s, thr, nsweeps);
+  return rc ? rc : settle(s);
+}
+
 // The heat bath's draw table for thr in device memory, rebuilt and uploaded when
 // the thresholds change.
 int heatbath_table(potts_state *s, const uint32_t thr[4]) {
@@ -1056,7 +1074,6 @@ int heatbath_table(potts_state *s, const uint32_t thr[4]) {
 // Metropolis colour-split path.
 int run_heatbath_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   const uint32_t L = (uint32_t)s->L;
-  const bool fresh = !s->planes_valid && capturing(s);
   if (!s->planes_valid) {
     HIP_TRY(potts::launch_pack(s->spins, planes_of(s), L, s->stream));
     s->planes_valid = true;
@@ -1088,12 +1105,6 @@ int run_heatbath_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) 
     HIP_TRY(potts::launch_fold_stripes(p, p.t0 + (uint64_t)count - 1, s->stream));
   }
   s->t += nsweeps;
-  const int rc = end_planes(s);
-  if (rc || !fresh) return rc;
-  // a captured call that packed: every replay packs what the one before left
-  HIP_TRY(potts::launch_unpack(planes_of(s), s->spins, L, s->stream));
-  s->spins_valid = true;
-  s->planes_valid = false;
   return POTTS_OK;
 }
 
@@ -1107,7 +1118,7 @@ int run_heatbath_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) 
 // allocate.
 bool heatbath_tiles(const potts_state *s, int64_t nsweeps) {
   if (capturing(s)) return false;
-  return s->kernel == 5 ? tiles_ok(s) : s->kernel == 0 && (s->L <= 3584 || (s->L <= 4096 && nsweeps > 3));
+  return s->kernel == 5 ? tiles_ok(s) : s->kernel == 0 && s->home != kPlanes && (s->L <= 3584 || (s->L <= 4096 && nsweeps > 3));
 }
 
 // The colour-split kernel with partial items elsewhere (L = 5000 59.5, one
@@ -1116,19 +1127,17 @@ bool heatbath_rag(const potts_state *s) {
   return s->L % 32 != 0 && s->kernel == 0 && s->L <= 65520 && !s->no_rag && !capturing(s);
 }
 
+bool heatbath_packed(const potts_state *s) {
+  return packed_ok(s) && (s->kernel == 0 || s->kernel == 4 || s->kernel == 7);
+}
+
 // Heat-bath sweeps: on tiles, else on a colour-split copy (kernel 0, or L % 32
 // == 0 and kernel 4 or 7), else one thread per 4-byte chunk (kernels.hip); the
 // sweep counter and records are shared with the Metropolis sweeps.
-int run_heatbath(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
-  if (!s) return fail(POTTS_EINVAL, "state is NULL");
-  if (nsweeps < 0) return fail(POTTS_EINVAL, "nsweeps must be >= 0");
-  if (nsweeps > INT64_MAX - s->t) return fail(POTTS_ERANGE, "sweep counter overflow");
-  if (nsweeps == 0) return POTTS_OK;
-  note_capture(s);
-  s->mirror_t = -1;
+int dispatch_heatbath(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   const int64_t rl = s->q + 1;
   const bool tiles = heatbath_tiles(s, nsweeps);
-  if (!tiles && ((packed_ok(s) && (s->kernel == 0 || s->kernel == 4 || s->kernel == 7)) || (heatbath_rag(s) && rag_ready(s)))) {
+  if (!tiles && (heatbath_packed(s) || (heatbath_rag(s) && rag_ready(s)))) {
     const int rc = heatbath_table(s, thr);
     if (rc) return rc;
     HIP_TRY(potts::launch_fill_u64(s->records + (s->t % s->rec_cap) * rl, (uint64_t)rl, 0ull, s->stream));
@@ -1137,6 +1146,7 @@ int run_heatbath(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   {
     const int rc = sync_spins(s);
     if (rc) return rc;
+    s->spins_valid = true;
     s->planes_valid = false;
   }
   if (tiles) {
@@ -1165,6 +1175,17 @@ int run_heatbath(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   }
   s->t += nsweeps;
   return POTTS_OK;
+}
+
+int run_heatbath(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
+  if (!s) return fail(POTTS_EINVAL, "state is NULL");
+  if (nsweeps < 0) return fail(POTTS_EINVAL, "nsweeps must be >= 0");
+  if (nsweeps > INT64_MAX - s->t) return fail(POTTS_ERANGE, "sweep counter overflow");
+  if (nsweeps == 0) return POTTS_OK;
+  note_capture(s, !heatbath_tiles(s, nsweeps) && heatbath_packed(s));
+  s->mirror_t = -1;
+  const int rc = dispatch_heatbath(s, thr, nsweeps);
+  return rc ? rc : settle(s);
 }
 
 // Validates [t0, t0+n) against the ring; returns the first slot.
@@ -1593,6 +1614,10 @@ int potts_set_spins(potts_state *s, const uint8_t *host_in, int64_t t) {
   HIP_TRY(hipStreamSynchronize(s->stream));
   s->spins_valid = true;
   s->planes_valid = false;
+  {
+    const int rc = settle(s);
+    if (rc) return rc;
+  }
   s->t = t;
   s->rec_from = t;
   s->mirror_t = -1;
@@ -1602,6 +1627,7 @@ int potts_set_spins(potts_state *s, const uint8_t *host_in, int64_t t) {
 void *potts_device_spins(potts_state *s) {
   if (!s || sync_spins(s)) return nullptr;
   // the caller may write through the pointer: the next sweep packs again
+  s->spins_valid = true;
   s->planes_valid = false;
   return (void *)s->spins;
 }
