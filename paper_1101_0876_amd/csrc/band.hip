@@ -16,18 +16,20 @@
 // Publication: the waves holding the edge rows run at raised priority and begin
 // with these; each lane stores its dwords of the edge into the exchange buffer
 // beside the number of the half sweep, in 8-byte words: a reader that finds the
-// number has the value, so no flag has to wait for the stores, and no reader for
-// a flag.  When these waves are done with their items they read the neighbours'
-// edges into the band's halo rows, again until every number is there, while the
-// other waves are still updating. A workgroup barrier ends the half sweep.  Numbers count half sweeps from an epoch the host advances by
-// 2 x sweeps per launch, so the buffer is never cleared.  A word is written
-// again two half sweeps later: by then both neighbours have published the half
-// sweep between, which they began after they had read it.  Every wait is bounded
-// in time: on expiry the workgroup stops and raises a host-visible error
-// word, and the neighbours waiting on it stop the same way, so the grid
-// always drains.  All workgroups must be resident at once (a neighbour wait
-// on a workgroup that has not started would never end): the launch is
-// cooperative, which the runtime refuses when the grid cannot be resident.
+// number has the value, so no flag has to wait for the stores, and no reader
+// for a flag. When these waves are done with their items they read the
+// neighbours' edges into the band's halo rows, again until every number is
+// there, while the other waves are still updating. A workgroup barrier ends the
+// half sweep. Numbers count half sweeps from an epoch the host advances by 2 x
+// sweeps per launch, so the buffer is cleared for captured launches only. A
+// word is written again two half sweeps later: by then both neighbours have
+// published the half sweep between, which they began after they had read it.
+// Every wait is bounded in time: on expiry the workgroup stops and raises a
+// host-visible error word, and the neighbours waiting on it stop the same way,
+// so the grid always drains. All workgroups must be resident at once (a
+// neighbour wait on a workgroup that has not started would never end): the
+// launch is cooperative, which the runtime refuses when the grid cannot be
+// resident.
 //
 // Ordering without L2 fences: the exchanged words are written and read only
 // with agent-scope atomic accesses, which gfx950 performs coherently across its

@@ -947,6 +947,10 @@ int run_band(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   p.k1 = (uint32_t)(s->seed >> 32);
   for (int i = 0; i < 4; ++i) p.thr.v[i] = thr[i];
   p.wait_ticks = s->bclock_khz * wait_us / 1000u;
+  // A replay numbers its half sweeps as the one before did, which left its last
+  // numbers behind: those of a single sweep are the ones that it waits for.
+  if (capturing(s))
+    HIP_TRY(potts::launch_fill_u64(reinterpret_cast<unsigned long long *>(s->bxbuf), s->bxwords, 0ull, s->stream));
   // one launch's records fold into distinct ring slots
   const int64_t kmax = std::min<int64_t>(potts::kBandMaxSweeps, s->rec_cap);
   for (int64_t done = 0; done < nsweeps;) {

@@ -40,6 +40,7 @@ CASES = [
     (2048, False, 48, 2, (1, 48)),  # bands before and between
     (2048, False, 2, 2, (48, 2)),
     (4096, False, 2, 2, (1, 2)),   # bands, captured too
+    (4096, False, 1, 1, (1,)),
     (3616, True, 4, 1, (4,)),
     (3616, True, 1, 4, (1,)),
     (1024, True, 1, 1, (2, 1)),
