@@ -519,16 +519,8 @@ static float tile_launch_us(const TileParams &p, uint32_t tx, uint32_t ty, uint3
          (turns > 1.0f ? 0.95f * turns : 1.0f);
 }
 
-bool auto_tile_shape(TileParams &p, int64_t nsweeps) {
-  // sides of 16 .. 256 that cut L into 1 .. 32 equal parts (rounded up to 8)
-  uint32_t sides[40], nsides = 0;
-  for (uint32_t k = 1; k <= 32; ++k) {
-    uint32_t t = ((p.L + k - 1) / k + 7u) & ~7u;
-    t = t < 16u ? 16u : t;
-    if (t <= 256u && (nsides == 0 || sides[nsides - 1] != t)) sides[nsides++] = t;
-  }
-  if (nsides == 0)
-    for (uint32_t t = 256; t >= 128; t -= 32) sides[nsides++] = t;
+// The shape out of tiles with these sides; false: none of them fits.
+static bool best_tile_shape(TileParams &p, int64_t nsweeps, const uint32_t *sides, uint32_t nsides) {
   const int64_t n = nsweeps > 64 ? 64 : nsweeps < 1 ? 1 : nsweeps;  // long calls: per sweep
   float best = 0;
   uint32_t btx = 0, bty = 0, bs = 0;
@@ -547,7 +539,22 @@ bool auto_tile_shape(TileParams &p, int64_t nsweeps) {
         }
       }
   }
-  return set_tile_shape(p, btx, bty, bs);
+  return bs != 0 && set_tile_shape(p, btx, bty, bs);
+}
+
+bool auto_tile_shape(TileParams &p, int64_t nsweeps) {
+  // sides of 16 .. 256 that cut L into 1 .. 32 equal parts (rounded up to 8)
+  uint32_t sides[40], nsides = 0;
+  for (uint32_t k = 1; k <= 32; ++k) {
+    uint32_t t = ((p.L + k - 1) / k + 7u) & ~7u;
+    t = t < 16u ? 16u : t;
+    if (t <= 256u && (nsides == 0 || sides[nsides - 1] != t)) sides[nsides++] = t;
+  }
+  if (nsides && best_tile_shape(p, nsweeps, sides, nsides)) return true;
+  // from L = 6672 the parts are too large for a workgroup (above 8192 there are
+  // none): tiles of these sides, the last ones cut
+  static const uint32_t fixed[] = {256, 224, 192, 160, 128};
+  return best_tile_shape(p, nsweeps, fixed, 5);
 }
 
 // ---- many lattices per launch -------------------------------------------------
