@@ -367,10 +367,12 @@ bool grow(void **p, size_t *cap, size_t n, size_t size) {
 // 3.9), 24 jobs 2.2 (4.2), 96 jobs 3.7 (5.2).  With more sites the
 // GPU is full either way, and one workgroup per lattice recomputes no halos.
 // Empty: the other launches take them (also without memory for the tiles).
+// run_jobs: the jobs of each run.
 constexpr uint64_t kTileSites = 1ull << 23;
 
 std::vector<potts::TileRun> tile_runs(potts_batch *b, bool all, std::vector<std::vector<int>> &run_jobs) {
   std::vector<potts::TileRun> runs;
+  run_jobs.clear();
   std::map<std::pair<int, bool>, std::vector<int>> groups;
   for (const ResidentGroup &g : b->res_groups) groups[{g.qc, g.wide}] = g.jobs;
   if (all)
