@@ -118,6 +118,7 @@ struct potts_batch {
   potts::TileParams *d_tjobs = nullptr;
   potts::TileRef *d_trefs = nullptr;
   size_t other_cap = 0, tparts_cap = 0, tjobs_cap = 0, trefs_cap = 0;
+  bool tiled = false;  // the strip jobs' last run was on tiles, which leave the next sweep's slot as it was
   potts::StatsParams *d_stats = nullptr;
   double *d_stats_out = nullptr;
   hipGraph_t graph = nullptr;
@@ -468,6 +469,15 @@ int queue_rest(potts_batch *b, std::vector<potts::TileRun> runs, std::vector<std
   if (rc) return rc;
   rc = upload(b->d_tiles + b->tiles_cap, all_rev.data(), all_rev.size() * sizeof(all_rev[0]), b->stream);
   if (rc) return rc;
+  // strip launches add to a slot that the sweep before has cleared
+  for (const StripGroup &g : b->strip_groups)
+    for (int j : g.jobs) {
+      const uint64_t n = (uint64_t)b->jobs[j].q + 1;
+      if (!all && b->tiled)
+        HIP_TRY(potts::launch_fill_u64(b->rec_arena + b->rec_off[j] + (uint64_t)(b->done[j] & (b->ring[j] - 1)) * n, n, 0ull,
+                                       b->stream));
+    }
+  b->tiled = all;
 
   // the resident jobs: tiles, queued beside the graph (a long run has many
   // turns), or resident launches within it

@@ -91,6 +91,7 @@ struct Job {
   int64_t left = 0;     // sweeps left in the current point
   uint32_t rows = 0;    // strip height (0: resident)
   bool resident = false;
+  bool tiled = false;   // its last sweeps ran on tiles, which leave the next sweep's slot as it was
   // results
   std::vector<potts_summary> points;
   std::vector<uint8_t> spins;
@@ -535,7 +536,10 @@ int iterate(potts_server *s, std::string &err) {
     run_jobs.clear();
   }
   std::set<const Job *> tiled;
-  for (const auto &jobs : run_jobs) tiled.insert(jobs.begin(), jobs.end());
+  for (const auto &jobs : run_jobs) {
+    tiled.insert(jobs.begin(), jobs.end());
+    for (Job *j : jobs) j->tiled = true;
+  }
   for (size_t k = 0; k < s->active.size(); ++k) {
     Job &j = *s->active[k];
     if (tiled.count(&j)) continue;
@@ -678,7 +682,15 @@ int iterate(potts_server *s, std::string &err) {
     p.jobs = s->d_res + res_off[gi];
     e = potts::launch_resident(p, (unsigned)res_groups[gi].jobs.size(), max_L, max_q, res_groups[gi].wide, s->stream);
   }
-  // strip groups: one launch per colour and sweep covering every job
+  // strip groups: one launch per colour and sweep covering every job; they add to
+  // a slot that the sweep before has cleared
+  for (SG &g : strip_groups)
+    for (Job *j : g.jobs) {
+      const uint64_t n = (uint64_t)j->req.q + 1;
+      if (j->tiled && e == hipSuccess)
+        e = potts::launch_fill_u64(j->ring + ((uint64_t)j->t & (uint64_t)(j->cap - 1)) * n, n, 0ull, s->stream);
+      j->tiled = false;
+    }
   for (int64_t sw = 0; sw < strip_sweeps && e == hipSuccess; ++sw) {
     for (size_t gi = 0; gi < strip_groups.size() && e == hipSuccess; ++gi) {
       potts::StripLaunch l{};
