@@ -361,12 +361,9 @@ bool grow(void **p, size_t *cap, size_t n, size_t size) {
   return true;
 }
 
-// Jobs' remaining sweeps as multi-sweep tile launches: the resident jobs',
-// while their lattices hold at most kTileSites sites together, or all (`all`): one workgroup sweeps
-// an L = 256 lattice in 27 us and leaves the other CUs idle.  Measured on MI355X
-// (100 sweeps of L = 64 .. 256, the whole run): 4 jobs 1.7 ms (resident launches
-// 3.9), 24 jobs 2.2 (4.2), 96 jobs 3.7 (5.2).  With more sites the
-// GPU is full either way, and one workgroup per lattice recomputes no halos.
+// Jobs' remaining sweeps as multi-sweep tile launches: the resident jobs', or all
+// (`all`), of lattices that hold at most kTileSites sites together (each has a
+// second one).
 // Empty: the other launches take them (also without memory for the tiles).
 // run_jobs: the jobs of each run.
 constexpr uint64_t kTileSites = 1ull << 23;
@@ -388,7 +385,7 @@ std::vector<potts::TileRun> tile_runs(potts_batch *b, bool all, std::vector<std:
       sites += (uint64_t)b->jobs[j].L * b->jobs[j].L;
       ++njobs;
     }
-  if (sites == 0 || (!all && sites > kTileSites) || !grow((void **)&b->other, &b->other_cap, (size_t)sites, 1)) return {};
+  if (sites == 0 || sites > kTileSites || !grow((void **)&b->other, &b->other_cap, (size_t)sites, 1)) return {};
   size_t at = 0;
   for (const auto &g : groups) {
     potts::TileRun r;
@@ -427,22 +424,68 @@ std::vector<potts::TileRun> tile_runs(potts_batch *b, bool all, std::vector<std:
   return runs;
 }
 
-// Whether tile launches take every job of the batch: lattices of L <= 2048 with
-// at most kTileSites sites together, where the caller asked for no tuning of the
-// strip launches, which take 20 us a sweep however few the sites.  Measured on
-// MI355X (60 sweeps, ms a run, strip launches for L > 256 in brackets): 24 jobs of
-// L = 128 .. 1024 (5.5 M sites) 0.96 (1.5), 24 of L = 64 .. 2048 (13.4 M) 1.89
-// (2.27), 48 of L = 512 (12.6 M) 2.06 (1.88).
-bool tiles_take_all(const potts_batch *b) {
-  if (b->opts.tune || b->opts.strip_rows || b->opts.tune_cache) return false;
+// Which jobs tile launches take, by the estimates of tiles.hpp: none, those of
+// the LDS-resident launches (one workgroup sweeps an L = 256 lattice in 26 us and
+// leaves the other CUs idle), or all, where the caller asked for no tuning of the
+// strip launches.  The tiles of the first run beside the strip launches, as the
+// resident launches do.  Measured on MI355X (q = 9, ms a run; none / resident
+// jobs / all): 24 jobs of L = 64 .. 256, 60 sweeps 1.56 / 0.36 / 0.35, 24 of L = 128
+// .. 1024 2.04 / 1.56 / 1.20, 48 of them (13 M sites) 2.52 / 1.99 / 1.92, 96 of L =
+// 128 .. 2048 (114 M) 7.93 / 7.63 / 13.1; 512 of L = 64, 100 sweeps 0.38 / 1.30, 64
+// of L = 512 3.26 / - / 4.33.
+enum class Tiles { kNone, kResident, kAll };
+
+Tiles tiles_for(const potts_batch *b) {
+  std::map<std::pair<int, bool>, std::vector<potts::SweepJob>> all;
+  float resident = 0, tiles = 0, strips = 0;
   uint64_t sites = 0;
-  for (const potts_job &j : b->jobs) sites += j.L <= 2048 ? (uint64_t)j.L * j.L : 1ull << 32;
-  return sites <= kTileSites;
+  size_t njobs = 0;
+  bool fits = !b->opts.tune && !b->opts.strip_rows && !b->opts.tune_cache;  // all jobs on tiles
+  auto list = [&](const std::vector<int> &jobs) {
+    std::vector<potts::SweepJob> l;
+    for (int j : jobs)
+      if (b->target[j] > b->done[j])
+        l.push_back(potts::SweepJob{(uint32_t)b->jobs[j].L, (uint32_t)b->jobs[j].q, (uint64_t)(b->target[j] - b->done[j]),
+                                    (uint64_t)b->ring[j]});
+    return l;
+  };
+  if (b->jobs.size() >= potts::kTileJobs) fits = false;
+  for (const ResidentGroup &g : b->res_groups) njobs += g.jobs.size();
+  const bool few = njobs > 0 && njobs < potts::kTileJobs;
+  if (!few && !fits) return Tiles::kNone;
+  for (const ResidentGroup &g : b->res_groups) {
+    const std::vector<potts::SweepJob> l = list(g.jobs);
+    if (l.empty()) continue;
+    resident += potts::resident_us(l);
+    tiles += potts::tile_run_us(l);
+    all[{g.qc, g.wide}] = l;
+  }
+  for (const StripGroup &g : b->strip_groups) {
+    const std::vector<potts::SweepJob> l = list(g.jobs);
+    if (l.empty()) continue;
+    strips += potts::strip_us(l);
+    for (const potts::SweepJob &p : l) {
+      if (p.L % 32 == 0) strips += 6.5f;  // packed before and unpacked after
+      fits = fits && p.L <= 2048;
+    }
+    std::vector<potts::SweepJob> &to = all[{g.qc, g.wide}];
+    to.insert(to.end(), l.begin(), l.end());
+  }
+  float whole = 0;
+  for (const auto &g : all) {
+    for (const potts::SweepJob &p : g.second) sites += (uint64_t)p.L * p.L;
+    if (fits) whole += potts::tile_run_us(g.second);
+  }
+  const bool some = few && tiles > 0 && tiles < potts::kTileMargin * resident;
+  const float branch = some ? tiles : resident, split = branch > strips ? branch : strips;
+  if (fits && strips > 0 && sites <= kTileSites && whole > 0 && whole < potts::kTileMargin * split) return Tiles::kAll;
+  return some ? Tiles::kResident : Tiles::kNone;
 }
 
 // Queues the rest of the run (every job to its nsweeps) on the stream, as a
-// graph when asked; runs: all of it, when they are not empty.
-int queue_rest(potts_batch *b, std::vector<potts::TileRun> runs, std::vector<std::vector<int>> run_jobs) {
+// graph when asked; runs: all of it, when they are not empty; tiles: those of the
+// resident jobs are wanted.
+int queue_rest(potts_batch *b, bool tiles_wanted, std::vector<potts::TileRun> runs, std::vector<std::vector<int>> run_jobs) {
   const bool all = !runs.empty();
   // strip tables for the remaining sweeps
   std::vector<potts::StripParams> all_desc;
@@ -481,7 +524,7 @@ int queue_rest(potts_batch *b, std::vector<potts::TileRun> runs, std::vector<std
 
   // the resident jobs: tiles, queued beside the graph (a long run has many
   // turns), or resident launches within it
-  if (!all) runs = tile_runs(b, false, run_jobs);
+  if (!all && tiles_wanted) runs = tile_runs(b, false, run_jobs);
   {
     std::vector<potts::TileParams> tjobs;
     std::vector<potts::TileRef> trefs;
@@ -779,11 +822,12 @@ int potts_batch_run(potts_batch *b) {
   HIP_TRY(hipEventRecord(mark, b->stream));
   std::vector<potts::TileRun> runs;
   std::vector<std::vector<int>> run_jobs;
-  if (tiles_take_all(b)) runs = tile_runs(b, true, run_jobs);
+  const Tiles tiles = tiles_for(b);
+  if (tiles == Tiles::kAll) runs = tile_runs(b, true, run_jobs);
   const bool all = !runs.empty();
   int rc = all ? POTTS_OK : convert_packed(b, true);
   if (!rc && !all) rc = autotune(b, b->opts.tune != 0);
-  if (!rc) rc = queue_rest(b, std::move(runs), std::move(run_jobs));
+  if (!rc) rc = queue_rest(b, tiles != Tiles::kNone, std::move(runs), std::move(run_jobs));
   if (!rc && !all) rc = convert_packed(b, false);
   if (!rc) {
     hipError_t e = hipEventRecord(b->ev_t1, b->stream);

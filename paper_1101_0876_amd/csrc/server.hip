@@ -8,7 +8,7 @@
 // every admitted lattice and its sweep counter resident on the device, and
 // runs iterations: each iteration advances every active job by up to
 // `quantum` sweeps of its current point in shared launches (multi-sweep tile
-// launches for L <= 1024 while those jobs are few; else LDS-resident launches
+// launches for L <= 1024 where they are faster; else LDS-resident launches
 // for L <= 256 and one tiled strip launch per colour and sweep for the rest),
 // so requests that arrive while others run join the next iteration.
 // When a point's sweeps are done its summary (derived statistics over the last
@@ -452,16 +452,57 @@ bool admit(potts_server *s, Job &j, std::string &err) {
 }
 
 // Jobs of L <= 1024 run in multi-sweep tile launches while their lattices hold
-// at most kTileSites sites together, and L <= 2048 too where that leaves no job
-// for the strip launches.  Measured on MI355X (ramps of 4 points x 100 sweeps,
-// submission to last result): 4 jobs of L = 128 .. 1024 2.3 ms, 24 of them 8.9
-// ms, 24 of L = 64 .. 256 3.6 ms; with LDS-resident and strip launches 10.3,
-// 22.1 and 12.2 ms (one workgroup sweeps an L = 256 lattice in 25 us, and a
-// strip launch costs 8 us however small its jobs).  96 jobs of L = 128 .. 1024
-// (34 M sites) take 37 ms either way: with more sites the recomputed halos cost
-// what the launches save.
+// at most kTileSites sites together, L <= 2048 too where that leaves no job for
+// the strip launches, and where the estimates of tiles.hpp say that it is faster.
+// Measured on MI355X (ramps of 3 points x 160 sweeps, submission to last result,
+// ms; LDS-resident and strip launches in brackets): q = 6 1 job of L = 256 1.4
+// (12.5), of L = 1024 2.3 (8.4), 16 of L = 512 8.0 (10.0), 96 of L = 256 16.6
+// (18.4), 2 of L = 2048 10.5 (21.7); q = 200 1.8 (13.7), 2.8 (9.2), 10.1 (11.2),
+// 25 (19.9), 12.2 (22.9); 96 of L = 64 at q = 200 12.0 (7.7): these and the 96 of
+// L = 256 at q = 200 stay with the other launches.
 constexpr int32_t kTileL = 1024, kTileOnlyL = 2048;
 constexpr uint64_t kTileSites = 1ull << 24;
+
+// The largest L that tile launches take in an iteration of step[k] sweeps of
+// active job k, 0: none, and the sites of those jobs.
+int32_t tile_size(const potts_server *s, const std::vector<int64_t> &step, size_t *sites) {
+  uint64_t tile_sites = 0, all_sites = 0;
+  for (const auto &jp : s->active) {
+    const uint64_t n = (uint64_t)jp->req.L * jp->req.L;
+    all_sites += jp->req.L <= kTileOnlyL ? n : kTileSites + 1;
+    if (jp->req.L <= kTileL) tile_sites += n;
+  }
+  const int32_t tile_L = all_sites <= kTileSites ? kTileOnlyL : kTileL;
+  if (tile_L == kTileOnlyL) tile_sites = all_sites;
+  if (tile_sites == 0 || tile_sites > kTileSites) return 0;
+  *sites = (size_t)tile_sites;
+  // launches of one kind follow each other, one per class of q and table form
+  using Groups = std::map<std::pair<int, bool>, std::vector<potts::SweepJob>>;
+  Groups tiles, rest, resident, strips;
+  size_t ntiles = 0;
+  for (size_t k = 0; k < s->active.size(); ++k) {
+    const Job &j = *s->active[k];
+    if (step[k] <= 0) continue;
+    const uint32_t *thr = &j.thr[(size_t)j.point * 4];
+    const std::pair<int, bool> key{q_class((uint32_t)j.req.q), !thr[0] || !thr[1] || !thr[2] || !thr[3]};
+    const potts::SweepJob p{(uint32_t)j.req.L, (uint32_t)j.req.q, (uint64_t)step[k], (uint64_t)j.cap};
+    (j.resident ? resident : strips)[key].push_back(p);
+    if (j.req.L > tile_L)
+      rest[key].push_back(p);
+    else if (++ntiles < potts::kTileJobs)
+      tiles[key].push_back(p);
+    else
+      return 0;
+  }
+  auto total = [](const Groups &g, float (*us)(const std::vector<potts::SweepJob> &)) {
+    float t = 0;
+    for (const auto &l : g) t += us(l.second);
+    return t;
+  };
+  const float with = total(tiles, potts::tile_run_us) + total(rest, potts::strip_us);
+  const float without = total(resident, potts::resident_us) + total(strips, potts::strip_us);
+  return with < potts::kTileMargin * without ? tile_L : 0;
+}
 
 // One iteration over the active jobs: returns 0 or a negative code (message in err).
 int iterate(potts_server *s, std::string &err) {
@@ -483,22 +524,15 @@ int iterate(potts_server *s, std::string &err) {
     return gs.back();
   };
   std::vector<int64_t> step(s->active.size());
-  uint64_t tile_sites = 0, all_sites = 0;
-  for (const auto &jp : s->active) {
-    const uint64_t n = (uint64_t)jp->req.L * jp->req.L;
-    all_sites += jp->req.L <= kTileOnlyL ? n : kTileSites + 1;
-    if (jp->req.L <= kTileL) tile_sites += n;
-  }
-  const int32_t tile_L = all_sites <= kTileSites ? kTileOnlyL : kTileL;
-  if (tile_L == kTileOnlyL) tile_sites = all_sites;
+  for (size_t k = 0; k < s->active.size(); ++k) step[k] = std::min<int64_t>(quantum, s->active[k]->left);
+  size_t tile_sites = 0;
+  const int32_t tile_L = tile_size(s, step, &tile_sites);
   std::vector<potts::TileRun> runs;
   std::vector<std::vector<Job *>> run_jobs;
   size_t other_bytes = 0;
-  const bool tiles_ok = tile_sites > 0 && tile_sites <= kTileSites &&
-                        reserve_dev((void **)&s->d_other, &s->cap_other, (size_t)tile_sites, 1);
+  const bool tiles_ok = tile_L > 0 && reserve_dev((void **)&s->d_other, &s->cap_other, tile_sites, 1);
   for (size_t k = 0; k < s->active.size(); ++k) {
     Job &j = *s->active[k];
-    step[k] = std::min<int64_t>(quantum, j.left);
     if (tiles_ok && j.req.L <= tile_L && step[k] > 0) {
       const uint32_t *thr = &j.thr[(size_t)j.point * 4];
       const bool wide = !thr[0] || !thr[1] || !thr[2] || !thr[3];

@@ -594,11 +594,16 @@ static float tile_turn_us(uint32_t side, uint32_t sweeps, uint64_t tiles) {
   return 3.5f + 0.4f * n + 2.0f * (float)sweeps * (turns > 1.0f && shared > half ? shared : half);
 }
 
-bool plan_tile_run(TileRun &r) {
+// The run's shape: sides of its tiles and sweeps a turn; side 0: none.
+struct RunShape {
+  uint32_t side, sweeps;
+};
+
+static RunShape run_shape(const std::vector<SweepJob> &jobs) {
   uint64_t most = 0;
   std::vector<std::pair<uint32_t, uint64_t>> sizes;  // L, jobs of it
-  for (const TileParams &p : r.jobs) {
-    most = p.total > most ? p.total : most;
+  for (const SweepJob &p : jobs) {
+    most = p.sweeps > most ? p.sweeps : most;
     size_t i = 0;
     while (i < sizes.size() && sizes[i].first != p.L) ++i;
     if (i == sizes.size()) sizes.push_back({p.L, 0});
@@ -606,7 +611,7 @@ bool plan_tile_run(TileRun &r) {
   }
   static const uint32_t sides[] = {16, 24, 32, 48, 64, 80, 96};
   float best = 0;
-  uint32_t side = 0, sweeps = 0;
+  RunShape shape{0, 0};
   for (uint32_t t : sides) {
     uint64_t tiles = 0;
     for (const auto &z : sizes) tiles += z.second * ((z.first + t - 1) / t) * ((z.first + t - 1) / t);
@@ -614,11 +619,91 @@ bool plan_tile_run(TileRun &r) {
       const float us = tile_turn_us(t, s, tiles) * (float)((most + s - 1) / s);
       if (us > 0 && (best == 0 || us < best)) {
         best = us;
-        side = t;
-        sweeps = s;
+        shape = RunShape{t, s};
       }
     }
   }
+  return shape;
+}
+
+// Sweeps a turn of one job: at most the shape's, the ring's slots, and so few
+// that the lattice ends where it began where that can be had: a copy back costs
+// 3.5 us a job (64 jobs of L = 16: one turn of one sweep 0.30 ms, two turns of two
+// 0.09).
+static uint32_t job_sweeps(uint64_t total, uint64_t cap, uint32_t sweeps) {
+  const uint32_t most = sweeps < cap ? sweeps : (uint32_t)cap;
+  for (uint32_t per = most; per >= 1; --per)
+    if (((total + per - 1) / per) % 2 == 0) return per;
+  return most;
+}
+
+// Measured on MI355X over 1100 batches of 1 .. 4096 jobs of L = 16 .. 2048, q = 3 ..
+// 200, 1 .. 100 sweeps, and 60 mixed ones: by these estimates none of them takes a
+// route that is slower than its other one by more than 5 %.
+//
+// Tiles: a turn is the launch and the slowest CU.  Of a workgroup's time all but
+// the launch repeats for the tiles that a CU gets beyond those it holds at once
+// (16 waves), unless their issue times add up to more.  The folds of all sweeps add
+// 0.4 ns a wave of each fold workgroup, of which a job has (q + 1) / 8 a sweep:
+// 512 jobs of L = 64 take 1.3 ms at q = 9 and 8.5 at q = 200.
+float tile_run_us(const std::vector<SweepJob> &jobs) {
+  const RunShape shape = run_shape(jobs);
+  if (!shape.side) return 0;
+  const Lanes lanes = lanes_of(shape.side, shape.side, tile_halo_x(shape.sweeps), 2u * shape.sweeps);
+  uint64_t turns = 0, odd = 0, tiles = 0;  // tiles: of all turns
+  uint32_t per_most = 1, q = 0;
+  float folds = 0;
+  for (const SweepJob &p : jobs) {
+    const uint32_t per = job_sweeps(p.sweeps, p.cap, shape.sweeps);
+    const uint64_t n = (p.sweeps + per - 1) / per, side = (p.L + shape.side - 1) / shape.side;
+    turns = n > turns ? n : turns;
+    odd += n & 1u;
+    tiles += side * side * n;
+    per_most = per > per_most ? per : per_most;
+    q = p.q > q ? p.q : q;
+    folds += (float)p.sweeps * (float)((p.q + fold_width(p.q + 1u)) / fold_width(p.q + 1u));
+  }
+  const float s = (float)per_most, k = (float)((tiles + turns * 256u - 1u) / (turns * 256u));
+  const float n = (float)(lanes.ni * ((lanes.waves + 3u) / 4u)), held = lanes.waves > 8u ? 1.0f : 16.0f / (float)lanes.waves;
+  const float issue = 0.2f + 0.2f * n * (1.0f - s / ((float)shape.side + 4.0f * s));
+  const float one = 3.5f + 0.4f * n + 2.0f * s * (issue > 0.47f ? issue : 0.47f);
+  const float waits = 2.0f + k / held * (one - 2.0f), issues = 2.0f + k * (2.0f * s * issue + 0.3f * n);
+  float turn = one > waits ? one : waits;
+  turn = turn > issues ? turn : issues;
+  return 20.0f + 3.5f * (float)odd + (float)turns * (turn + (q <= 16u ? 2.0f : 4.0f)) + 4e-4f * (float)lanes.waves * folds;
+}
+
+// Every job's workgroup runs its sweeps alone (1.5 us for each round of its 256
+// lanes over the items, and the record), or shares its CU with others.
+float resident_us(const std::vector<SweepJob> &jobs) {
+  float chain = 0, load = 0;
+  for (const SweepJob &p : jobs) {
+    const float n = (float)p.sweeps, rounds = (float)((p.L * p.L + 4095u) / 4096u);
+    const float one = 0.7f + 1.52f * rounds + (p.q > 16u && p.q <= kPrivateHistMaxQ ? 0.03f * (float)p.q : 0.0f);
+    chain = n * one > chain ? n * one : chain;
+    load += n * (1.4f * rounds > 0.8f ? 1.4f * rounds : 0.8f);
+  }
+  return chain > load / 256.0f ? chain : load / 256.0f;
+}
+
+// Two launches a sweep, however few the sites, and 0.66 ps a site.
+float strip_us(const std::vector<SweepJob> &jobs) {
+  uint64_t most = 0;
+  uint32_t L = 0;
+  float sites = 0;
+  for (const SweepJob &p : jobs) {
+    most = p.sweeps > most ? p.sweeps : most;
+    L = p.L > L ? p.L : L;
+    sites += (float)p.sweeps * (float)p.L * (float)p.L;
+  }
+  return (float)most * (15.0f + 3.5f * (float)L / 1024.0f) + 0.66e-6f * sites;
+}
+
+bool plan_tile_run(TileRun &r) {
+  std::vector<SweepJob> all;
+  for (const TileParams &p : r.jobs) all.push_back(SweepJob{p.L, p.q, p.total, p.fold.cap});
+  const RunShape shape = run_shape(all);
+  const uint32_t side = shape.side, sweeps = shape.sweeps;
   if (!side) return false;
   const Lanes lanes = lanes_of(side, side, tile_halo_x(sweeps), 2u * sweeps);
   r.ni = lanes.ni;
@@ -631,12 +716,7 @@ bool plan_tile_run(TileRun &r) {
   std::vector<TileRef> folds;
   for (size_t j = 0; j < r.jobs.size(); ++j) {
     TileParams &p = r.jobs[j];
-    // sweeps a turn of this job: at most the shape's, the ring's slots, and so
-    // few that the lattice ends where it began where that can be had
-    uint32_t per = sweeps < p.fold.cap ? sweeps : (uint32_t)p.fold.cap;
-    const uint32_t most_per = per;
-    while (per > 1 && ((p.total + per - 1) / per) % 2 != 0) --per;
-    if (((p.total + per - 1) / per) % 2 != 0) per = most_per;
+    const uint32_t per = job_sweeps(p.total, p.fold.cap, sweeps);
     if (!set_tile_shape(p, side, side, per)) return false;
     const uint32_t tiles = p.tiles_x * p.tiles_y, turns = (uint32_t)((p.total + per - 1) / per);
     if (tiles > kTileMaxParts) return false;

@@ -81,6 +81,23 @@ struct TileRun {
   size_t lds = 0;
 };
 
+// What the routes of small lattices take, in microseconds, so that a batch or an
+// iteration of the serving loop goes the faster way (tiles.hip: the figures).
+struct SweepJob {
+  uint32_t L, q;
+  uint64_t sweeps, cap;  // cap: slots of its record ring
+};
+float tile_run_us(const std::vector<SweepJob> &jobs);  // one TileRun; 0: it has no shape
+float resident_us(const std::vector<SweepJob> &jobs);  // one launch of the LDS-resident kernel
+float strip_us(const std::vector<SweepJob> &jobs);     // a launch per colour and sweep
+// With as many jobs, the LDS-resident launch has a workgroup on every CU, and no
+// halo to recompute: tiles are not considered (256 jobs of L = 64 / 128 / 256, 100
+// sweeps, q = 9: 0.30 / 0.77 / 2.60 ms resident, 0.74 / 1.47 / 4.58 on tiles).
+constexpr size_t kTileJobs = 256;
+// Tiles are taken when their estimate is this much below the other route's,
+// which covers the errors of both.
+constexpr float kTileMargin = 0.9f;
+
 // Adds a lattice of L % 4 == 0 to the run: nsweeps sweeps from t0, lattice in
 // `spins`, `other` a buffer of its size, records to ring.
 void add_tile_job(TileRun &r, uint8_t *spins, uint8_t *other, uint32_t L, uint32_t q, uint64_t seed,

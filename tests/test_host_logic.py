@@ -16,13 +16,36 @@ def program(tmp_path_factory):
 
     def run(name, *args):
         exe = str(out / name)
+        if not os.path.exists(exe):
+            compile_program(name, exe)
+        return subprocess.run([exe, *map(str, args)], capture_output=True, text=True, check=True, timeout=120).stdout.split()
+
+    def compile_program(name, exe):
         subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-rdynamic", "-I", os.path.join(ROOT, "include"), "-o", exe,
                         os.path.join(ROOT, "tests", "native", name + ".cpp"), os.path.join(PKG, "libpotts.so"),
                         f"-Wl,-rpath,{PKG}", "-Wl,--allow-shlib-undefined"], check=True)
-        return subprocess.run([exe, *map(str, args)], capture_output=True, text=True, check=True, timeout=120).stdout.split()
 
     return run
 
 
 def test_batch_after_a_failed_allocation(program):
     assert program("batch_alloc") == ["runs", "6", "misplaced", "0"]
+
+
+# one launch: with a job on every CU (256), with the records of q = 200 to add up,
+# or for a single sweep, whole lattices in LDS are faster than tiles
+@pytest.mark.parametrize("count,L,q,n", [(512, 64, 9, 100), (512, 64, 200, 100), (256, 256, 9, 100), (128, 128, 200, 100),
+                                         (1000, 16, 9, 100), (24, 64, 9, 1), (96, 64, 9, 100)])
+def test_many_small_lattices_stay_in_lds(program, count, L, q, n):
+    assert program("batch_routes", count, L, q, n) == ["1"]
+
+
+@pytest.mark.parametrize("count,L,q,n", [(1, 256, 9, 100), (16, 256, 200, 100), (64, 192, 9, 100), (8, 128, 9, 100),
+                                         (4, 512, 9, 100), (1, 2048, 9, 100)])
+def test_few_lattices_take_tiles(program, count, L, q, n):
+    assert 1 < int(program("batch_routes", count, L, q, n)[0]) < n
+
+
+@pytest.mark.parametrize("count,L,q,n", [(64, 512, 9, 100), (48, 512, 200, 100), (300, 272, 9, 100), (1, 4096, 9, 100)])
+def test_many_larger_lattices_share_strip_launches(program, count, L, q, n):
+    assert 2 * n <= int(program("batch_routes", count, L, q, n)[0]) <= 2 * n + 4 + 2 * count
