@@ -453,7 +453,9 @@ void potts_batch_free(potts_batch *b);
  * gives exactly the bits it gives alone.
  */
 typedef struct {
-    int64_t hbm_budget;  /* bytes of lattices + record rings held at once (<= 0: 200 GiB) */
+    int64_t hbm_budget;  /* bytes of lattices + record rings, and of the multi-sweep
+                            launches' second lattices and totals where they fit
+                            beside them, held at once (<= 0: 200 GiB) */
     int32_t max_slots;   /* jobs on the device at once (<= 0: 256)              */
     int32_t quantum;     /* sweeps per job per iteration (<= 0: 32)             */
     void *hip_stream;    /* hipStream_t, NULL = the server's own stream         */

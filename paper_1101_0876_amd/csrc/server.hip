@@ -134,7 +134,7 @@ struct potts_server {
   potts::ResidentJob *d_res = nullptr;
   potts::StatsParams *d_stats = nullptr;
   // multi-sweep tile launches: descriptors, table, totals, and the second
-  // buffers of the iteration's lattices (at most kTileSites bytes)
+  // buffers of the iteration's lattices (at most kTileSites bytes), within the budget
   potts::TileParams *d_tjobs = nullptr;
   potts::TileRef *d_trefs = nullptr;
   uint32_t *d_tparts = nullptr;
@@ -169,6 +169,37 @@ bool reserve_dev(void **p, size_t *cap, size_t n, size_t size) {
   *p = q;
   *cap = want;
   return true;
+}
+
+// Bytes of the tile runs' buffers, which count against the HBM budget.
+size_t tile_bytes(const potts_server *s) { return s->cap_other + s->cap_tparts * sizeof(uint32_t); }
+
+// One of them with room for n entries (its contents are not kept); false: the
+// budget, or the memory, has no room beside the admitted jobs.
+bool reserve_tile(potts_server *s, void **p, size_t *cap, size_t n, size_t size) {
+  if (n <= *cap) return true;
+  const size_t used = s->used_bytes + tile_bytes(s) - *cap * size, budget = (size_t)s->cfg.hbm_budget;
+  if (used > budget || n > (budget - used) / size) return false;
+  const size_t want = std::min(std::max<size_t>(n, *cap * 2), (budget - used) / size);
+  if (*p) (void)hipFree(*p);
+  *p = nullptr;
+  *cap = 0;
+  if (hipMalloc(p, want * size) != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+    return false;
+  }
+  *cap = want;
+  return true;
+}
+
+// Gives them back to a job that needs the room (between iterations).
+void release_tiles(potts_server *s) {
+  for (void *p : {(void *)s->d_other, (void *)s->d_tparts})
+    if (p) (void)hipFree(p);
+  s->d_other = nullptr;
+  s->d_tparts = nullptr;
+  s->cap_other = s->cap_tparts = 0;
 }
 
 bool reserve_stage(potts_server *s, size_t bytes) {
@@ -530,7 +561,7 @@ int iterate(potts_server *s, std::string &err) {
   std::vector<potts::TileRun> runs;
   std::vector<std::vector<Job *>> run_jobs;
   size_t other_bytes = 0;
-  const bool tiles_ok = tile_L > 0 && reserve_dev((void **)&s->d_other, &s->cap_other, tile_sites, 1);
+  const bool tiles_ok = tile_L > 0 && reserve_tile(s, (void **)&s->d_other, &s->cap_other, tile_sites, 1);
   for (size_t k = 0; k < s->active.size(); ++k) {
     Job &j = *s->active[k];
     if (tiles_ok && j.req.L <= tile_L && step[k] > 0) {
@@ -558,7 +589,7 @@ int iterate(potts_server *s, std::string &err) {
     placed = placed && potts::plan_tile_run(r);
     parts_words += r.parts_words;
   }
-  placed = placed && reserve_dev((void **)&s->d_tparts, &s->cap_tparts, parts_words, sizeof(uint32_t));
+  placed = placed && reserve_tile(s, (void **)&s->d_tparts, &s->cap_tparts, parts_words, sizeof(uint32_t));
   if (placed) {
     parts_words = 0;
     for (potts::TileRun &r : runs) {
@@ -924,6 +955,7 @@ void server_loop(potts_server *s) {
         std::unique_ptr<Job> jp = std::move(s->queue.front());
         s->queue.pop_front();
         lk.unlock();
+        if (s->used_bytes + jp->bytes + tile_bytes(s) > (size_t)s->cfg.hbm_budget) release_tiles(s);
         std::string err;
         if (!admit(s, *jp, err)) {
           fail_all(s, POTTS_ENOMEM, err);

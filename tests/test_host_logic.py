@@ -49,3 +49,14 @@ def test_few_lattices_take_tiles(program, count, L, q, n):
 @pytest.mark.parametrize("count,L,q,n", [(64, 512, 9, 100), (48, 512, 200, 100), (300, 272, 9, 100), (1, 4096, 9, 100)])
 def test_many_larger_lattices_share_strip_launches(program, count, L, q, n):
     assert 2 * n <= int(program("batch_routes", count, L, q, n)[0]) <= 2 * n + 4 + 2 * count
+
+
+# tables of jobs and workgroups come on top: a few KiB
+@pytest.mark.parametrize("jobs", [1, 2, 3, 4, 6])
+def test_served_jobs_keep_to_the_budget(program, jobs):
+    assert int(program("serve_budget", jobs)[0]) <= 64
+
+
+def test_served_jobs_take_tiles_within_the_budget(program):
+    strips, tiles = (int(program("serve_budget", jobs)[1]) for jobs in (4, 16))
+    assert 0 < tiles < strips
