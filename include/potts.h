@@ -175,8 +175,8 @@ int potts_sweep_heatbath_thr(potts_state *s, const uint32_t thr[4], int64_t nswe
  * kernel; the automatic choice for such L, and for L = 80 and 96),
  * 7 = persistent sweeps on LDS bands (L % 32 == 0, L <= 16384, a band shape
  * from potts_tune_band whose grid the GPU holds at once; the automatic choice
- * for 4032 < L <= 4096, and for calls of 48 sweeps and more at L = 2048, when
- * it can take the lattice): each workgroup keeps
+ * for L = 4096, and at L = 2048 for calls of 32 sweeps and more, 16 once it has
+ * run, when it can take the lattice): each workgroup keeps
  * a band of whole rows of the colour-split lattice in LDS for up to 64 sweeps
  * per cooperative launch and trades its two edge rows with the neighbouring
  * bands after every half sweep (an exchange buffer of 4 x L x L / rows bytes,

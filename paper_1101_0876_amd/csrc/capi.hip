@@ -501,17 +501,22 @@ bool band_ok(potts_state *s) {
   return s->L % 32 == 0 && s->L <= 16384 && band_shape(s, &rows, &block);
 }
 
-// The automatic choice for 4032 < L <= 4096 (L = 4096 16.3 us per sweep, q = 6;
-// tiles 21.9, the colour-split kernel 25.4) and, for calls of 48 sweeps and more
-// outside stream capture, at L = 2048 (5.8, tiles 7.3; on a new state, which has
-// the exchange buffer and the planes to set up, 47 sweeps 335 us against 377, 16
-// sweeps 178 against 150): there bands of 16 and 8 rows give every CU the
-// same whole number of items per lane.  Between, bands leave CUs or lanes idle (L =
-// 1984 8.5, tiles 7.0; 3072 14.9, 12.7; 3968 25, 21.4), and from L = 8192 no band
-// of whole rows whose grid the GPU holds at once fits in LDS.
+// The automatic choice where the rows of a band are whole waves of items (L / 32 a
+// multiple of 64: elsewhere a wave spans rows of both parities and runs the
+// update twice) and the bands of whole rows fit in LDS: L = 2048 and 4096.
+// Measured on MI355X (us per sweep, 128 sweeps a call, q = 6 / 24 / 96 / 200; tiles
+// in brackets, and the colour-split kernel): L = 4096 16.3 / 16.5 / 17.6 / 18.8 (21.7 /
+// 23.1 / 22.8 / 24.7; 25.0 / 27.1 / 25.2 / 28.6), 2048 5.7 / 6.3 / 6.0 / 6.3 (7.5 / 7.9 / 8.0 /
+// 8.5), 4064 27.5 / 28.3 / 28.4 / 31.0 (21.8 / 23.2 / 22.9 / 24.8).  From L = 8192
+// no band of whole rows whose grid the GPU holds at once fits in LDS.
+// A launch costs more than the tiles': at L = 2048, outside stream capture, calls
+// of 16 sweeps and more (q = 6 / 200: 8 sweeps 71 / 83 us, tiles 71 / 81; 16 115 / 130,
+// 142 / 165), of 32 on a state that has the exchange buffer and the planes still to
+// set up (24 sweeps 202 / 227 us, 197 / 235; 32 251 / 269, 261 / 304).
 bool auto_band(potts_state *s, int64_t nsweeps) {
-  const bool size = (s->L > 4032 && s->L <= 4096) || (s->L == 2048 && nsweeps >= 48 && !capturing(s));
-  return size && band_ok(s);
+  if (s->L % 2048 || s->L > 4096) return false;
+  if (s->L == 2048 && (capturing(s) || nsweeps < (s->bxbuf ? 16 : 32))) return false;
+  return band_ok(s);
 }
 
 bool use_band(potts_state *s, int64_t nsweeps) {

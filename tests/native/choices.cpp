@@ -1,0 +1,30 @@
+// Launches of the sweep calls argv[4..] (sweeps each) of one lattice without a
+// GPU (fake_hip.hpp): argv[1] "square" or "cube", L, q.  Prints, per call, plain
+// and cooperative launches.  A colour-split sweep is two launches, the pack and
+// the unpack one each; 64 band sweeps are one cooperative launch and a fold.
+#include <stdio.h>
+
+#include "fake_hip.hpp"
+
+#include "potts.h"
+
+int main(int argc, char **argv) {
+  if (argc < 5) return 2;
+  const bool cube = argv[1][0] == 'c';
+  potts_state *s = nullptr;
+  potts3d_state *c = nullptr;
+  if (cube ? potts3d_init(atoi(argv[2]), atoi(argv[3]), 1, POTTS_RANDOM, &c)
+           : potts_init(atoi(argv[2]), atoi(argv[3]), 1, POTTS_RANDOM, &s))
+    return 1;
+  for (int k = 4; k < argc; ++k) {
+    fake::launches = fake::cooperative = 0;
+    const int n = atoi(argv[k]);
+    if (cube ? potts3d_sweep(c, 0.5, n) : potts_sweep(s, 1.0, n)) return 1;
+    printf("%ld+%ld\n", fake::launches, fake::cooperative);
+  }
+  if (cube)
+    potts3d_free(c);
+  else
+    potts_free(s);
+  return 0;
+}

@@ -23,7 +23,7 @@ inline std::mutex mu;
 inline std::map<void *, size_t> held;  // device memory
 inline size_t now = 0, peak = 0;
 inline long allocations = 0, fail_at = -1;  // hipMalloc number fail_at fails
-inline long launches = 0;
+inline long launches = 0, cooperative = 0;
 inline std::vector<Copy> device_copies, host_copies;
 
 inline int alloc(void **p, size_t n) {
@@ -100,7 +100,7 @@ struct Dim {
   uint32_t x, y, z;
 };
 int hipLaunchKernel(const void *, Dim, Dim, void **, size_t, void *) { return ++fake::launches, 0; }
-int hipLaunchCooperativeKernel(const void *, Dim, Dim, void **, unsigned, void *) { return 0; }
+int hipLaunchCooperativeKernel(const void *, Dim, Dim, void **, unsigned, void *) { return ++fake::cooperative, 0; }
 int __hipPushCallConfiguration(Dim, Dim, size_t, void *) { return 0; }
 int __hipPopCallConfiguration(Dim *g, Dim *b, size_t *lds, void **s) {
   *g = *b = Dim{1, 1, 1};

@@ -60,3 +60,18 @@ def test_served_jobs_keep_to_the_budget(program, jobs):
 def test_served_jobs_take_tiles_within_the_budget(program):
     strips, tiles = (int(program("serve_budget", jobs)[1]) for jobs in (4, 16))
     assert 0 < tiles < strips
+
+
+def calls(program, *args):
+    """(plain, cooperative) launches of each sweep call"""
+    return [tuple(map(int, x.split("+"))) for x in program("choices", *args)]
+
+
+# bands: one cooperative launch for up to 64 sweeps.  L = 4064, whose rows are no
+# whole waves of items, is faster on tiles; at L = 2048 they are from 16 sweeps on,
+# 32 on a new state
+def test_band_choice(program):
+    assert [c for _, c in calls(program, "square", 4096, 6, 1, 64, 65)] == [1, 1, 2]
+    assert [c for _, c in calls(program, "square", 4064, 6, 1, 64)] == [0, 0]
+    assert [c for _, c in calls(program, "square", 1984, 6, 64)] == [0]
+    assert [c for _, c in calls(program, "square", 2048, 200, 31, 32, 15, 16)] == [0, 1, 0, 1]
