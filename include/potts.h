@@ -155,15 +155,15 @@ int potts_sweep_heatbath_thr(potts_state *s, const uint32_t thr[4], int64_t nswe
  * lattice in LDS and runs all sweeps of a call in one launch), 4 = the
  * colour-split kernel (L % 32 == 0, L <= 65520: a call copies the lattice into
  * two colour planes in the second buffer, sweeps there and copies it back;
- * the automatic choice above 4736, for calls of one sweep above 3584, where
- * kernel 7 does not take the lattice; there it takes L % 32 != 0 too, on planes
- * of its own, allocated on first use),
+ * the automatic choice above 4736, and above 3584 for calls that kernels 5 and 7
+ * do not take; there it takes L % 32 != 0 too, on planes of its own, allocated on
+ * first use),
  * 5 = the multi-sweep tile kernel (to be asked for, L % 16 == 0 and L <=
- * 65520; the automatic choice, for any L, up to 3584, up to 4736 for calls of
- * several sweeps, where kernels 6 and 7 do not take it, outside stream
- * capture: each
- * launch runs several sweeps, one LDS tile
- * per workgroup whose halo is recomputed, and moves the row-major lattice
+ * 65520; the automatic choice, for any L, up to 3584 and, for calls of several
+ * sweeps, up to 4608 (4736 with caller-owned buffers or L % 32 != 0), where
+ * kernels 6 and 7 do not take it, outside stream capture: each launch runs
+ * several sweeps, one LDS tile per workgroup whose halo is recomputed, and moves
+ * the row-major lattice
  * between the state's two buffers; with library-owned buffers they trade
  * roles, so potts_device_spins may return the other one afterwards; shape
  * from potts_tune_tiles), 6 = the LDS-resident kernel with its random words

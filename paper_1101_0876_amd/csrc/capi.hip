@@ -332,7 +332,10 @@ bool use_drawn(const potts_state *s, int64_t nsweeps) {
   return s->drawn || potts::drawn_inline((uint32_t)s->L, nsweeps) || !capturing(s);
 }
 
-// kernel 0: under stream capture, where the tiles leave it to this kernel
+// kernel 0: where the tiles leave it to this kernel, under stream capture and for
+// one sweep of L = 112, whose single launch is shorter than a tile launch and its
+// fold (8.0 us a call against 9.2; two sweeps 13.3 against 9.0, L = 128 8.8 either
+// way), unless the tiles leave the record in host memory
 bool use_resident(const potts_state *s) {
   return resident_ok(s) && (s->kernel == 3 || s->kernel == 6 || s->kernel == 0);
 }
@@ -413,13 +416,22 @@ bool tiles_ok(const potts_state *s) {
 // us per sweep, 200 sweeps a call; in brackets what else takes the size): L =
 // 100 1.6 (one launch per half sweep 5.6), 256 1.6 (LDS-resident 21.9), 512
 // 1.8 (colour-split 12.1), 1000 3.2 (chunk 29.8), 1024 3.2 (colour-split
-// 12.0), 2048 7.3 (bands 5.8, see auto_band), 2560 10.1 (bands 14.5), 3584 17.4 (bands 17.8),
-// 3968 21.4 (bands 25.8), 4224 23.1 (colour-split 32.2), 4608 27.8 (31.1), 4864
-// 32.6 (31.4).  A call of one sweep recomputes its halo for nothing: there the
-// colour-split kernel takes over above 3584 (41 against 47 us a call at L =
-// 3968).
+// 12.0), 2048 7.3 (bands 5.8, see auto_band), 2560 10.1 (bands 14.5), 3584 17.4
+// (bands 17.8), 3968 21.4 (bands 25.8), 4224 23.1 (colour-split 28.8).  At q = 24 /
+// 96 / 200 (128 sweeps a call): L = 1984 7.8 / 7.9 / 8.4 (colour-split 15.0 / 16.4 /
+// 21.0), 4032 23.1 / 22.9 / 24.7 (27.4 / 25.3 / 28.8).
+// Above 3584 the halo of a short call is recomputed for little: colour-split takes
+// calls of one sweep (us a call, tiles in brackets: L = 3968 29 (35), 4512 31 (42)),
+// above 4320 of two (4128 61 (57), 4320 59 (59), 4512 59 (64); three there 87 (86))
+// and, where the planes hold the lattice, which tiles would unpack first (8 us and
+// as much to pack again), up to three.  From L = 4640 on it takes all calls (two
+// sweeps 66 (75), five 159 (172), 16 501 (495)).  Where every colour-split call
+// packs or unpacks, tiles take calls of two sweeps and lattices up to L = 4736.
 bool auto_tiles(const potts_state *s, int64_t nsweeps) {
-  return !drawn_ok(s) && (s->L <= 3584 || (s->L <= 4736 && nsweeps > 1));
+  if (drawn_ok(s)) return false;
+  const bool converts = s->L % 32 || !s->owns_spins || s->home == kRows;
+  const int64_t least = !converts && !s->spins_valid ? 4 : converts || s->L <= 4320 ? 2 : 3;
+  return s->L <= 3584 || (s->L <= (converts ? 4736 : 4608) && nsweeps >= least);
 }
 
 // Whether the state's stream is being captured into a graph.  There the sizes
@@ -447,6 +459,7 @@ void note_capture(potts_state *s, bool on_planes) {
 bool use_tiles(const potts_state *s, int64_t nsweeps) {
   if (s->kernel == 5) return tiles_ok(s);
   if (s->kernel != 0 || s->home == kPlanes || !auto_tiles(s, nsweeps)) return false;
+  if (nsweeps == 1 && s->L < 128 && resident_ok(s) && !s->mirror) return false;
   return !capturing(s) || (s->L > 256 && s->L < 2048 && s->L % 16 == 0 && s->spins_valid);
 }
 

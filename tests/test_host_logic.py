@@ -75,3 +75,19 @@ def test_band_choice(program):
     assert [c for _, c in calls(program, "square", 4064, 6, 1, 64)] == [0, 0]
     assert [c for _, c in calls(program, "square", 1984, 6, 64)] == [0]
     assert [c for _, c in calls(program, "square", 2048, 200, 31, 32, 15, 16)] == [0, 1, 0, 1]
+
+
+# Launches of a call: colour-split 2 a sweep, a cleared record and a fold, and 1 to
+# pack the rows; tiles one for up to eight sweeps and a fold, and 1 to unpack the
+# planes.  Calls of one sweep and longer ones do not move the lattice back and
+# forth, and L = 4640 takes the planes only.
+def test_short_calls_stay_where_the_lattice_is(program):
+    assert [n for n, _ in calls(program, "square", 4512, 6, 1, 2, 3, 1)] == [5, 6, 8, 4]
+    assert calls(program, "square", 4512, 6, 3)[0][0] < 6
+    assert calls(program, "square", 4128, 6, 2)[0][0] < 6
+    assert calls(program, "square", 4128, 6, 1, 16)[1][0] < 16
+    assert calls(program, "square", 4640, 6, 16)[0][0] == 35
+
+
+def test_one_sweep_of_a_small_lattice(program):
+    assert [n for n, _ in calls(program, "square", 112, 6, 1, 2)] == [1, 2]  # LDS-resident; a tile launch and its fold
