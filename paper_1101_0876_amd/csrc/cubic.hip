@@ -251,13 +251,18 @@ void release(potts3d_state *s) {
 bool packed_ok(const potts3d_state *s) { return s->L % 32 == 0; }
 
 // The automatic choice: the colour-split kernel where L % 32 == 0, and from L =
-// 68 for every L (partial items): the chunk kernel's launches all end in one
-// line of atomics and its bytes are merged one by one.  Measured on MI355X (q =
-// 3, us per sweep, the chunk kernel in brackets): L = 60 14.3 (11.5), 100 13.9
-// (32.0), 200 27.8 (124), 300 42.8 (158), 1000 1010 (3140).  Without memory
-// for the second copy the chunk kernel sweeps such an L in place.
-bool use_packed(const potts3d_state *s) {
-  return s->kernel == 1 || (s->kernel == 0 && (packed_ok(s) || (s->L > 64 && !s->no_planes)));
+// 72 for every L (partial items): the chunk kernel's launches all end in one
+// line of atomics and its bytes are merged one by one.  A call ends with the rows
+// made current again, so single sweeps go there from L = 80.  Measured on MI355X
+// (us a call of 1 / 2 / 50 sweeps, the chunk kernel in brackets): q = 3 L = 68 19.5 /
+// 32 / 688 (16.1 / 31 / 718), 72 19.8 / 33 / 702 (17.6 / 34 / 792), 80 20.1 / 34 / 699
+// (21.1 / 41 / 973), 100 20 / 35 / 704 (34 / 67 / 1610); q = 200 L = 68 22.6 / 40 / 867 (19.2 /
+// 35 / 786), 72 23.1 / 39 / 852 (19.7 / 37 / 873), 80 21.9 / 38 / 813 (23.1 / 45 / 1072);
+// q = 3 us per sweep L = 200 27.8 (124), 300 42.8 (158), 1000 1010 (3140).  Without
+// memory for the second copy the chunk kernel sweeps such an L in place.
+bool use_packed(const potts3d_state *s, int64_t nsweeps) {
+  if (s->kernel == 1) return true;
+  return s->kernel == 0 && (packed_ok(s) || (s->L >= (nsweeps > 1 ? 72 : 80) && !s->no_planes));
 }
 
 bool capturing(const potts3d_state *s) {
@@ -309,7 +314,7 @@ int run(potts3d_state *s, const uint32_t thr[6], int64_t nsweeps) {
   const int64_t rl = s->q + 1;
   // a graph's replays, and the calls after it, sweep such a cube where it is
   if (!packed_ok(s) && capturing(s)) s->no_planes = true;
-  bool packed = use_packed(s);
+  bool packed = use_packed(s, nsweeps);
   int rc = packed ? sync_planes(s) : sync_spins(s);
   if (rc == POTTS_ENOMEM && s->kernel == 0 && !packed_ok(s)) {
     packed = false;

@@ -91,3 +91,10 @@ def test_short_calls_stay_where_the_lattice_is(program):
 
 def test_one_sweep_of_a_small_lattice(program):
     assert [n for n, _ in calls(program, "square", 112, 6, 1, 2)] == [1, 2]  # LDS-resident; a tile launch and its fold
+
+
+# cubes: the chunk kernel has 2 launches a sweep and one to clear the record, the
+# colour-split kernel a fold, a pack and an unpack besides the 2 a sweep
+def test_small_cubes(program):
+    for L, want in ((68, [3, 5, 101]), (72, [3, 7, 102]), (76, [3, 7, 102]), (80, [5, 6, 102])):
+        assert [n for n, _ in calls(program, "cube", L, 200, 1, 2, 50)] == want, L
