@@ -82,10 +82,12 @@ struct potts_state {
   size_t tparts_words = 0;
   std::vector<uint32_t *> old_tparts;      // outgrown, named by captured launches
   uint32_t last_tx = 0, last_ty = 0, last_sweeps = 0;  // automatic shape of the call before
-  // pinned host memory, from the first potts_observables on, that takes the last
-  // sweep's record with the ring (kernels 5 and 6): sweep mirror_t's once the
-  // stream has been synchronized, -1: none
+  // pinned host memory that takes the last sweep's record with the ring (kernels 5
+  // and 6): sweep mirror_t's once the stream has been synchronized, -1: none, -2:
+  // none, but the last call would have left it there.  Allocated after as many
+  // copies instead (copied) as potts_observables says.
   unsigned long long *mirror = nullptr;
+  uint32_t copied = 0;
   int64_t mirror_t = -1;
   // pre-drawn random words of a chunk of sweeps (drawn.hpp), allocated on first use
   uint32_t *drawn = nullptr;
@@ -621,13 +623,14 @@ int run_resident(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     HIP_TRY(potts::launch_resident(p, 1, j.L, j.q, wide_table(thr), s->stream));
   }
   s->t += nsweeps;
+  if (s->kernel == 0 && !capturing(s)) s->mirror_t = -2;  // with host memory for the record, tiles take the call
   return POTTS_OK;
 }
 
 // The host copy of the last record that a call's launches may write (not under
 // stream capture: a replay would write it again later), and its sweep.
 unsigned long long *mirror_of(const potts_state *s) { return capturing(s) ? nullptr : s->mirror; }
-void note_mirror(potts_state *s) { s->mirror_t = mirror_of(s) ? s->t - 1 : -1; }
+void note_mirror(potts_state *s) { s->mirror_t = mirror_of(s) ? s->t - 1 : capturing(s) ? -1 : -2; }
 
 // The same with the random words drawn first by a generator kernel over the
 // whole GPU, kDrawnChunk sweeps at a time.
@@ -1440,6 +1443,11 @@ int potts_measure(potts_state *s, potts_obs *out) {
   return POTTS_OK;
 }
 
+// The host copy saves 9 us of a step of 24 (L = 64, one sweep and its observables);
+// allocating it takes 18 and freeing it 12: a program that looks at a new lattice
+// a few times does not pay for it.
+constexpr uint32_t kObservations = 4;
+
 int potts_observables(potts_state *s, potts_obs *out) {
   if (!s || !out) return fail(POTTS_EINVAL, "NULL argument");
   if (s->t == 0 || s->rec_from >= s->t) return potts_measure(s, out);
@@ -1454,8 +1462,8 @@ int potts_observables(potts_state *s, potts_obs *out) {
   rc = copy_records(s, s->t - 1, 1, rec.data());
   if (rc) return rc;
   fill_obs(s, rec.data(), out);
-  if (!s->mirror && hipHostMalloc(reinterpret_cast<void **>(&s->mirror), (size_t)(s->q + 1) * 8,
-                                  hipHostMallocDefault) != hipSuccess) {
+  if (s->mirror_t == -2 && !s->mirror && ++s->copied >= kObservations &&
+      hipHostMalloc(reinterpret_cast<void **>(&s->mirror), (size_t)(s->q + 1) * 8, hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     s->mirror = nullptr;
   }

@@ -23,7 +23,7 @@ inline std::mutex mu;
 inline std::map<void *, size_t> held;  // device memory
 inline size_t now = 0, peak = 0;
 inline long allocations = 0, fail_at = -1;  // hipMalloc number fail_at fails
-inline long launches = 0, cooperative = 0;
+inline long launches = 0, cooperative = 0, host_allocations = 0;
 inline std::vector<Copy> device_copies, host_copies;
 
 inline int alloc(void **p, size_t n) {
@@ -64,7 +64,7 @@ int hipMalloc(void **p, size_t n) { return fake::alloc(p, n); }
 int hipMallocAsync(void **p, size_t n, void *) { return fake::alloc(p, n); }
 int hipFree(void *p) { return fake::release(p); }
 int hipFreeAsync(void *p, void *) { return fake::release(p); }
-int hipHostMalloc(void **p, size_t n, unsigned) { return (*p = calloc(1, n)) ? 0 : 2; }
+int hipHostMalloc(void **p, size_t n, unsigned) { return ++fake::host_allocations, (*p = calloc(1, n)) ? 0 : 2; }
 int hipHostFree(void *p) { return free(p), 0; }
 int hipMemcpy(void *d, const void *s, size_t n, int kind) { return fake::copy(d, s, n, kind); }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int kind, void *) { return fake::copy(d, s, n, kind); }

@@ -98,3 +98,10 @@ def test_one_sweep_of_a_small_lattice(program):
 def test_small_cubes(program):
     for L, want in ((68, [3, 5, 101]), (72, [3, 7, 102]), (76, [3, 7, 102]), (80, [5, 6, 102])):
         assert [n for n, _ in calls(program, "cube", L, 200, 1, 2, 50)] == want, L
+
+
+# the host copy of the last record: not for a lattice that is looked at a few
+# times, and never where the kernel does not fill it
+@pytest.mark.parametrize("L,want", [(64, "000111"), (112, "000111"), (1000, "000111"), (4864, "000000")])
+def test_pinned_record_after_some_observations(program, L, want):
+    assert "".join(program("observations", L)) == want
