@@ -51,7 +51,8 @@ struct potts_state {
   bool spins_valid = true;    // spins holds the current configuration
   bool planes_valid = false;  // the planes hold it, colour-split
   // the planes of L % 32 != 0, whose padded rows do not fit in spins2
-  // (allocated on first use; no_rag: there was no memory for them)
+  // (allocated on first use; no_rag: there was no memory for them, or the
+  // lattice's home is the rows)
   uint8_t *rag_planes = nullptr;
   bool no_rag = false;
   // a sweep call of the state was captured into a graph: its replays find the
@@ -150,8 +151,7 @@ int sync_spins(potts_state *s) {
 // Queued after the sweeps of a call: the lattice is where the next call and a
 // replay look for it.  Caller-owned buffers: the row-major lattice is current
 // after every call, and the next call packs it again, so writes between calls
-// are seen.  L % 32 != 0: it is current too, since a captured call works on it
-// in place.
+// are seen.
 int settle(potts_state *s) {
   if (s->home == kPlanes) {
     if (!s->planes_valid) HIP_TRY(potts::launch_pack(s->spins, planes_of(s), (uint32_t)s->L, s->stream));
@@ -159,12 +159,12 @@ int settle(potts_state *s) {
     s->spins_valid = false;
     return POTTS_OK;
   }
-  if (s->owns_spins && s->home != kRows && s->L % 32 == 0) return POTTS_OK;
+  if (s->owns_spins && s->home != kRows) return POTTS_OK;
   if (!s->spins_valid) {
     HIP_TRY(potts::launch_unpack(planes_of(s), s->spins, (uint32_t)s->L, s->stream));
     s->spins_valid = true;
   }
-  s->planes_valid = s->planes_valid && s->owns_spins && s->home != kRows;
+  s->planes_valid = false;
   return POTTS_OK;
 }
 
@@ -350,17 +350,25 @@ bool auto_tiles(const potts_state *s, int64_t nsweeps);
 // The colour-split kernel with partial items, the automatic choice for L % 32
 // != 0 above the tiles' range (q = 6, us per sweep on MI355X: L = 5000 33.6, the
 // chunk kernel 136; L = 6000 44.0, the strip kernel 59.0; L = 10000 95, 98).
-// Not under stream capture (it may have to allocate its planes) nor where there
-// was no memory for them.
+// Not where there was no memory for its planes, nor on a lattice whose home is
+// the rows (a captured call may not allocate).
+// On caller-owned buffers every call packs and unpacks the rows, 0.85 ps a site
+// more than the strip kernel (L % 16 == 0) has beside its sweeps: calls of fewer
+// sweeps than make up for it stay there (us a call, strip kernel in brackets: L =
+// 5008 n = 1 61 (52), 2 93 (98); 7184 3 224 (223), 5 345 (363); 10000 10 1026 (991);
+// 16016 10 2474 (2325); 32752 10 9785 (9868)).
 bool use_rag(const potts_state *s, int64_t nsweeps) {
-  return s->L % 32 != 0 && s->kernel == 0 && s->L <= 65520 && !s->no_rag && !auto_tiles(s, nsweeps) && !drawn_ok(s) &&
-         !capturing(s);
+  if (s->L % 32 == 0 || s->kernel != 0 || s->L > 65520) return false;
+  if (s->home == kPlanes) return true;
+  if (s->no_rag || auto_tiles(s, nsweeps) || drawn_ok(s)) return false;
+  return s->owns_spins || !strip_ok(s) || nsweeps >= (s->L <= 6144 ? 2 : s->L <= 7424 ? 4 : 24);
 }
 
-// Allocates the planes of L % 32 != 0; false: no memory, the kernels that
-// sweep in place take the lattice.
+// Allocates the planes of L % 32 != 0; false: no memory (or a captured call), the
+// kernels that sweep in place take the lattice.
 bool rag_ready(potts_state *s) {
   if (s->rag_planes) return true;
+  if (capturing(s)) return false;
   const size_t bytes = 2 * (size_t)s->L * potts::plane_pitch((uint32_t)s->L);
   if (hipMalloc(&s->rag_planes, bytes) == hipSuccess) return true;
   (void)hipGetLastError();
@@ -428,10 +436,10 @@ bool tiles_ok(const potts_state *s) {
 // and, where the planes hold the lattice, which tiles would unpack first (8 us and
 // as much to pack again), up to three.  From L = 4640 on it takes all calls (two
 // sweeps 66 (75), five 159 (172), 16 501 (495)).  Where every colour-split call
-// packs or unpacks, tiles take calls of two sweeps and lattices up to L = 4736.
+// packs and unpacks, tiles take calls of two sweeps and lattices up to L = 4736.
 bool auto_tiles(const potts_state *s, int64_t nsweeps) {
   if (drawn_ok(s)) return false;
-  const bool converts = s->L % 32 || !s->owns_spins || s->home == kRows;
+  const bool converts = !s->owns_spins || s->home == kRows;
   const int64_t least = !converts && !s->spins_valid ? 4 : converts || s->L <= 4320 ? 2 : 3;
   return s->L <= 3584 || (s->L <= (converts ? 4736 : 4608) && nsweeps >= least);
 }
@@ -450,12 +458,12 @@ bool capturing(const potts_state *s) {
 
 // A call that is being captured fixes the lattice's home: the planes if only
 // they hold it, or if they do and the call sweeps on them (on_planes), else the
-// rows.  L % 32 != 0, whose planes are never the only copy, is swept in place.
+// rows, where L % 32 != 0 is then swept in place for good.
 void note_capture(potts_state *s, bool on_planes) {
   if (!capturing(s)) return;
   s->captured = true;
-  s->no_rag = true;
   if (s->home == kAnywhere) s->home = !s->spins_valid || (s->planes_valid && on_planes) ? kPlanes : kRows;
+  s->no_rag = s->home == kRows;
 }
 
 bool use_tiles(const potts_state *s, int64_t nsweeps) {
@@ -1067,7 +1075,7 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     if (rc) return rc;
   }
   if (nsweeps == 0) return POTTS_OK;
-  note_capture(s, use_band(s, nsweeps) || use_packed(s, nsweeps));
+  note_capture(s, use_band(s, nsweeps) || use_packed(s, nsweeps) || use_rag(s, nsweeps));
   s->mirror_t = -1;
   const int rc = dispatch_sweeps(s, thr, nsweeps);
   return rc ? rc : settle(s);
@@ -1149,7 +1157,7 @@ bool heatbath_tiles(const potts_state *s, int64_t nsweeps) {
 // The colour-split kernel with partial items elsewhere (L = 5000 59.5, one
 // chunk per thread 146.9; 10000 173, 278), as use_rag.
 bool heatbath_rag(const potts_state *s) {
-  return s->L % 32 != 0 && s->kernel == 0 && s->L <= 65520 && !s->no_rag && !capturing(s);
+  return s->L % 32 != 0 && s->kernel == 0 && s->L <= 65520 && !s->no_rag;
 }
 
 bool heatbath_packed(const potts_state *s) {
@@ -1207,7 +1215,7 @@ int run_heatbath(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   if (nsweeps < 0) return fail(POTTS_EINVAL, "nsweeps must be >= 0");
   if (nsweeps > INT64_MAX - s->t) return fail(POTTS_ERANGE, "sweep counter overflow");
   if (nsweeps == 0) return POTTS_OK;
-  note_capture(s, !heatbath_tiles(s, nsweeps) && heatbath_packed(s));
+  note_capture(s, !heatbath_tiles(s, nsweeps) && (heatbath_packed(s) || heatbath_rag(s)));
   s->mirror_t = -1;
   const int rc = dispatch_heatbath(s, thr, nsweeps);
   return rc ? rc : settle(s);

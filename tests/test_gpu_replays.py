@@ -44,6 +44,11 @@ CASES = [
     (3616, True, 4, 1, (4,)),
     (3616, True, 1, 4, (1,)),
     (1024, True, 1, 1, (2, 1)),
+    (4740, False, 1, 1, (1,)),     # partial items, on planes of their own
+    (4740, False, 0, 1, (2,)),
+    (4100, False, 1, 5, (5,)),
+    (4100, False, 5, 1, (1,)),
+    (3620, True, 1, 1, (4,)),
 ]
 
 

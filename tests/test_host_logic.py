@@ -105,3 +105,15 @@ def test_small_cubes(program):
 @pytest.mark.parametrize("L,want", [(64, "000111"), (112, "000111"), (1000, "000111"), (4864, "000000")])
 def test_pinned_record_after_some_observations(program, L, want):
     assert "".join(program("observations", L)) == want
+
+
+# L % 32 != 0: the planes hold a lattice of the library's own between calls; in the
+# caller's buffers every call packs and unpacks, or stays in the strip kernel (a
+# cleared record, 2 a sweep and a fold) where it is too short to make up for it
+def test_ragged_planes(program):
+    assert [n for n, _ in calls(program, "square", 5008, 6, 1, 1, 2)] == [5, 4, 6]
+    assert [n for n, _ in calls(program, "square", 8016, 6, 1, 1)] == [5, 4]
+    assert [n for n, _ in calls(program, "buffers", 5008, 6, 1, 2)] == [4, 8]
+    assert [n for n, _ in calls(program, "buffers", 7184, 6, 3, 4)] == [8, 12]
+    assert [n for n, _ in calls(program, "buffers", 8016, 6, 23, 24)] == [48, 52]
+    assert [n for n, _ in calls(program, "buffers", 5012, 6, 1)] == [6]  # one 4-byte chunk a lane otherwise
