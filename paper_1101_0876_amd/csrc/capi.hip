@@ -434,13 +434,15 @@ bool tiles_ok(const potts_state *s) {
 // calls of one sweep (us a call, tiles in brackets: L = 3968 29 (35), 4512 31 (42)),
 // above 4320 of two (4128 61 (57), 4320 59 (59), 4512 59 (64); three there 87 (86))
 // and, where the planes hold the lattice, which tiles would unpack first (8 us and
-// as much to pack again), up to three.  From L = 4640 on it takes all calls (two
-// sweeps 66 (75), five 159 (172), 16 501 (495)).  Where every colour-split call
+// as much to pack again), up to three (4320 four 116 (98)) and seven (4512 six 169
+// (170), eight 225 (212)).  From L = 4640 on it takes all calls (two sweeps 66 (75),
+// five 159 (172), 16 501 (495)).  Where every colour-split call
 // packs and unpacks, tiles take calls of two sweeps and lattices up to L = 4736.
 bool auto_tiles(const potts_state *s, int64_t nsweeps) {
   if (drawn_ok(s)) return false;
   const bool converts = !s->owns_spins || s->home == kRows;
-  const int64_t least = !converts && !s->spins_valid ? 4 : converts || s->L <= 4320 ? 2 : 3;
+  const bool moves = !converts && !s->spins_valid;
+  const int64_t least = s->L <= 4320 ? (moves ? 4 : 2) : moves ? 8 : converts ? 2 : 3;
   return s->L <= 3584 || (s->L <= (converts ? 4736 : 4608) && nsweeps >= least);
 }
 
@@ -1147,11 +1149,13 @@ int run_heatbath_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) 
 // the L that are not multiples of 32, per chunk): L = 64 2.4 (17.5), 1000 4.9
 // (31.3), 1024 5.0 (19.6), 2000 12.6 (110), 2048 12.9 (21.2), 3072 23.0 (33.6),
 // 4096 41.5 (43.2); calls of one sweep at L = 3328 48.5 (51.1), 3584 57.6 (57.1),
-// of two at L = 4096 58.4 (51.7).  Not under stream capture: they may have to
-// allocate.
+// of two at L = 4096 58.4 (51.7).  Above 3584 a lattice on the planes stays there
+// for calls of fewer than twelve sweeps: moving it takes 16 us.  Not under stream
+// capture: they may have to allocate.
 bool heatbath_tiles(const potts_state *s, int64_t nsweeps) {
   if (capturing(s)) return false;
-  return s->kernel == 5 ? tiles_ok(s) : s->kernel == 0 && s->home != kPlanes && (s->L <= 3584 || (s->L <= 4096 && nsweeps > 3));
+  return s->kernel == 5 ? tiles_ok(s) : s->kernel == 0 && s->home != kPlanes &&
+                                          (s->L <= 3584 || (s->L <= 4096 && nsweeps >= (s->spins_valid ? 4 : 12)));
 }
 
 // The colour-split kernel with partial items elsewhere (L = 5000 59.5, one

@@ -1,6 +1,6 @@
 // Launches of the sweep calls argv[4..] (sweeps each) of one lattice without a
 // GPU (fake_hip.hpp): argv[1] "square", "buffers" (the same in the caller's
-// buffers) or "cube", L, q.  Prints, per call, plain and cooperative launches.  A colour-split sweep is two launches, the pack and
+// buffers), "heat bath" or "cube", L, q.  Prints, per call, plain and cooperative launches.  A colour-split sweep is two launches, the pack and
 // the unpack one each; 64 band sweeps are one cooperative launch and a fold.
 #include <stdio.h>
 
@@ -23,7 +23,7 @@ int main(int argc, char **argv) {
   for (int k = 4; k < argc; ++k) {
     fake::launches = fake::cooperative = 0;
     const int n = atoi(argv[k]);
-    if (cube ? potts3d_sweep(c, 0.5, n) : potts_sweep(s, 1.0, n)) return 1;
+    if (cube ? potts3d_sweep(c, 0.5, n) : argv[1][0] == 'h' ? potts_sweep_heatbath(s, 1.0, n) : potts_sweep(s, 1.0, n)) return 1;
     printf("%ld+%ld\n", fake::launches, fake::cooperative);
   }
   if (cube)

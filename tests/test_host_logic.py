@@ -82,10 +82,13 @@ def test_band_choice(program):
 # planes.  Calls of one sweep and longer ones do not move the lattice back and
 # forth, and L = 4640 takes the planes only.
 def test_short_calls_stay_where_the_lattice_is(program):
-    assert [n for n, _ in calls(program, "square", 4512, 6, 1, 2, 3, 1)] == [5, 6, 8, 4]
+    assert [n for n, _ in calls(program, "square", 4512, 6, 1, 2, 3, 7, 1)] == [5, 6, 8, 16, 4]
+    assert [n for n, _ in calls(program, "heat bath", 3968, 6, 1, 4, 11)] == [5, 10, 24]
+    assert calls(program, "heat bath", 3968, 6, 1, 16)[1][0] < 16
+    assert calls(program, "heat bath", 3968, 6, 4)[0][0] < 10
     assert calls(program, "square", 4512, 6, 3)[0][0] < 6
     assert calls(program, "square", 4128, 6, 2)[0][0] < 6
-    assert calls(program, "square", 4128, 6, 1, 16)[1][0] < 16
+    assert calls(program, "square", 4128, 6, 1, 4)[1][0] < 8
     assert calls(program, "square", 4640, 6, 16)[0][0] == 35
 
 
