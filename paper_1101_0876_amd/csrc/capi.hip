@@ -41,7 +41,9 @@ struct potts_state {
   bool have_thr = false;
   double thr_beta = 0.0;
   uint32_t thr[4] = {0, 0, 0, 0};
-  int kernel = 0;          // 0 automatic, 1 strip, 2 chunk, 3 LDS-resident, 4 colour-split, 5 tiles, 6 LDS-resident with pre-drawn words, 7 LDS bands
+  // 0 automatic, 1 strip, 2 chunk, 3 LDS-resident, 4 colour-split, 5 tiles, 6
+  // LDS-resident with pre-drawn words, 7 LDS bands
+  int kernel = 0;
   uint32_t rows = 0;       // strip rows per work item, 0 = automatic
   unsigned max_groups = 0; // persistent grid size, 0 = automatic
   uint32_t wpe = 0;        // colour-split kernel: waves per SIMD asked of the compiler (0 = its choice)

@@ -542,7 +542,9 @@ static hipError_t launch_d(const ResidentJob &j, const uint32_t *words, unsigned
   const uint32_t items = (j.L * j.L >> 3) / D, block = (items + 63u) & ~63u;
   const size_t lds = 4u * ((size_t)kDrawnGroup * drawn_set_words(j.q, PRIV) + 2u * D * items);
   const uint2 *w = reinterpret_cast<const uint2 *>(words);
-  auto kernel = D == 1 ? (w ? drawn_kernel<CMP, PRIV, MONO, false, 1> : drawn_kernel<CMP, PRIV, MONO, true, 1>) : (w ? drawn_kernel<CMP, PRIV, MONO, false, 2> : drawn_kernel<CMP, PRIV, MONO, true, 2>);
+  auto kernel = drawn_kernel<CMP, PRIV, MONO, false, 1>;
+  if (D == 1 && !w) kernel = drawn_kernel<CMP, PRIV, MONO, true, 1>;
+  if (D == 2) kernel = w ? drawn_kernel<CMP, PRIV, MONO, false, 2> : drawn_kernel<CMP, PRIV, MONO, true, 2>;
   if (lds > 48u * 1024u) {
     const hipError_t e =
         hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
