@@ -371,10 +371,12 @@ int potts_load(const char *path, potts_state **out);
  * together.  Each job gives exactly the spins and records it gives alone
  * (same seed, start, beta, sweeps): the random numbers depend on the site
  * and sweep only.  Jobs with L <= 256 run in the LDS-resident kernel (one
- * workgroup each, all sweeps in one launch); larger jobs share one strip
- * launch per colour and sweep through a workgroup tile table.  The remaining
- * launches of a run are captured in one hipGraph (resident and strip work as
- * two overlapping branches) and replayed.
+ * workgroup each, all sweeps in one launch) or, where that is estimated to be
+ * faster, in multi-sweep tile launches, and so does a whole small batch; larger
+ * jobs share one strip launch per colour and sweep through a workgroup tile
+ * table.  The remaining launches of a run other than the tiles' are captured in
+ * one hipGraph (resident and strip work as two overlapping branches) and
+ * replayed.
  */
 typedef struct {
     int32_t L, q;        /* L % 16 == 0, 16 <= L <= 65520; 2 <= q <= 256       */

@@ -50,7 +50,8 @@
 // flag per edge wave raised after its stores had completed, and records summed
 // between two barriers: 17.6), 2048 5.8 (8.4).  With the edge rows updated a
 // dword a lane by all waves and the edges fetched by the waves with the fewest
-// items: 16.8 and 6.7.  What is left above the large lattices' 0.82 ps per site
+// items: 16.8 and 6.7.  Two 8-row bands of 512 lanes a CU, one to cover the
+// other's barrier: 17.7 against 17.3 (q = 24 17.0, 16.6; 200 19.3, 18.9).  What is left above the large lattices' 0.82 ps per site
 // update (13.7 us) is the barrier of each half sweep: the waves of a SIMD start
 // and end together, and nothing covers their first reads and last items.
 #include <hip/hip_runtime.h>
