@@ -83,6 +83,7 @@ struct potts_state {
   uint32_t tile_tx = 0, tile_ty = 0, tile_sweeps = 0;
   uint32_t *tparts = nullptr;
   size_t tparts_words = 0;
+  bool no_tiles = false;                   // there was no memory for them: kernels that need none sweep
   std::vector<uint32_t *> old_tparts;      // outgrown, named by captured launches
   uint32_t last_tx = 0, last_ty = 0, last_sweeps = 0;  // automatic shape of the call before
   // pinned host memory that takes the last sweep's record with the ring (kernels 5
@@ -382,7 +383,7 @@ bool rag_ready(potts_state *s) {
 bool use_packed(const potts_state *s, int64_t nsweeps) {
   return packed_ok(s) &&
          (s->kernel == 4 ||
-          (s->kernel == 0 && (s->home == kPlanes || (!drawn_ok(s) && !auto_tiles(s, nsweeps)))));
+          (s->kernel == 0 && (s->home == kPlanes || (!drawn_ok(s) && (s->no_tiles || !auto_tiles(s, nsweeps))))));
 }
 
 bool use_strip(const potts_state *s) { return strip_ok(s) && (s->kernel == 1 || s->kernel == 0); }
@@ -472,7 +473,7 @@ void note_capture(potts_state *s, bool on_planes) {
 
 bool use_tiles(const potts_state *s, int64_t nsweeps) {
   if (s->kernel == 5) return tiles_ok(s);
-  if (s->kernel != 0 || s->home == kPlanes || !auto_tiles(s, nsweeps)) return false;
+  if (s->kernel != 0 || s->home == kPlanes || s->no_tiles || !auto_tiles(s, nsweeps)) return false;
   if (nsweeps == 1 && s->L < 128 && resident_ok(s) && !s->mirror) return false;
   return !capturing(s) || (s->L > 256 && s->L < 2048 && s->L % 16 == 0 && s->spins_valid);
 }
@@ -1013,8 +1014,17 @@ int dispatch_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
     s->spins_valid = true;
     s->planes_valid = false;
   }
-  if (use_drawn(s, nsweeps)) return run_drawn(s, thr, nsweeps);
-  if (use_tiles(s, nsweeps)) return run_tiles(s, thr, nsweeps);
+  // without memory for the words or the totals the automatic choice is a kernel
+  // that needs none
+  if (use_drawn(s, nsweeps)) {
+    const int rc = run_drawn(s, thr, nsweeps);
+    return rc == POTTS_ENOMEM && s->kernel == 0 ? run_resident(s, thr, nsweeps) : rc;
+  }
+  if (use_tiles(s, nsweeps)) {
+    const int rc = run_tiles(s, thr, nsweeps);
+    if (rc != POTTS_ENOMEM || s->kernel != 0) return rc;
+    s->no_tiles = true;
+  }
   if (use_resident(s)) return run_resident(s, thr, nsweeps);
   const int64_t rl = s->q + 1;
   HIP_TRY(potts::launch_fill_u64(s->records + (s->t % s->rec_cap) * rl, (uint64_t)rl, 0ull, s->stream));
@@ -1088,12 +1098,10 @@ int run_sweeps(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
 // The heat bath's draw table for thr in device memory, rebuilt and uploaded when
 // the thresholds change.
 int heatbath_table(potts_state *s, const uint32_t thr[4]) {
-  if (!s->hb_dev) {
-    if (hipMalloc(&s->hb_dev, sizeof(potts::HbTable)) != hipSuccess ||
-        hipHostMalloc(&s->hb_host, sizeof(potts::HbTable), hipHostMallocDefault) != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(POTTS_ENOMEM, "allocation of the heat-bath table failed");
-    }
+  if ((!s->hb_dev && hipMalloc(&s->hb_dev, sizeof(potts::HbTable)) != hipSuccess) ||
+      (!s->hb_host && hipHostMalloc(&s->hb_host, sizeof(potts::HbTable), hipHostMallocDefault) != hipSuccess)) {
+    (void)hipGetLastError();
+    return fail(POTTS_ENOMEM, "allocation of the heat-bath table failed");
   }
   if (!s->hb_valid || memcmp(s->hb_thr, thr, sizeof(s->hb_thr)) != 0) {
     // the previous upload from the host copy may still be queued
@@ -1155,7 +1163,7 @@ int run_heatbath_packed(potts_state *s, const uint32_t thr[4], int64_t nsweeps) 
 // for calls of fewer than twelve sweeps: moving it takes 16 us.  Not under stream
 // capture: they may have to allocate.
 bool heatbath_tiles(const potts_state *s, int64_t nsweeps) {
-  if (capturing(s)) return false;
+  if (capturing(s) || s->no_tiles) return false;
   return s->kernel == 5 ? tiles_ok(s) : s->kernel == 0 && s->home != kPlanes &&
                                           (s->L <= 3584 || (s->L <= 4096 && nsweeps >= (s->spins_valid ? 4 : 12)));
 }
@@ -1175,23 +1183,32 @@ bool heatbath_packed(const potts_state *s) {
 // sweep counter and records are shared with the Metropolis sweeps.
 int dispatch_heatbath(potts_state *s, const uint32_t thr[4], int64_t nsweeps) {
   const int64_t rl = s->q + 1;
-  const bool tiles = heatbath_tiles(s, nsweeps);
-  if (!tiles && (heatbath_packed(s) || (heatbath_rag(s) && rag_ready(s)))) {
-    const int rc = heatbath_table(s, thr);
-    if (rc) return rc;
-    HIP_TRY(potts::launch_fill_u64(s->records + (s->t % s->rec_cap) * rl, (uint64_t)rl, 0ull, s->stream));
-    return run_heatbath_packed(s, thr, nsweeps);
-  }
-  {
+  auto to_rows = [s] {
     const int rc = sync_spins(s);
     if (rc) return rc;
     s->spins_valid = true;
     s->planes_valid = false;
+    return POTTS_OK;
+  };
+  if (heatbath_tiles(s, nsweeps)) {
+    int rc = to_rows();
+    if (!rc) rc = heatbath_table(s, thr);
+    if (!rc) rc = run_tiles(s, thr, nsweeps, s->hb_dev);
+    if (rc != POTTS_ENOMEM) return rc;
+    s->no_tiles = true;
   }
-  if (tiles) {
-    const int rc = heatbath_table(s, thr);
+  if (heatbath_packed(s) || heatbath_rag(s)) {
+    int rc = heatbath_table(s, thr);
+    if (!rc && (s->L % 32 == 0 || rag_ready(s))) {
+      HIP_TRY(potts::launch_fill_u64(s->records + (s->t % s->rec_cap) * rl, (uint64_t)rl, 0ull, s->stream));
+      return run_heatbath_packed(s, thr, nsweeps);
+    }
+    if (rc && (rc != POTTS_ENOMEM || s->L % 32 == 0)) return rc;
+  }
+  // one 4-byte chunk a lane needs no memory
+  {
+    const int rc = to_rows();
     if (rc) return rc;
-    return run_tiles(s, thr, nsweeps, s->hb_dev);
   }
   HIP_TRY(potts::launch_fill_u64(s->records + (s->t % s->rec_cap) * rl, (uint64_t)rl, 0ull, s->stream));
   potts::SweepParams p{};

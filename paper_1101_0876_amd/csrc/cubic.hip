@@ -36,6 +36,7 @@ struct potts3d_state {
   uint8_t *spins = nullptr;   // row-major cube
   uint8_t *planes = nullptr;  // colour-split copy
   bool no_planes = false;     // L % 32 != 0: no memory for it, or calls were captured: the chunk kernel sweeps
+  bool no_parts = false;      // no memory for the totals: likewise, for any L
   uint32_t *parts = nullptr;  // totals of two sweeps of the colour-split kernel
   size_t parts_words = 0;
   std::vector<uint32_t *> old_parts;  // outgrown (a captured launch may name them)
@@ -262,7 +263,7 @@ bool packed_ok(const potts3d_state *s) { return s->L % 32 == 0; }
 // memory for the second copy the chunk kernel sweeps such an L in place.
 bool use_packed(const potts3d_state *s, int64_t nsweeps) {
   if (s->kernel == 1) return true;
-  return s->kernel == 0 && (packed_ok(s) || (s->L >= (nsweeps > 1 ? 72 : 80) && !s->no_planes));
+  return s->kernel == 0 && !s->no_parts && (packed_ok(s) || (s->L >= (nsweeps > 1 ? 72 : 80) && !s->no_planes));
 }
 
 bool capturing(const potts3d_state *s) {
@@ -342,6 +343,10 @@ int run(potts3d_state *s, const uint32_t thr[6], int64_t nsweeps) {
       s->parts_words = 0;
       if (hipMalloc(&s->parts, 2 * words * sizeof(uint32_t)) != hipSuccess) {
         (void)hipGetLastError();
+        if (s->kernel == 0) {
+          s->no_parts = true;
+          return run(s, thr, nsweeps);
+        }
         return fail(POTTS_ENOMEM, "device allocation of the record totals failed");
       }
       s->parts_words = 2 * words;

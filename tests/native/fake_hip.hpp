@@ -23,13 +23,14 @@ inline std::mutex mu;
 inline std::map<void *, size_t> held;  // device memory
 inline size_t now = 0, peak = 0;
 inline long allocations = 0, fail_at = -1;  // hipMalloc number fail_at fails
+inline bool fail_all = false;
 inline long launches = 0, cooperative = 0, host_allocations = 0;
 inline std::vector<Copy> device_copies, host_copies;
 
 inline int alloc(void **p, size_t n) {
   std::lock_guard<std::mutex> lock(mu);
   *p = nullptr;
-  if (allocations++ == fail_at) return 2;  // hipErrorOutOfMemory
+  if (allocations++ == fail_at || fail_all) return 2;  // hipErrorOutOfMemory
   *p = calloc(1, n ? n : 1);
   held[*p] = n;
   now += n;

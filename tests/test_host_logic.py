@@ -120,3 +120,14 @@ def test_ragged_planes(program):
     assert [n for n, _ in calls(program, "buffers", 7184, 6, 3, 4)] == [8, 12]
     assert [n for n, _ in calls(program, "buffers", 8016, 6, 23, 24)] == [48, 52]
     assert [n for n, _ in calls(program, "buffers", 5012, 6, 1)] == [6]  # one 4-byte chunk a lane otherwise
+
+
+# a kernel that needs no memory takes the lattice where there is none (L = 64's
+# drawn words, the bands and the planes of L^2 bytes apart)
+@pytest.mark.parametrize("kind,L,q,n", [("square", 80, 6, 10), ("square", 96, 200, 3), ("square", 112, 9, 5),
+                                        ("square", 100, 6, 9), ("square", 256, 40, 9), ("square", 1000, 6, 9),
+                                        ("square", 1024, 6, 9), ("square", 5008, 6, 2), ("square", 4740, 6, 2),
+                                        ("heat bath", 100, 6, 9), ("heat bath", 1000, 40, 2), ("heat bath", 4740, 6, 1),
+                                        ("cube", 100, 3, 4), ("cube", 60, 3, 4), ("nnn", 504, 9, 9), ("nnn", 4092, 200, 2)])
+def test_sweeps_without_memory(program, kind, L, q, n):
+    assert program("sweep_alloc", kind, L, q, n)[0] == "14/14"
