@@ -582,14 +582,18 @@ int iterate(potts_server *s, std::string &err) {
       other_bytes += (size_t)j.req.L * j.req.L;
     }
   }
-  // without a plan or memory for the totals the jobs go the other way
-  size_t parts_words = 0;
+  // without a plan or memory for totals and tables the jobs go the other way
+  size_t parts_words = 0, ntjobs = 0, ntrefs = 0;
   bool placed = !runs.empty();
   for (potts::TileRun &r : runs) {
     placed = placed && potts::plan_tile_run(r);
     parts_words += r.parts_words;
+    ntjobs += r.jobs.size();
+    ntrefs += r.refs.size();
   }
-  placed = placed && reserve_tile(s, (void **)&s->d_tparts, &s->cap_tparts, parts_words, sizeof(uint32_t));
+  placed = placed && reserve_tile(s, (void **)&s->d_tparts, &s->cap_tparts, parts_words, sizeof(uint32_t)) &&
+           reserve_dev((void **)&s->d_tjobs, &s->cap_tjobs, ntjobs, sizeof(potts::TileParams)) &&
+           reserve_dev((void **)&s->d_trefs, &s->cap_trefs, ntrefs, sizeof(potts::TileRef));
   if (placed) {
     parts_words = 0;
     for (potts::TileRun &r : runs) {
@@ -689,8 +693,6 @@ int iterate(potts_server *s, std::string &err) {
   if (!reserve_dev((void **)&s->d_strip, &s->cap_strip, desc.size(), sizeof(potts::StripParams)) ||
       !reserve_dev((void **)&s->d_tiles, &s->cap_tiles, tiles.size(), sizeof(potts::StripTile)) ||
       !reserve_dev((void **)&s->d_res, &s->cap_res, res.size(), sizeof(potts::ResidentJob)) ||
-      !reserve_dev((void **)&s->d_tjobs, &s->cap_tjobs, tjobs.size(), sizeof(potts::TileParams)) ||
-      !reserve_dev((void **)&s->d_trefs, &s->cap_trefs, trefs.size(), sizeof(potts::TileRef)) ||
       !reserve_dev((void **)&s->d_stats, &s->cap_stats, stats.size(), sizeof(potts::StatsParams))) {
     err = "descriptor table allocation failed";
     return POTTS_ENOMEM;

@@ -131,3 +131,7 @@ def test_ragged_planes(program):
                                         ("cube", 100, 3, 4), ("cube", 60, 3, 4), ("nnn", 504, 9, 9), ("nnn", 4092, 200, 2)])
 def test_sweeps_without_memory(program, kind, L, q, n):
     assert program("sweep_alloc", kind, L, q, n)[0] == "14/14"
+
+
+def test_served_job_without_memory_for_tiles(program):
+    assert program("serve_alloc") == ["0"] * 4
